@@ -30,31 +30,8 @@
 namespace rlbm {
 
 // ---------------------------------------------------------------------------
-// storage codecs
+// storage references
 // ---------------------------------------------------------------------------
-template <typename S>
-struct Codec;
-
-template <>
-struct Codec<double> {
-    static __device__ __forceinline__ double ld(const void* p, size_t idx, double) {
-        return static_cast<const double*>(p)[idx];
-    }
-    static __device__ __forceinline__ void st(void* p, size_t idx, double v, double) {
-        static_cast<double*>(p)[idx] = v;
-    }
-};
-
-template <>
-struct Codec<float> {
-    static __device__ __forceinline__ double ld(const void* p, size_t idx, double ref) {
-        return (double)static_cast<const float*>(p)[idx] + ref;
-    }
-    static __device__ __forceinline__ void st(void* p, size_t idx, double v, double ref) {
-        static_cast<float*>(p)[idx] = __double2float_rn(v - ref);
-    }
-};
-
 // FP32 deviation storage: population (l, i) is stored as its deviation from
 // s_l(y) G_li, where G_li is the zero-velocity equilibrium shape of lattice l
 // at the domain-mean initial state normalised to unit zeroth moment, and
@@ -1274,55 +1251,6 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
 // ---------------------------------------------------------------------------
 // boundary reconstruction (section 4)
 // ---------------------------------------------------------------------------
-// Equilibrium of lattice l at velocity i for the state (rho, Y, u, T)
-// (section 4.1, eqs. faEqGeneral, fEqGeneral, gEqGeneral).  With SPV the
-// species equilibria use per-species velocities us (the wall's local state,
-// eq. locua); otherwise the mixture velocity.
-template <int M, bool SPV>
-struct EqState {
-    double rho, th, U, T;
-    double u[3];
-    double Y[M];
-    double us[SPV ? M : 1][3];
-};
-
-template <int M, bool SPV>
-__device__ __forceinline__ void eq_prepare(MechC mc, EqState<M, SPV>& e, double T) {
-    e.T = T;
-    e.th = mc.R_univ * mix_inv_m<M>(mc, e.Y) * T;
-    e.U = mix_U<M>(mc, e.Y, T);
-}
-
-template <int M, int W, bool SPV>
-__device__ __forceinline__ double eq_value(MechC mc, const EqState<M, SPV>& e, int l, int slaved, int i) {
-    constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG;
-    const int c0 = cx_of(i), c1 = cy_of(i), c2 = cz_of(i);
-    if (l == LG) {
-        GeqAxis gx, gy, gz;
-        geq_axis(e.u[0], e.th, gx);
-        geq_axis(e.u[1], e.th, gy);
-        geq_axis(e.u[2], e.th, gz);
-        const double Wx = sel3d(c0, gx.W[0], gx.W[1], gx.W[2]), kx = sel3d(c0, gx.k[0], gx.k[1], gx.k[2]);
-        const double Wy = sel3d(c1, gy.W[0], gy.W[1], gy.W[2]), ky = sel3d(c1, gy.k[0], gy.k[1], gy.k[2]);
-        const double Wz = sel3d(c2, gz.W[0], gz.W[1], gz.W[2]), kz = sel3d(c2, gz.k[0], gz.k[1], gz.k[2]);
-        return e.rho * (e.U * Wx * Wy * Wz + kx * Wy * Wz + Wx * (ky * Wz + Wy * kz));
-    }
-    if (l == LF)
-        return e.rho * psi(c0, e.u[0], e.u[0] * e.u[0] + e.th) * psi(c1, e.u[1], e.u[1] * e.u[1] + e.th) *
-               psi(c2, e.u[2], e.u[2] * e.u[2] + e.th);
-    const int a = W ? l : l + (l >= slaved ? 1 : 0);
-    double Ya = 0.0, tha = 0.0, w0 = e.u[0], w1 = e.u[1], w2 = e.u[2];
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-        if (c == a) {
-            Ya = e.Y[c];
-            tha = mc.Ra[c] * e.T;
-            if constexpr (SPV) { w0 = e.us[c][0]; w1 = e.us[c][1]; w2 = e.us[c][2]; }
-        }
-    }
-    return e.rho * Ya * psi(c0, w0, w0 * w0 + tha) * psi(c1, w1, w1 * w1 + tha) * psi(c2, w2, w2 * w2 + tha);
-}
-
 // ---------------------------------------------------------------------------
 // k_boundary: reconstruction at interface nodes (section 4).  A block takes
 // 64 consecutive entries of the interface list (grouped by boundary type and
@@ -1805,28 +1733,107 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
 // ---------------------------------------------------------------------------
 // initial state, read-out, populations I/O, invariants
 // ---------------------------------------------------------------------------
+// The read-out kernels take k_update's split: three waves per 64 nodes, wave w
+// the nine velocities with c_z = w - 1.
+constexpr int IO_NODES = 64;
+constexpr int IO_THREADS = 3 * IO_NODES;
+
 // Node that pulls the population stored at slot (node, i): node + c_i,
-// wrapped on every axis (the placeholder rule of the pull offsets).
-__device__ __forceinline__ long long reader_of(const LatDev& L, long long node, int i) {
-    const int nx = L.nx, ny = L.ny, nz = L.nz;
-    const int x = (int)(node % nx);
-    const long long r = node / nx;
-    const int y = (int)(r % ny), z = (int)(r / ny);
-    const int xr = (x + cx_of(i) + nx) % nx, yr = (y + cy_of(i) + ny) % ny, zr = (z + cz_of(i) + nz) % nz;
-    return ((long long)zr * ny + yr) * nx + xr;
+// wrapped on every axis (the placeholder rule of the pull offsets o).
+__device__ __forceinline__ int reader_at(int node, const PullOff& o, int c0, int c1, int c2) {
+    return node + sel3(c0, o.x[2], 0, o.x[0]) + sel3(c1, o.y[2], 0, o.y[0]) + sel3(c2, o.z[2], 0, o.z[0]);
 }
 
-// Reference value of slot (node, i) of lattice l in buffer q (FP32 storage).
-template <int M, typename S, int W>
-__device__ __forceinline__ double slot_ref(const LatDev& L, int q, long long node, int l, int i) {
-    if constexpr (sizeof(S) == 8) {
-        return 0.0;
-    } else {
-        constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
-        const RLBM_CONST double* G = as_const(L.ref);
-        const RLBM_GLOBAL float* sc = scale_at(L, q, reader_of(L, node, i));
-        if (l == LG) return ref_g(sc[LG], sc[LF], G[l * Q + i], G[REF_K<NL> + i]);
-        return ref_of(sc[l], G[l * Q + i]);
+// The NL reference scales of node n in buffer q (FP32 storage), as whole
+// 16-byte loads (rss is a multiple of four floats).
+template <int NL>
+__device__ __forceinline__ void scales_of(const LatDev& L, int q, int n, float (&out)[NL]) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const RLBM_GLOBAL f4* p4 = reinterpret_cast<const RLBM_GLOBAL f4*>(scale_at(L, q, n));
+#pragma unroll
+    for (int v = 0; v < (NL + 3) / 4; ++v) {
+        const f4 w = p4[v];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (4 * v + e < NL) out[4 * v + e] = w[e];
+    }
+}
+
+// Moments of the stored populations of one node over the c_z = c2 layer: rho,
+// rho u, rho E and the stored species' rho_a.  Every load of a row of three
+// velocities is in flight together (NL populations and the reader's scales as
+// 16-byte loads), where a loop over single velocities waited for each.
+template <int M, int W>
+struct LayerSums {
+    static constexpr int N = 5 + Lat<M, W>::NSP;   // rho, j[3], rho E, rho_a
+    double v[N];
+};
+template <int M, typename S, int W, bool CHECK>
+__device__ __forceinline__ void layer_sums(const LatDev& L, int q, int node, int c2, LayerSums<M, W>& t, bool& bad) {
+    constexpr int NSP = Lat<M, W>::NSP, LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
+    const RLBM_GLOBAL S* src = as_global(static_cast<const S*>(L.pop[q]));
+    const size_t P = (size_t)L.P;
+    const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
+    PullOff o;
+    pull_offsets(L, x, y, z, o);
+#pragma unroll
+    for (int a = 0; a < LayerSums<M, W>::N; ++a) t.v[a] = 0.0;
+#pragma unroll 1
+    for (int c1 = -1; c1 <= 1; ++c1) {
+        const int i0 = 9 * (c2 + 1) + 3 * (c1 + 1);
+        S raw[3][NL];
+        float sc[3][NL];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+#pragma unroll
+            for (int l = 0; l < NL; ++l) raw[c][l] = ld_at(src + (size_t)(l * Q + i0 + c) * P, node);
+            if constexpr (sizeof(S) == 4) scales_of<NL>(L, q, reader_at(node, o, c - 1, c1, c2), sc[c]);
+        }
+        double m[NL], jx = 0.0;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) m[l] = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+#pragma unroll
+            for (int l = 0; l < NL; ++l) {
+                double v = (double)raw[c][l];
+                if constexpr (sizeof(S) == 4) {
+                    const RLBM_CONST double* G = as_const(L.ref) + opaque_zero();
+                    const int i = i0 + c;
+                    v += l == LG ? ref_g(sc[c][LG], sc[c][LF], G[LG * Q + i], G[REF_K<NL> + i]) : ref_of(sc[c][l], G[l * Q + i]);
+                }
+                if constexpr (CHECK) bad |= !isfinite(v);
+                m[l] += v;
+                if (l == LF) jx += c == 2 ? v : (c == 0 ? -v : 0.0);
+            }
+        }
+        t.v[0] += m[LF];
+        t.v[1] += jx;
+        t.v[2] += (double)c1 * m[LF];
+        t.v[3] += (double)c2 * m[LF];
+        t.v[4] += m[LG];
+#pragma unroll
+        for (int l = 0; l < NSP; ++l) t.v[5 + l] += m[l];
+    }
+}
+
+// The species densities of a node in species order from its layer sums (the
+// slaved one by difference, eq. strongest).
+template <int M, int W>
+__device__ __forceinline__ void species_of_sums(const LayerSums<M, W>& t, int s, double (&ra)[M]) {
+    double rs = t.v[0];
+#pragma unroll
+    for (int l = 0; l < Lat<M, W>::NSP; ++l) rs -= t.v[5 + l];
+#pragma unroll
+    for (int a = 0; a < M; ++a) {
+        if constexpr (W) ra[a] = t.v[5 + a];
+        else {
+            double v = rs;
+#pragma unroll
+            for (int l = 0; l < Lat<M, W>::NSP; ++l)
+                if (a != s && l == lat_of(a, s)) v = t.v[5 + l];
+            ra[a] = v;
+        }
     }
 }
 
@@ -1859,51 +1866,100 @@ __global__ __launch_bounds__(256) void k_scale_init(const LatDev* __restrict__ l
     so[LG] = __double2float_rn(rho * (mix_U<M>(mc, Y, T_in[node]) + 0.5 * usq));
 }
 
+// Initial populations: the equilibria of the given state, k_update's split
+// (three waves per 64 nodes, one c_z layer each).  A lattice's axis factors
+// are formed once and multiplied out over the layer's nine velocities; the
+// kernel is bound by its stores.  512x64x64, FP32 storage: 2.38 -> 1.21 ms
+// against one thread per node that evaluated every velocity from the state.
 template <int M, typename S, int W>
-__global__ __launch_bounds__(256) void k_init(const LatDev* __restrict__ lat, const double* __restrict__ rho_in,
-                                              const double* __restrict__ u_in, const double* __restrict__ T_in,
-                                              const double* __restrict__ Y_in) {
+__global__ __launch_bounds__(IO_THREADS) void k_init(const LatDev* __restrict__ lat, const double* __restrict__ rho_in,
+                                                     const double* __restrict__ u_in, const double* __restrict__ T_in,
+                                                     const double* __restrict__ Y_in) {
+    constexpr int NSP = Lat<M, W>::NSP, LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
     const LatDev& L = *lat;
-    const long long node = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (node >= L.N) return;
+    const int node = (int)blockIdx.x * IO_NODES + (int)threadIdx.x % IO_NODES;
+    const int c2 = __builtin_amdgcn_readfirstlane((int)threadIdx.x / IO_NODES) - 1;
+    if (node >= (int)L.N) return;
     MechC mc = *as_const(L.mech);
-    const size_t N = (size_t)L.N;
-    void* dst = L.pop[L.parity0];
-    EqState<M, false> e;
-    e.rho = rho_in[node];
-    const double T = T_in[node];
+    const size_t N = (size_t)L.N, P = (size_t)L.P;
+    const int s = W ? M : L.slaved;
+    RLBM_GLOBAL S* dst = as_global(static_cast<S*>(L.pop[L.parity0]));
+    const double rho = rho_in[node], T = T_in[node];
+    double u[3], Y[M];
 #pragma unroll
-    for (int dd = 0; dd < 3; ++dd) e.u[dd] = u_in[dd * N + node];
+    for (int d = 0; d < 3; ++d) u[d] = u_in[d * N + node];
 #pragma unroll
-    for (int a = 0; a < M; ++a) e.Y[a] = Y_in[a * N + node];
-    eq_prepare<M, false>(mc, e, T);
-    for (int l = 0; l < Lat<M, W>::NL; ++l)
-        for (int i = 0; i < Q; ++i) {
-            const int li = l * Q + i;
-            Codec<S>::st(dst, (size_t)li * L.P + node, eq_value<M, W, false>(mc, e, l, L.slaved, i),
-                         slot_ref<M, S, W>(L, L.parity0, node, l, i));
+    for (int a = 0; a < M; ++a) Y[a] = Y_in[a * N + node];
+    const double th = mc.R_univ * mix_inv_m<M>(mc, Y) * T;
+    const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
+    PullOff o;
+    pull_offsets(L, x, y, z, o);
+#pragma unroll 1
+    for (int l = 0; l < NL; ++l) {
+        double X[3], Yf[3], kx[3] = {0.0, 0.0, 0.0}, ky[3] = {0.0, 0.0, 0.0}, Zf, kz = 0.0, amp = rho, U = 1.0;
+        if (l == LG) {
+            GeqAxis gx, gy, gz;
+            geq_axis(u[0], th, gx);
+            geq_axis(u[1], th, gy);
+            geq_axis(u[2], th, gz);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) { X[c] = gx.W[c]; kx[c] = gx.k[c]; Yf[c] = gy.W[c]; ky[c] = gy.k[c]; }
+            Zf = sel3d(c2, gz.W[0], gz.W[1], gz.W[2]);
+            kz = sel3d(c2, gz.k[0], gz.k[1], gz.k[2]);
+            U = mix_U<M>(mc, Y, T);
+        } else {
+            double tl = th;
+            if (l < NSP) {
+                const int a = W ? l : l + (l >= s ? 1 : 0);
+                tl = mc.Ra[a] * T;
+                amp = rho * Y_in[a * N + node];
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                X[c] = psi(c - 1, u[0], u[0] * u[0] + tl);
+                Yf[c] = psi(c - 1, u[1], u[1] * u[1] + tl);
+            }
+            Zf = psi(c2, u[2], u[2] * u[2] + tl);
         }
+        const RLBM_CONST double* G = as_const(L.ref);
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const int c0 = j % 3, c1 = j / 3, i = 9 * (c2 + 1) + j;
+            const double wyz = Yf[c1] * Zf;
+            const double v = amp * (U * X[c0] * wyz + kx[c0] * wyz + X[c0] * (ky[c1] * Zf + Yf[c1] * kz));
+            RLBM_GLOBAL S* pl = dst + (size_t)(l * Q + i) * P;
+            if constexpr (sizeof(S) == 4) {
+                const int rd = reader_at(node, o, c0 - 1, c1 - 1, c2);
+                const RLBM_GLOBAL float* sc = scale_at(L, L.parity0, rd);
+                const double ref = l == LG ? ref_g(sc[LG], sc[LF], G[l * Q + i], G[REF_K<NL> + i]) : ref_of(sc[l], G[l * Q + i]);
+                st_at(pl, node, __double2float_rn(v - ref));
+            } else {
+                st_at(pl, node, v);
+            }
+        }
+    }
+    if (c2 != 0) return;
     double* aux = L.aux;
-    aux[AUX_RHO * N + node] = e.rho;
+    aux[AUX_RHO * N + node] = rho;
 #pragma unroll
     for (int dd = 0; dd < 3; ++dd) {
-        aux[(AUX_U + dd) * N + node] = e.u[dd];
-        aux[(AUX_PHI + dd) * N + node] = e.rho * e.u[dd] * (1.0 - 3.0 * e.th) - e.rho * e.u[dd] * e.u[dd] * e.u[dd];
+        aux[(AUX_U + dd) * N + node] = u[dd];
+        aux[(AUX_PHI + dd) * N + node] = rho * u[dd] * (1.0 - 3.0 * th) - rho * u[dd] * u[dd] * u[dd];
     }
     aux[AUX_T * N + node] = T;
 #pragma unroll
-    for (int a = 0; a < M; ++a) aux[(AUX_Y + a) * N + node] = e.Y[a];
+    for (int a = 0; a < M; ++a) aux[(AUX_Y + a) * N + node] = Y[a];
     if (L.n_if) {
         const int k = L.if_index[node];
         if (k >= 0 && L.if_out[k] >= 0) {
             const int ko = L.if_out[k];
             const size_t No = (size_t)L.n_out;
-            L.out_state[0 * No + ko] = e.rho;
+            L.out_state[0 * No + ko] = rho;
 #pragma unroll
-            for (int dd = 0; dd < 3; ++dd) L.out_state[(1 + dd) * No + ko] = e.u[dd];
+            for (int dd = 0; dd < 3; ++dd) L.out_state[(1 + dd) * No + ko] = u[dd];
             L.out_state[4 * No + ko] = T;
 #pragma unroll
-            for (int a = 0; a < M; ++a) L.out_state[(5 + a) * No + ko] = e.Y[a];
+            for (int a = 0; a < M; ++a) L.out_state[(5 + a) * No + ko] = Y[a];
         }
     }
 }
@@ -1954,53 +2010,53 @@ __global__ __launch_bounds__(512) void k_refs(const LatDev* __restrict__ lat, do
     }
 }
 
+// Macroscopic fields of the stored populations.  Bound by the populations'
+// read; the layers' sums meet in LDS and the first wave solves for T.
+// 512x64x64, FP32 storage: 2.41 -> 0.59 ms against one thread per node
+// looping over single velocities; 1024 nodes: 106 -> 8 us.
 template <int M, typename S, int W>
-__global__ __launch_bounds__(256) void k_fields(const LatDev* __restrict__ lat, long long t, double* rho_o,
-                                                double* u_o, double* T_o, double* Y_o, double* P_o) {
+__global__ __launch_bounds__(IO_THREADS) void k_fields(const LatDev* __restrict__ lat, long long t, double* rho_o,
+                                                       double* u_o, double* T_o, double* Y_o, double* P_o) {
+    constexpr int NV = LayerSums<M, W>::N;
+    __shared__ double part[2][NV][IO_NODES];
     const LatDev& L = *lat;
-    const long long node = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (node >= L.N) return;
-    MechC mc = *as_const(L.mech);
+    const int lane = (int)threadIdx.x % IO_NODES;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / IO_NODES);
+    const int n = (int)blockIdx.x * IO_NODES + lane;
     const size_t N = (size_t)L.N;
-    const int q = (L.parity0 + t) & 1;
-    const void* src = L.pop[q];
-    constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG;
-    const int s = W ? M : L.slaved;
-    double rho = 0.0, j[3] = {0.0, 0.0, 0.0}, rE = 0.0, ra[M];
-    for (int i = 0; i < Q; ++i) {
-        const double f = Codec<S>::ld(src, (size_t)(LF * Q + i) * L.P + node, slot_ref<M, S, W>(L, q, node, LF, i));
-        rho += f; j[0] += f * cx_of(i); j[1] += f * cy_of(i); j[2] += f * cz_of(i);
-        rE += Codec<S>::ld(src, (size_t)(LG * Q + i) * L.P + node, slot_ref<M, S, W>(L, q, node, LG, i));
-    }
-    double rs = rho;
+    const bool live = n < (int)N;
+    const int node = live ? n : 0;
+    LayerSums<M, W> m;
+    bool bad = false;
+    layer_sums<M, S, W, false>(L, (int)((L.parity0 + t) & 1), node, w - 1, m, bad);
+    if (w) {
 #pragma unroll
-    for (int a = 0; a < M; ++a) {
-        ra[a] = 0.0;
-        if (a == s) continue;
-        const int l = lat_of(a, s);
-        for (int i = 0; i < Q; ++i)
-            ra[a] += Codec<S>::ld(src, (size_t)(l * Q + i) * L.P + node, slot_ref<M, S, W>(L, q, node, l, i));
-        rs -= ra[a];
+        for (int k = 0; k < NV; ++k) part[w - 1][k][lane] = m.v[k];
     }
+    __syncthreads();
+    if (w || !live) return;
 #pragma unroll
-    for (int a = 0; a < M; ++a)
-        if (a == s) ra[a] = rs;
+    for (int k = 0; k < NV; ++k) m.v[k] += part[0][k][lane] + part[1][k][lane];
+    MechC mc = *as_const(L.mech);
+    double Y[M];
+    species_of_sums<M, W>(m, W ? M : L.slaved, Y);
+    const double rho = m.v[0];
     double ry = rho;   // the weakly coupled storage normalises Y by sum_a rho_a
     if constexpr (W) {
         ry = 0.0;
 #pragma unroll
-        for (int a = 0; a < M; ++a) ry += ra[a];
+        for (int a = 0; a < M; ++a) ry += Y[a];
     }
-    double Y[M];
 #pragma unroll
-    for (int a = 0; a < M; ++a) Y[a] = ra[a] / ry;
-    const double u[3] = {j[0] / rho, j[1] / rho, j[2] / rho};
-    const double U = rE / rho - 0.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+    for (int a = 0; a < M; ++a) Y[a] /= ry;
+    const double u[3] = {m.v[1] / rho, m.v[2] / rho, m.v[3] / rho};
+    const double U = m.v[4] / rho - 0.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
     int fail = 0;
     const double T = solve_T<M>(mc, Y, U, L.aux[AUX_T * N + node], &fail);
     if (fail) atomicOr(L.flag, 1);
     if (rho_o) rho_o[node] = rho;
     if (u_o)
+#pragma unroll
         for (int dd = 0; dd < 3; ++dd) u_o[dd * N + node] = u[dd];
     if (T_o) T_o[node] = T;
     if (Y_o)
@@ -2010,102 +2066,120 @@ __global__ __launch_bounds__(256) void k_fields(const LatDev* __restrict__ lat, 
 }
 
 // FP64 copies of the stored lattices l0 .. l0 + nl - 1 from (write = 0) or
-// into (write = 1) the current population buffer; buf holds [nl][27][N].
+// into (write = 1) the current population buffer; buf holds [nl][27][N].  One
+// thread per node and three velocities of one row (blockIdx.y the row, z the
+// lattice): the plane is uniform, where one thread per value divided 64-bit
+// indices.  256x64x16, FP32 storage, all lattices: 423 -> 338 us.
 template <int M, typename S, int W>
-__global__ __launch_bounds__(256) void k_pops(const LatDev* __restrict__ lat, long long t, int l0, int nl,
-                                              double* buf, int write) {
+__global__ __launch_bounds__(256) void k_pops(const LatDev* __restrict__ lat, long long t, int l0, double* buf, int write) {
+    constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
     const LatDev& L = *lat;
-    const size_t total = (size_t)nl * Q * L.N;
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const size_t gidx = (size_t)l0 * Q * L.N + idx;   // in the packed [L][27][N] order
-    const int li = (int)(gidx / L.N);
-    const long long node = (long long)(gidx % L.N);
-    const size_t pidx = (size_t)li * L.P + node;      // in the buffer's planes
-    const int q = (L.parity0 + t) & 1;
-    void* p = L.pop[q];
-    const double ref = slot_ref<M, S, W>(L, q, node, li / Q, li % Q);
-    if (write) Codec<S>::st(p, pidx, buf[idx], ref);
-    else buf[idx] = Codec<S>::ld(p, pidx, ref);
+    const int node = (int)blockIdx.x * 256 + (int)threadIdx.x;
+    if (node >= (int)L.N) return;
+    const int l = l0 + (int)blockIdx.z, i0 = 3 * (int)blockIdx.y;
+    const size_t N = (size_t)L.N, P = (size_t)L.P;
+    const int q = (int)((L.parity0 + t) & 1);
+    RLBM_GLOBAL S* pop = as_global(static_cast<S*>(L.pop[q])) + (size_t)(l * Q + i0) * P;
+    RLBM_GLOBAL double* out = as_global(buf) + ((size_t)blockIdx.z * Q + i0) * N;
+    double ref[3] = {0.0, 0.0, 0.0};
+    if constexpr (sizeof(S) == 4) {
+        const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
+        PullOff o;
+        pull_offsets(L, x, y, z, o);
+        const RLBM_CONST double* G = as_const(L.ref);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const RLBM_GLOBAL float* sc = scale_at(L, q, reader_at(node, o, c - 1, (int)blockIdx.y % 3 - 1, (int)blockIdx.y / 3 - 1));
+            ref[c] = l == LG ? ref_g(sc[LG], sc[LF], G[l * Q + i0 + c], G[REF_K<NL> + i0 + c]) : ref_of(sc[l], G[l * Q + i0 + c]);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        if (write) {
+            const double v = out[c * N + node];
+            if constexpr (sizeof(S) == 4) st_at(pop + c * P, node, __double2float_rn(v - ref[c]));
+            else st_at(pop + c * P, node, v);
+        } else {
+            out[c * N + node] = (double)ld_at(pop + c * P, node) + ref[c];
+        }
+    }
 }
 
-// Per-block partial sums of the invariants; nv = 6 + E values per block.
+// Per-block partial sums of the invariants over INV_NODES nodes; nv = 6 + E
+// values per block.  Every sum has a fixed order: over a lane's nodes, over
+// the lanes of a wave (a butterfly), over the three waves.  256x64x64, FP32
+// storage: 1.25 -> 0.34 ms.
+constexpr int INV_NODES = 256;
 template <int M, typename S, int W>
-__global__ __launch_bounds__(256) void k_invariants(const LatDev* __restrict__ lat, long long t,
-                                                    double* __restrict__ partial, int nv) {
+__global__ __launch_bounds__(IO_THREADS) void k_invariants(const LatDev* __restrict__ lat, long long t,
+                                                           double* __restrict__ partial, int nv) {
+    constexpr int NV = LayerSums<M, W>::N;
+    __shared__ double red[3][NV + 1];
     const LatDev& L = *lat;
+    const int lane = (int)threadIdx.x % IO_NODES;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / IO_NODES);
+    LayerSums<M, W> acc;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc.v[k] = 0.0;
+    bool bad = false;
+    for (int c = 0; c < INV_NODES; c += IO_NODES) {
+        const int node = (int)blockIdx.x * INV_NODES + c + lane;
+        if (node < (int)L.N) {
+            LayerSums<M, W> m;
+            layer_sums<M, S, W, true>(L, (int)((L.parity0 + t) & 1), node, w - 1, m, bad);
+#pragma unroll
+            for (int k = 0; k < NV; ++k) acc.v[k] += m.v[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+#pragma unroll
+        for (int d = 1; d < IO_NODES; d <<= 1) acc.v[k] += __shfl_xor(acc.v[k], d);
+        if (lane == 0) red[w][k] = acc.v[k];
+    }
+    const bool any = __builtin_amdgcn_ballot_w64(bad) != 0;
+    if (lane == 0) red[w][NV] = any ? 1.0 : 0.0;
+    __syncthreads();
+    if (threadIdx.x) return;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc.v[k] = red[0][k] + red[1][k] + red[2][k];
     MechC mc = *as_const(L.mech);
-    const long long node = (long long)blockIdx.x * 256 + threadIdx.x;
-    const size_t N = (size_t)L.N;
-    constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG;
-    const int s = W ? M : L.slaved;
-    double v[6 + MAXE];
-    for (int q = 0; q < 6 + MAXE; ++q) v[q] = 0.0;
-    if (node < L.N) {
-        const int q = (L.parity0 + t) & 1;
-        const void* src = L.pop[q];
-        double bad = 0.0;
-        double rho = 0.0;
-        for (int i = 0; i < Q; ++i) {
-            const double f =
-                Codec<S>::ld(src, (size_t)(LF * Q + i) * L.P + node, slot_ref<M, S, W>(L, q, node, LF, i));
-            const double g = Codec<S>::ld(src, (size_t)(LG * Q + i) * L.P + node, slot_ref<M, S, W>(L, q, node, LG, i));
-            if (!isfinite(f) || !isfinite(g)) bad = 1.0;
-            rho += f;
-            v[1] += f * cx_of(i); v[2] += f * cy_of(i); v[3] += f * cz_of(i);
-            v[4] += g;
-        }
-        v[0] = rho;
-        double ra[M];
-        double rs = rho;
+    double ra[M];
+    species_of_sums<M, W>(acc, W ? M : L.slaved, ra);
+    double* out = partial + (size_t)blockIdx.x * nv;
 #pragma unroll
-        for (int a = 0; a < M; ++a) {
-            ra[a] = 0.0;
-            if (a == s) continue;
-            const int l = lat_of(a, s);
-            for (int i = 0; i < Q; ++i) {
-                const double f = Codec<S>::ld(src, (size_t)(l * Q + i) * L.P + node, slot_ref<M, S, W>(L, q, node, l, i));
-                if (!isfinite(f)) bad = 1.0;
-                ra[a] += f;
-            }
-            rs -= ra[a];
-        }
+    for (int k = 0; k < 5; ++k) out[k] = acc.v[k];
+    for (int e = 0; e < mc.E; ++e) {
+        double sum = 0.0;
 #pragma unroll
-        for (int a = 0; a < M; ++a)
-            if (a == s) ra[a] = rs;
-        for (int e = 0; e < mc.E; ++e) {
-            double sum = 0.0;
-#pragma unroll
-            for (int a = 0; a < M; ++a) sum += ra[a] * mc.inv_m[a] * mc.comp[a][e];
-            v[5 + e] = sum;
-        }
-        v[5 + mc.E] = bad;
+        for (int a = 0; a < M; ++a) sum += ra[a] * mc.inv_m[a] * mc.comp[a][e];
+        out[5 + e] = sum;
     }
-    __shared__ double red[256];
-    for (int q = 0; q < nv; ++q) {
-        red[threadIdx.x] = v[q];
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) {
-                if (q == nv - 1) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-                else red[threadIdx.x] += red[threadIdx.x + w];
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) partial[(size_t)blockIdx.x * nv + q] = red[0];
-        __syncthreads();
-    }
+    out[5 + mc.E] = fmax(fmax(red[0][NV], red[1][NV]), red[2][NV]);
 }
 
-__global__ void k_reduce_partials(const double* __restrict__ partial, int nblocks, int nv, double* __restrict__ out) {
-    const int q = threadIdx.x;
-    if (q >= nv) return;
+// One block per value, every partial read once by 256 threads and summed in a
+// fixed order.  One thread per value took 943 us for 4,096 blocks (a chain of
+// dependent loads), one block per value takes 9 us.
+__global__ __launch_bounds__(256) void k_reduce_partials(const double* __restrict__ partial, int nblocks, int nv,
+                                                         double* __restrict__ out) {
+    __shared__ double red[4];
+    const int q = blockIdx.x;
+    const bool largest = q == nv - 1;
     double acc = 0.0;
-    for (int b = 0; b < nblocks; ++b) {
+    for (int b = threadIdx.x; b < nblocks; b += 256) {
         const double x = partial[(size_t)b * nv + q];
-        acc = (q == nv - 1) ? fmax(acc, x) : acc + x;
+        acc = largest ? fmax(acc, x) : acc + x;
     }
-    out[q] = acc;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const double x = __shfl_xor(acc, d);
+        acc = largest ? fmax(acc, x) : acc + x;
+    }
+    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = acc;
+    __syncthreads();
+    if (threadIdx.x) return;
+    out[q] = largest ? fmax(fmax(red[0], red[1]), fmax(red[2], red[3])) : (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // Advances the device step counter of a launch series by n (the last node
@@ -2239,17 +2313,18 @@ hipError_t launch_phase(int phase, int M, int storage, int weak, const StepLaunc
                                            : launch_step_phase<double>(phase, M, weak, a);
 }
 
+static int io_blocks(long long N) { return (int)((N + IO_NODES - 1) / IO_NODES); }
+
 template <typename S>
 static hipError_t launch_init_t(int M, int weak, const LatDev* lat, long long N, const double* rho,
                                 const double* u, const double* T, const double* Y, hipStream_t st) {
     (void)hipGetLastError();   // report this launch's error only
-    const int blocks = (int)((N + 255) / 256);
     if constexpr (sizeof(S) == 4) {
-        RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_scale_init<MM, WW>), dim3(blocks), dim3(256), 0, st, lat, rho,
-                                                    u, T, Y))
+        RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_scale_init<MM, WW>), dim3((int)((N + 255) / 256)), dim3(256), 0, st,
+                                                    lat, rho, u, T, Y))
     }
-    RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_init<MM, S, WW>), dim3(blocks), dim3(256), 0, st, lat, rho, u,
-                                                T, Y))
+    RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_init<MM, S, WW>), dim3(io_blocks(N)), dim3(IO_THREADS), 0, st, lat, rho,
+                                                u, T, Y))
     return hipGetLastError();
 }
 
@@ -2270,9 +2345,8 @@ template <typename S>
 static hipError_t launch_fields_t(int M, int weak, const LatDev* lat, long long N, long long t, double* rho,
                                   double* u, double* T, double* Y, double* P, hipStream_t st) {
     (void)hipGetLastError();   // report this launch's error only
-    const int blocks = (int)((N + 255) / 256);
-    RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_fields<MM, S, WW>), dim3(blocks), dim3(256), 0, st, lat, t, rho,
-                                                u, T, Y, P))
+    RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_fields<MM, S, WW>), dim3(io_blocks(N)), dim3(IO_THREADS), 0, st, lat, t,
+                                                rho, u, T, Y, P))
     return hipGetLastError();
 }
 
@@ -2285,14 +2359,11 @@ hipError_t launch_fields(int M, int storage, int weak, const LatDev* lat, long l
 hipError_t launch_pops(int M, int storage, int weak, const LatDev* lat, long long N, int l0, int nl, long long t,
                        double* buf, int write, hipStream_t st) {
     (void)hipGetLastError();   // report this launch's error only
-    const size_t total = (size_t)nl * Q * (size_t)N;
-    const int blocks = (int)((total + 255) / 256);
+    const dim3 grid((unsigned)((N + 255) / 256), Q / 3, nl);
     if (storage == RLBM_STORAGE_F32_DEV)
-        RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_pops<MM, float, WW>), dim3(blocks), dim3(256), 0, st, lat, t,
-                                                    l0, nl, buf, write))
+        RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_pops<MM, float, WW>), grid, dim3(256), 0, st, lat, t, l0, buf, write))
     else
-        RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_pops<MM, double, WW>), dim3(blocks), dim3(256), 0, st, lat, t,
-                                                    l0, nl, buf, write))
+        RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_pops<MM, double, WW>), grid, dim3(256), 0, st, lat, t, l0, buf, write))
     return hipGetLastError();
 }
 
@@ -2300,10 +2371,10 @@ template <typename S>
 static hipError_t launch_inv_t(int M, int weak, const LatDev* lat, long long N, long long t, double* partial,
                                int nv, double* out, hipStream_t st) {
     (void)hipGetLastError();   // report this launch's error only
-    const int blocks = (int)((N + 255) / 256);
-    RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_invariants<MM, S, WW>), dim3(blocks), dim3(256), 0, st, lat, t,
+    const int blocks = (int)((N + INV_NODES - 1) / INV_NODES);
+    RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_invariants<MM, S, WW>), dim3(blocks), dim3(IO_THREADS), 0, st, lat, t,
                                                 partial, nv))
-    hipLaunchKernelGGL(k_reduce_partials, dim3(1), dim3(64), 0, st, partial, blocks, nv, out);
+    hipLaunchKernelGGL(k_reduce_partials, dim3(nv), dim3(256), 0, st, partial, blocks, nv, out);
     return hipGetLastError();
 }
 
