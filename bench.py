@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_update_channel3d_512x64x64_traffic.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_kernels_channel3d_512x64x64_traffic.json")
 
 
 def _kernel_hash():
@@ -82,9 +82,10 @@ def _time_storage(case, storage, steps, warmup):
     e0 = torch.cuda.Event(enable_timing=True)
     e1 = torch.cuda.Event(enable_timing=True)
     # the dominant kernel's duration: the library records HIP events around
-    # every k_update launch on the lattice stream during the timed steps
-    # themselves (only that kernel, so the other launches run back to back)
-    lat.set_timing(True, kernels=("update",))
+    # every launch of the moments phase (k_species) on the lattice stream
+    # during the timed steps themselves (only that kernel, so the other
+    # launches run back to back)
+    lat.set_timing(True, kernels=("local",))
     e0.record(stream)
     t0 = time.perf_counter()
     lat.step(steps)
@@ -104,8 +105,14 @@ def _time_storage(case, storage, steps, warmup):
     ok = inv[-1] == 0.0
     del lat
     torch.cuda.empty_cache()
-    return {"ms_total": ms, "wall_s": wall, "kernels": kt, "update_timed": kt_timed["update"],
+    return {"ms_total": ms, "wall_s": wall, "kernels": kt, "species_timed": kt_timed["local"],
             "finite": bool(ok)}
+
+
+def _species_bytes(L, s):
+    """Algorithmic bytes per node of k_species: the L - 2 species lattices read
+    and written once, the momentum and the energy lattice read once."""
+    return 2 * (L - 2) * 27 * s + 2 * 27 * s
 
 
 def _step_roofline(storage, case, N, bytes_node, ms_step):
@@ -290,8 +297,8 @@ def _bench_substeps(args):
 def _bench_coupling(args):
     """Cost of the weakly coupled storage (all M species lattices, L = M + 2)
     against the slaved one (L = M + 1) on the 512x64x64 channel in both
-    storages: MLUPS, per-kernel times and k_update's algorithmic HBM rate
-    (2 L 27 s bytes per node)."""
+    storages: MLUPS, per-kernel times and k_species' algorithmic HBM rate
+    (_species_bytes per node)."""
     from paper_2108_07605_amd import workloads as wl
     mech = wl.mechanism_h2air9()
     N = args.nx * args.ny * args.nz
@@ -302,13 +309,13 @@ def _bench_coupling(args):
         for st in ("f32dev", "f64"):
             r = _time_storage(case, st, args.steps, args.warmup)
             ms = r["ms_total"] / args.steps
-            upd_ms, upd_n = r["update_timed"]
-            upd = upd_ms / max(upd_n, 1)
+            spc_ms, spc_n = r["species_timed"]
+            spc = spc_ms / max(spc_n, 1)
             s_b = 4 if st == "f32dev" else 8
             rows[f"{coupling} {st}"] = {
                 "L": L, "ms_per_step": ms, "mlups": N / (ms * 1e-3) / 1e6,
                 "kernels_ms_avg": {k: v[0] / max(v[1], 1) for k, v in r["kernels"].items()},
-                "update_GBps": 2 * L * 27 * s_b * N / (upd * 1e-3) / 1e9, "finite": r["finite"]}
+                "species_GBps": _species_bytes(L, s_b) * N / (spc * 1e-3) / 1e9, "finite": r["finite"]}
     return {"metric": "MLUPS, weakly coupled vs slaved storage", "value": rows["weak f32dev"]["mlups"],
             "unit": "MLUPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "higher_is_better": True, "dtype": "f64", "data": "synthetic",
@@ -518,22 +525,22 @@ def main():
         bytes_node = 2 * L * 27 * s                      # populations read + written once
         ms_step = r["ms_total"] / args.steps
         mlups = N / (ms_step * 1e-3) / 1e6
-        # dominant kernel: the collision (k_update), the largest share of the
-        # step, whose algorithmic traffic is the population read + write; its
-        # duration is the average over the timed steps
-        coll_name = "update"
-        coll_ms, coll_n = r["update_timed"]
-        coll_avg = coll_ms / max(coll_n, 1)
-        achieved = bytes_node * N / (coll_avg * 1e-3) / 1e9
-        traffic = _traffic(st, "k_" + coll_name, (case["nx"], case["ny"], case["nz"]))
+        # dominant kernel: k_species (the moments and the species' collision),
+        # the largest share of the step; its duration is the average over the
+        # timed steps
+        spc_ms, spc_n = r["species_timed"]
+        spc_avg = spc_ms / max(spc_n, 1)
+        spc_bytes = _species_bytes(L, s)
+        achieved = spc_bytes * N / (spc_avg * 1e-3) / 1e9
+        traffic = _traffic(st, "k_species", (case["nx"], case["ny"], case["nz"]))
         res[st] = {
             "mlups": mlups, "ms_per_step": ms_step, "finite": r["finite"],
             "kernels_ms_avg": {k: v[0] / max(v[1], 1) for k, v in r["kernels"].items()},
-            "update_ms_avg_timed": coll_avg,
+            "species_ms_avg_timed": spc_avg,
             "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                          "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                          "traffic": traffic,
-                         "kernel": "k_" + coll_name, "alg_bytes_per_node": bytes_node},
+                         "kernel": "k_species", "alg_bytes_per_node": spc_bytes},
             "step_frac_of_hbm_roofline": mlups * 1e6 * bytes_node / (HBM_PEAK_GBS * 1e9),
             "step_roofline": _step_roofline(st, case, N, bytes_node, ms_step),
         }

@@ -245,9 +245,12 @@ int rlbm_lattice_shape(const rlbm_lattice* lat, int32_t* L, int64_t* N, int64_t*
 
 /* Per-kernel timing with HIP events recorded on the lattice stream around
  * the launches of the kernels selected by `enable`: bit k set times kernel k
- * in {0: boundary, 1: moments, diffusion and the forward-Euler reaction
- * increment, 2: gradients (with the linearly implicit reaction increment
- * before them where selected), 3: update}; 0 switches timing off.  Event pairs are pooled and reused.
+ * in {0: boundary, 1: moments, diffusion, the forward-Euler reaction
+ * increment and the collision of the species, 2: the linearly implicit
+ * reaction increment and the gradients after it (no launch with
+ * RLBM_REACTION_EXPLICIT), 3: gradients and the collision of f and g (every
+ * collision with RLBM_REACTION_LINEARLY_IMPLICIT)}; 0 switches timing off.
+ * Event pairs are pooled and reused.
  * rlbm_kernel_times synchronises and returns the accumulated milliseconds
  * ms[k] and launch counts counts[k] since the last reset. */
 int rlbm_set_timing(rlbm_lattice* lat, int enable);

@@ -1,20 +1,25 @@
 // HIP kernels of the reactive-mixture lattice Boltzmann step for gfx950.
 //
-// One time step is four launches over a (possibly batched) work list:
+// One time step is three launches over a (possibly batched) work list:
 //   k_boundary   interface nodes: advection + wall / inlet / outlet
-//                reconstruction (section 4) into a side buffer;
-//   k_local      every node: advection, moments, temperature (eq.
+//                reconstruction (section 4) into the planes' interface slots;
+//   k_species    every node: advection, moments, temperature (eq.
 //                temperature), relaxation rates, Stefan-Maxwell diffusion
-//                velocities (eq. transform1) and the reaction increment by l
-//                forward-Euler sub-steps (eq. R3); publishes rho, u, T, Y,
-//                Phi_a and the enthalpy moments for the neighbours and writes
-//                the per-node record read by k_update;
-//   k_gradients  the same-time gradients of Phi_a and sum_b H_b Y_b
-//                (k_chem_implicit instead for lattices with the linearly
-//                implicit reaction update: its sub-steps, then the gradients);
-//   k_update     every node: advection again and the collisions of all stored
-//                lattices, written to the other population buffer.
-// Populations are structure-of-arrays [L][27][N] (x fastest), pulled from the
+//                velocities (eq. transform1), the reaction increment by l
+//                forward-Euler sub-steps (eq. R3) and the collision of the
+//                species lattices, whose populations stay in registers from
+//                the moments to the collision; publishes T, Phi_a and the
+//                enthalpy moments for the neighbours and the record that
+//                k_flow reads;
+//   k_flow       every node: the same-time gradients of Phi_a and
+//                sum_b H_b Y_b and the collisions of the momentum and energy
+//                lattices.
+// Lattices with the linearly implicit reaction update, whose Jacobian takes
+// the registers that would hold the populations, run
+//   k_local (moments, diffusion), k_chem_implicit (its sub-steps, then the
+//   gradients) and k_update (advection again, every collision)
+// in place of the last two.
+// Populations are structure-of-arrays [L][27][P] (x fastest), pulled from the
 // source buffer, so every load and store of a wavefront is coalesced.  The
 // storage type S is double (FP64) or float (FP32 deviation from a reference
 // population per lattice and velocity, decoded to FP64 on load).
@@ -35,8 +40,8 @@ namespace rlbm {
 // FP32 deviation storage: population (l, i) is stored as its deviation from
 // s_l(y) G_li, where G_li is the zero-velocity equilibrium shape of lattice l
 // at the domain-mean initial state normalised to unit zeroth moment, and
-// s_l(y) the zeroth moment of lattice l (rho_a, rho or rho E) at the node y
-// that reads the population, as it was when the population was written.
+// s_l(y) a zeroth moment of lattice l (rho_a, rho or rho E) at the node y
+// that reads the population, rounded to FP32.
 // Both factors hold FP32 values, so their product is exact in FP64: every
 // writer and reader forms the same reference however the compiler fuses it.
 __device__ __forceinline__ double ref_of(float s, double G) { return (double)s * G; }
@@ -67,11 +72,27 @@ template <int NL> constexpr int REF_M0 = NL * Q;
 template <int NL> constexpr int REF_M2 = NL * Q + NL;
 template <int NL> constexpr int REF_K = NL * Q + NL + 1;
 template <int NL> constexpr int REF_K0 = NL * Q + NL + 1 + Q;
+// then the shapes again, velocity by velocity: [Q][NL] (one wide scalar load
+// per velocity where a kernel walks the lattices)
+template <int NL> constexpr int REF_T = NL * Q + NL + 2 + Q;
 
-// Scales s_l of node n in buffer q: rss floats per node, lattices in order
-// (stored species, rho, rho E).
+// Scales s_l of node n in buffer q: the stored species (rss floats per node),
+// and rho, rho E.  A species population written in a step is encoded with the
+// zeroth moment its reader had one step earlier, which is known before the
+// step's moments (the species collide in the kernel that forms them); f and g,
+// which collide a kernel later, with the moment of the step itself.  Buffer
+// par of the species scales decodes the step's source populations, buffer
+// par ^ 1 (the previous step's moments) encodes what it writes, and the step's
+// own moments then replace buffer par, for the step after.
 __device__ __forceinline__ const RLBM_GLOBAL float* scale_at(const LatDev& L, int q, long long n) {
     return as_global(L.rscale[q]) + (size_t)n * L.rss;
+}
+__device__ __forceinline__ const RLBM_GLOBAL float* fscale_at(const LatDev& L, int q, long long n) {
+    return as_global(L.fscale[q]) + 2 * (size_t)n;
+}
+// the scale of lattice l (wave-uniform; LF: the momentum lattice)
+__device__ __forceinline__ float scale_l(const LatDev& L, int q, long long n, int l, int LF) {
+    return l < LF ? scale_at(L, q, n)[l] : fscale_at(L, q, n)[l - LF];
 }
 
 // Block index -> work tile, XCD-aware.  Workgroups are dispatched to the
@@ -95,6 +116,11 @@ __device__ __forceinline__ S ld_at(const RLBM_GLOBAL S* base, int idx) {
 template <typename S>
 __device__ __forceinline__ void st_at(RLBM_GLOBAL S* base, int idx, S v) {
     *(RLBM_GLOBAL S*)((RLBM_GLOBAL char*)base + (unsigned)(idx * (int)sizeof(S))) = v;
+}
+
+template <typename S>
+__device__ __forceinline__ void st_off(RLBM_GLOBAL S* base, unsigned off, S v) {
+    *(RLBM_GLOBAL S*)((RLBM_GLOBAL char*)base + off) = v;
 }
 
 // A correction row of the per-node record: FP32 (rounded to nearest even)
@@ -153,6 +179,40 @@ __device__ __forceinline__ void pull_offsets(const LatDev& L, int x, int y, int 
 
 __device__ __forceinline__ int sel3(int c, int m, int z, int p) { return c < 0 ? m : (c == 0 ? z : p); }
 __device__ __forceinline__ double sel3d(int c, double m, double z, double p) { return c < 0 ? m : (c == 0 ? z : p); }
+
+// Node that pulls the population stored at slot (node, i): node + c_i,
+// wrapped on every axis (the placeholder rule of the pull offsets o).
+__device__ __forceinline__ int reader_at(int node, const PullOff& o, int c0, int c1, int c2) {
+    return node + sel3(c0, o.x[2], 0, o.x[0]) + sel3(c1, o.y[2], 0, o.y[0]) + sel3(c2, o.z[2], 0, o.z[0]);
+}
+
+// The NSP species scales of node n in buffer q (FP32 storage), as whole
+// 16-byte loads (rss is a multiple of four floats).
+template <int NSP>
+__device__ __forceinline__ void species_scales(const LatDev& L, int q, int n, float* out) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const RLBM_GLOBAL f4* p4 = reinterpret_cast<const RLBM_GLOBAL f4*>(scale_at(L, q, n));
+#pragma unroll
+    for (int v = 0; v < (NSP + 3) / 4; ++v) {
+        const f4 w = p4[v];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (4 * v + e < NSP) out[4 * v + e] = w[e];
+    }
+}
+// rho and rho E scales of node n in buffer q.
+__device__ __forceinline__ void flow_scales(const LatDev& L, int q, int n, float* out) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 v = *reinterpret_cast<const RLBM_GLOBAL f2*>(fscale_at(L, q, n));
+    out[0] = v.x;
+    out[1] = v.y;
+}
+// all NL of them, stored lattices in order
+template <int NL>
+__device__ __forceinline__ void scales_of(const LatDev& L, int q, int n, float (&out)[NL]) {
+    species_scales<NL - 2>(L, q, n, out);
+    flow_scales(L, q, n, out + NL - 2);
+}
 
 // Stored lattice of species a; a slaved index of M (the weakly coupled
 // storage) stores every species at its own index.
@@ -269,15 +329,16 @@ __device__ __forceinline__ void stefan_maxwell(const LatDev& L, int node, const 
 // omega_1 of the momentum and energy lattices.
 __device__ __forceinline__ void relax_rates(MechC mc, double T, double P, double Rmix, double& common,
                                             double& omega, double& omega1) {
-    const double lnr = log(T * mc.inv_T_ref);
-    common = mc.R_univ * mc.R_univ * T / Rmix * P * mc.inv_P_ref * exp(-mc.D_exp * lnr);
-    const double mu = mc.mu_ref * exp(mc.mu_exp * lnr);
-    omega = 1.0 / (mu / P + 0.5);
-    omega1 = 1.0 / (mu * mc.inv_Pr / P + 0.5);
+    const double lnr = ln(T * mc.inv_T_ref);
+    common = mc.R_univ * mc.R_univ * T * recip(Rmix) * P * mc.inv_P_ref * expo(mc.ec, -mc.D_exp * lnr);
+    const double muP = mc.mu_ref * expo(mc.ec, mc.mu_exp * lnr) * recip(P);
+    omega = recip(muP + 0.5);
+    omega1 = recip(fma(muP, mc.inv_Pr, 0.5));
 }
 
 // ---------------------------------------------------------------------------
 // k_local: moments and everything else a node needs from its own populations
+// (lattices with the linearly implicit reaction update)
 // ---------------------------------------------------------------------------
 // Moments of the node's post-advection, post-boundary populations (eqs.
 // density1, momentum1, fdensity, f1momMomentum, g0momTotalEnergy), the
@@ -288,10 +349,10 @@ __device__ __forceinline__ void relax_rates(MechC mc, double T, double P, double
 // u_a - u is written out at once and only rho_a stays in registers.  In FP32
 // deviation storage the sums run over the stored deviations and the
 // reference's own moments are added in closed form (zeroth s_l sum_i G_li,
-// second s_f sum_i G_fi c c, first zero by symmetry); the stored lattices'
-// zeroth moments (rho_a, rho, rho E) become the scales of the references of
-// the populations written this step.  The Stefan-Maxwell solve comes last,
-// once the streaming part no longer holds registers.
+// second s_f sum_i G_fi c c, first zero by symmetry); rho and rho E become
+// the scales of the references of the f and g populations written this step.
+// The Stefan-Maxwell solve comes last, once the streaming part no longer holds
+// registers.
 template <int M>
 struct LocalMoments {
     double rho, rhoE, j[3], q[3], Pd[3], Po[3];   // Pd: xx yy zz, Po: xy xz yz
@@ -332,6 +393,15 @@ __device__ __forceinline__ S ld_win(const RLBM_GLOBAL S* win, unsigned plane, in
         return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (unsigned)idx * 8u, iw * plane, 0));
 }
 
+// Scales of what is written for f and g this step: the node's rho and rho E.
+__device__ __forceinline__ void store_fscale(const LatDev& L, int q, int node, double rho, double rhoE) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    f2 v;
+    v.x = __double2float_rn(rho);
+    v.y = __double2float_rn(rhoE);
+    *(reinterpret_cast<RLBM_GLOBAL f2*>(as_global(L.fscale[q])) + node) = v;
+}
+
 // The moment sums of k_local.  IF = false: no lane of the wave is an
 // interface node and every population is pulled from the source buffer;
 // IF = true: interface lanes read their reconstructed populations from the
@@ -354,11 +424,10 @@ __device__ __forceinline__ void local_moments(const LatDev& L, int par, int k, i
         const int idx = IF ? (k >= 0 ? (int)N + k : off_of(i)) : off_of(i);
         return ld_win(src + (size_t)(l * Q + 9 * (i / 9)) * P, nb, i % 9, idx);
     };
-    const RLBM_GLOBAL float* sc = nullptr;
-    RLBM_GLOBAL float* so = nullptr;
+    const RLBM_GLOBAL float *sc = nullptr, *fs = nullptr;
     if constexpr (sizeof(S) == 4) {
         sc = scale_at(L, par, node);
-        so = as_global(L.rscale[par ^ 1]) + (size_t)node * L.rss;
+        fs = fscale_at(L, par, node);
     }
 
     // the first species lattice's loads go out with the momentum and energy
@@ -389,13 +458,12 @@ __device__ __forceinline__ void local_moments(const LatDev& L, int par, int k, i
     }
     if constexpr (sizeof(S) == 4) {
         const RLBM_CONST double* G = as_const(L.ref);
-        const double sf = (double)sc[LF];
+        const double sf = (double)fs[0];
         rho += sf * G[REF_M0<NL> + LF];
-        rhoE += (double)sc[LG] * G[REF_M0<NL> + LG] + sf * G[REF_K0<NL>];
+        rhoE += (double)fs[1] * G[REF_M0<NL> + LG] + sf * G[REF_K0<NL>];
         const double p2 = sf * G[REF_M2<NL>];
         Pd[0] += p2; Pd[1] += p2; Pd[2] += p2;
-        so[LF] = __double2float_rn(rho);
-        so[LG] = __double2float_rn(rhoE);
+        store_fscale(L, par ^ 1, node, rho, rhoE);
     }
     const double inv_rho = 1.0 / rho;
     const double u[3] = {j[0] * inv_rho, j[1] * inv_rho, j[2] * inv_rho};
@@ -441,7 +509,6 @@ __device__ __forceinline__ void local_moments(const LatDev& L, int par, int k, i
         if constexpr (sizeof(S) == 4) {
             const RLBM_CONST double* rm = as_const(L.ref) + REF_M0<NL> + opaque_zero();
             ra += (double)sc[l] * rm[l];
-            so[l] = __double2float_rn(ra);
         }
         const int a = W ? l : l + (l >= s ? 1 : 0);
         put_species(a, ra, jx, jy, jz);
@@ -471,7 +538,7 @@ __global__ __launch_bounds__(NODE_TILE) __attribute__((amdgpu_waves_per_eu(2, 2)
     const int b = xcd_block();
     const int lj = find_lattice(blk, n_lat, b);
     const LatDev& L = lats[lj];
-    if (t >= L.t_end) return;
+    if (t >= L.t_end || L.reaction == RLBM_REACTION_EXPLICIT) return;
     const int node = (b - blk[lj]) * NODE_TILE + threadIdx.x;
     if (node >= L.N) return;
     MechC mc = *as_const(L.mech);
@@ -574,33 +641,6 @@ __global__ __launch_bounds__(NODE_TILE) __attribute__((amdgpu_waves_per_eu(2, 2)
     prm[PRM_T * N + node] = T;
     prm[PRM_UINT * N + node] = U;
     stefan_maxwell<M, W, sizeof(S) == 4>(L, node, ls, T, rho, common, omega1, Y, Qb, rho * inv_rhoY);
-
-    // reaction increment (eq. R3, forward Euler), with the LDS columns the
-    // diffusion step has finished with; the arithmetic-bound chemistry then
-    // runs under this kernel's memory traffic.  Lattices with the linearly
-    // implicit update take it in k_chem_implicit.
-    if (L.reaction == RLBM_REACTION_EXPLICIT) {
-        reload_barrier();
-        const ChemLds<LOC_T> cl{&s_dv[0][threadIdx.x], &s_dv[M][threadIdx.x], nullptr};
-        double ra[M], fin[M];
-#pragma unroll
-        for (int a = 0; a < M; ++a) ra[a] = s_ra[a][threadIdx.x];
-        double rY = rho;   // the density that normalises the composition
-        if constexpr (W) {
-            rY = 0.0;
-#pragma unroll
-            for (int a = 0; a < M; ++a) rY += ra[a];
-        }
-        int fail_r = 0;
-        reaction_increment<M, LOC_T, false>(mc, ra, rY, U, T, L.substeps, cl, fin, &fail_r);
-        if (fail_r) atomicOr(L.flag, 1);
-        // Delta rho_a against the densities read again from LDS, so that they
-        // need not stay in registers through the sub-steps
-        reload_barrier();
-#pragma unroll
-        for (int a = 0; a < M; ++a)
-            st_corr<sizeof(S) == 4>(as_global(prm), PRM_SP + 6 * a + 5, N, node, fin[a] - s_ra[a][threadIdx.x]);
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -625,19 +665,20 @@ __device__ __forceinline__ void store_gradients(const LatDev& L, int node, const
 
 // Any node: the 26 neighbours' fields, each at its own offset.
 template <int M>
-__device__ __forceinline__ void node_gradients(const LatDev& L, int node) {
+__device__ __forceinline__ void node_gradients(const LatDev& L, int node, double (&acc)[6]) {
     const int nx = L.nx, ny = L.ny, nz = L.nz;
     const int x = node % nx, r = node / nx, y = r % ny, z = r / ny;
     const size_t N = (size_t)L.N;
     const double* aux = L.aux;
-    const double T = L.prm[PRM_T * N + node];
+    const double T = aux[AUX_T * N + node];
     const double T2 = T * T, T3 = T2 * T, T4 = T3 * T, T5 = T4 * T;
     const bool px = L.per[0], py = L.per[1], pz = L.per[2];
     const int gx[3] = {x == 0 ? (px ? nx - 1 : 0) : x - 1, x, x == nx - 1 ? (px ? 0 : x) : x + 1};
     const int gy[3] = {y == 0 ? (py ? ny - 1 : 0) : y - 1, y, y == ny - 1 ? (py ? 0 : y) : y + 1};
     const int gz[3] = {z == 0 ? (pz ? nz - 1 : 0) : z - 1, z, z == nz - 1 ? (pz ? 0 : z) : z + 1};
     const double* Pk = aux + (size_t)(AUX_Y + M) * N;
-    double acc[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 6; ++k) acc[k] = 0.0;
 #pragma unroll 1
     for (int czi = 0; czi < 3; ++czi) {
         const int cz = czi - 1;
@@ -656,7 +697,6 @@ __device__ __forceinline__ void node_gradients(const LatDev& L, int node) {
             if (cz) { acc[2] += (cz * w) * aux[(AUX_PHI + 2) * N + nb]; acc[5] += (cz * w) * hy; }
         }
     }
-    store_gradients<M>(L, node, acc);
 }
 
 // The weights factor per direction, w_i = w(c_ix) w(c_iy) w(c_iz) with
@@ -713,11 +753,11 @@ __device__ __forceinline__ double poly5(double t, const double (&v)[6]) {
 // lane that receives them (the adjacent lane's T).  Every lane of the wave
 // must reach this function.
 template <int M>
-__device__ __forceinline__ void row_tile_gradients(const LatDev& L, int node, int lane) {
+__device__ __forceinline__ void row_tile_gradients(const LatDev& L, int node, int lane, double (&acc)[6]) {
     const int nx = L.nx, ny = L.ny, nz = L.nz;
     const int x = node % nx, r = node / nx, y = r % ny, z = r / ny;
     const size_t N = (size_t)L.N;
-    const double T = L.prm[PRM_T * N + node];
+    const double T = L.aux[AUX_T * N + node];
     const bool px = L.per[0], py = L.per[1], pz = L.per[2];
     const int gy[3] = {y == 0 ? (py ? ny - 1 : 0) : y - 1, y, y == ny - 1 ? (py ? 0 : y) : y + 1};
     const int gz[3] = {z == 0 ? (pz ? nz - 1 : 0) : z - 1, z, z == nz - 1 ? (pz ? 0 : z) : z + 1};
@@ -758,103 +798,87 @@ __device__ __forceinline__ void row_tile_gradients(const LatDev& L, int node, in
         }
     }
     constexpr double w0 = 2.0 / 3.0, w1 = 1.0 / 6.0;
-    const double acc[6] = {0.5 * (fp_ax - fm_ax),
-                           0.5 * (w1 * fm_by + w0 * f0_by + w1 * fp_by),
-                           0.5 * (w1 * fm_cz + w0 * f0_cz + w1 * fp_cz),
-                           0.5 * (hp_a - hm_a),
-                           0.5 * (w1 * hm_b + w0 * h0_b + w1 * hp_b),
-                           0.5 * (w1 * hm_c + w0 * h0_c + w1 * hp_c)};
+    acc[0] = 0.5 * (fp_ax - fm_ax);
+    acc[1] = 0.5 * (w1 * fm_by + w0 * f0_by + w1 * fp_by);
+    acc[2] = 0.5 * (w1 * fm_cz + w0 * f0_cz + w1 * fp_cz);
+    acc[3] = 0.5 * (hp_a - hm_a);
+    acc[4] = 0.5 * (w1 * hm_b + w0 * h0_b + w1 * hp_b);
+    acc[5] = 0.5 * (w1 * hm_c + w0 * h0_c + w1 * hp_c);
+}
+
+// The gradients at `node`, lane `lane` of its tile: a tile inside one x-row
+// (wave-uniform) passes column sums between its lanes.
+template <int M>
+__device__ __forceinline__ void tile_gradients(const LatDev& L, int node, int lane, double (&acc)[6]) {
+    const int x0 = __builtin_amdgcn_readfirstlane((node - lane) % L.nx);
+    if (x0 + NODE_TILE <= L.nx) row_tile_gradients<M>(L, node, lane, acc);
+    else node_gradients<M>(L, node, acc);
+}
+
+// ---------------------------------------------------------------------------
+// k_chem_implicit: for lattices with the linearly implicit reaction update,
+// that increment (reading rho_a, rho, U, T from the per-node record and
+// writing Delta rho_a into it), then the gradients.  The stencil's neighbour
+// loads are latency-bound and the chemistry arithmetic-bound, so the two
+// share one launch.  Holds an (M-1)^2 matrix in registers.
+// ---------------------------------------------------------------------------
+static_assert(NODE_TILE == 64, "one wave per tile");
+template <int M>
+__global__ __launch_bounds__(NODE_TILE) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_chem_implicit(
+    const LatDev* __restrict__ lats, const int* __restrict__ blk, int n_lat, const long long* __restrict__ tp, long long toff) {
+    const long long t = step_time(tp, toff);
+    const int b = xcd_block(), tid = (int)threadIdx.x;
+    const int lj = find_lattice(blk, n_lat, b);
+    const LatDev& L = lats[lj];
+    if (t >= L.t_end || L.reaction != RLBM_REACTION_LINEARLY_IMPLICIT) return;
+    const int node = (b - blk[lj]) * NODE_TILE + tid;
+    if (node >= L.N) return;
+    MechC mc = *as_const(L.mech);
+    double* prm = L.prm;
+    const size_t N = (size_t)L.N;
+    // one row more than species: the unused factor slots name it (masked)
+    __shared__ double s_c[M + 1][NODE_TILE], s_g[M + 1][NODE_TILE], s_q[M + 1][NODE_TILE];
+    const ChemLds<NODE_TILE> ls{&s_c[0][tid], &s_g[0][tid], &s_q[0][tid]};
+    s_c[M][tid] = 1.0;
+    s_g[M][tid] = 0.0;
+    s_q[M][tid] = 0.0;
+    double rho_a[M], fin[M];
+#pragma unroll
+    for (int a = 0; a < M; ++a) rho_a[a] = prm[(PRM_SP + 6 * a) * N + node];
+    // the density that normalises the composition (sum_a rho_a in the
+    // weakly coupled storage)
+    double rho = prm[PRM_RHO * N + node];
+    if (L.weak) {
+        rho = 0.0;
+#pragma unroll
+        for (int a = 0; a < M; ++a) rho += rho_a[a];
+    }
+    const double U = prm[PRM_UINT * N + node];
+    const double T = prm[PRM_T * N + node];
+    int fail = 0;
+    reaction_increment<M, NODE_TILE>(mc, rho_a, rho, U, T, L.substeps, ls, fin, &fail);
+    if (fail) atomicOr(L.flag, 1);
+    // Delta rho_a against the densities read again, so that they need not
+    // stay in registers through the sub-steps
+    reload_barrier();
+    if (L.storage == RLBM_STORAGE_F32_DEV) {
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+            st_corr<true>(as_global(prm), PRM_SP + 6 * a + 5, N, node, fin[a] - prm[(PRM_SP + 6 * a) * N + node]);
+    } else {
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+            st_corr<false>(as_global(prm), PRM_SP + 6 * a + 5, N, node, fin[a] - prm[(PRM_SP + 6 * a) * N + node]);
+    }
+    double acc[6];
+    tile_gradients<M>(L, node, tid, acc);
     store_gradients<M>(L, node, acc);
 }
 
 // ---------------------------------------------------------------------------
-// k_gradients: the same-time gradients of every node of the lattices whose
-// reaction increment k_local has written (the forward-Euler update).
-// k_chem_implicit: for lattices with the linearly implicit update, that
-// increment (reading rho_a, rho, U, T from the per-node record and writing
-// Delta rho_a into it), then the gradients.  The stencil's neighbour loads
-// are latency-bound and the implicit chemistry arithmetic-bound, so the two
-// share one launch.  A launch serves the lattices of its scheme; the blocks of
-// the others return at once.
-// ---------------------------------------------------------------------------
-template <int M, bool IMPL>
-__device__ __forceinline__ void chem_body(const LatDev* __restrict__ lats, const int* __restrict__ blk, int n_lat,
-                                          const long long* __restrict__ tp, long long toff, int b, int tid) {
-    const long long t = step_time(tp, toff);
-    const int lj = find_lattice(blk, n_lat, b);
-    const LatDev& L = lats[lj];
-    if (t >= L.t_end) return;
-    if ((L.reaction == RLBM_REACTION_LINEARLY_IMPLICIT) != IMPL) return;
-    const int node = (b - blk[lj]) * NODE_TILE + tid;
-    if (node >= L.N) return;
-    if constexpr (IMPL) {
-        MechC mc = *as_const(L.mech);
-        double* prm = L.prm;
-        const size_t N = (size_t)L.N;
-        __shared__ double s_c[M][NODE_TILE], s_g[M][NODE_TILE], s_q[M][NODE_TILE];
-        const ChemLds<NODE_TILE> ls{&s_c[0][threadIdx.x], &s_g[0][threadIdx.x], &s_q[0][threadIdx.x]};
-        double rho_a[M], fin[M];
-#pragma unroll
-        for (int a = 0; a < M; ++a) rho_a[a] = prm[(PRM_SP + 6 * a) * N + node];
-        // the density that normalises the composition (sum_a rho_a in the
-        // weakly coupled storage)
-        double rho = prm[PRM_RHO * N + node];
-        if (L.weak) {
-            rho = 0.0;
-#pragma unroll
-            for (int a = 0; a < M; ++a) rho += rho_a[a];
-        }
-        const double U = prm[PRM_UINT * N + node];
-        const double T = prm[PRM_T * N + node];
-        int fail = 0;
-        reaction_increment<M, NODE_TILE, true>(mc, rho_a, rho, U, T, L.substeps, ls, fin, &fail);
-        if (fail) atomicOr(L.flag, 1);
-        // Delta rho_a against the densities read again, so that they need not
-        // stay in registers through the sub-steps
-        reload_barrier();
-        if (L.storage == RLBM_STORAGE_F32_DEV) {
-#pragma unroll
-            for (int a = 0; a < M; ++a)
-                st_corr<true>(as_global(prm), PRM_SP + 6 * a + 5, N, node, fin[a] - prm[(PRM_SP + 6 * a) * N + node]);
-        } else {
-#pragma unroll
-            for (int a = 0; a < M; ++a)
-                st_corr<false>(as_global(prm), PRM_SP + 6 * a + 5, N, node, fin[a] - prm[(PRM_SP + 6 * a) * N + node]);
-        }
-    }
-    // wave-uniform: the tile's 64 nodes lie in one x-row
-    const int x0 = __builtin_amdgcn_readfirstlane((node - tid) % L.nx);
-    if (x0 + NODE_TILE <= L.nx)
-        row_tile_gradients<M>(L, node, tid);
-    else
-        node_gradients<M>(L, node);
-}
-
-// GRAD_TILES tiles per block, one wave each (the stencil shares nothing
-// between waves): the lattice of each tile is looked up per wave, and tiles
-// past the end of the list return.
-constexpr int GRAD_TILES = 4;
-static_assert(NODE_TILE == 64, "one wave per tile");
-template <int M>
-__global__ __launch_bounds__(GRAD_TILES * NODE_TILE) void k_gradients(const LatDev* __restrict__ lats,
-                                                                      const int* __restrict__ blk, int n_lat,
-                                                                      const long long* __restrict__ tp, long long toff) {
-    const int tile = xcd_block() * GRAD_TILES + __builtin_amdgcn_readfirstlane((int)threadIdx.x / NODE_TILE);
-    if (tile >= blk[n_lat]) return;
-    chem_body<M, false>(lats, blk, n_lat, tp, toff, tile, (int)threadIdx.x % NODE_TILE);
-}
-
-// The linearly implicit variant holds an (M-1)^2 matrix in registers.
-template <int M>
-__global__ __launch_bounds__(NODE_TILE) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_chem_implicit(
-    const LatDev* __restrict__ lats, const int* __restrict__ blk, int n_lat, const long long* __restrict__ tp, long long toff) {
-    chem_body<M, true>(lats, blk, n_lat, tp, toff, xcd_block(), (int)threadIdx.x);
-}
-
-
-// ---------------------------------------------------------------------------
 // k_update: the collision of every stored lattice (section 2.3 eq.
-// finalNumericalEquationsReactive, section 3.2 eq. f, section 3.3 eq. g).
+// finalNumericalEquationsReactive, section 3.2 eq. f, section 3.3 eq. g) of the
+// lattices with the linearly implicit reaction update.
 // A block of three waves covers 64 consecutive nodes; wave w takes the nine
 // velocities with c_z = w - 1, one node per lane.  The per-node record is
 // staged once in LDS with the species in slot order (the stored species in
@@ -928,7 +952,7 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
     const int b = xcd_block();
     const int lj = find_lattice(blk, n_lat, b);
     const LatDev& L = lats[lj];
-    if (t >= L.t_end) return;
+    if (t >= L.t_end || L.reaction == RLBM_REACTION_EXPLICIT) return;
     const int node0 = (b - blk[lj]) * UPD_NODES;
     const int lane = threadIdx.x % UPD_NODES;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / UPD_NODES);
@@ -977,11 +1001,10 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
                     v[q] = ld_at(prm + (size_t)srow * L.N, nd);
             }
             if constexpr (sizeof(S) == 4) {
-                const RLBM_GLOBAL float* sc = scale_at(L, par, nd);
 #pragma unroll
                 for (int q = 0; q < LPW; ++q) {
                     const int l = WV + UPD_WAVES * q;
-                    w[q] = sc[l < NS ? l : 0];
+                    w[q] = scale_l(L, par, nd, l < NS ? l : 0, LF);
                 }
             }
 #pragma unroll
@@ -1024,23 +1047,6 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
     };
     // FP32 deviation storage: reference scales of this node (decode) and of
     // the node that reads what is written for velocity (c0, c1, c2) (encode)
-    constexpr int NS4 = (NS + 3) / 4;
-    auto load_scales = [&](int q, int n, float* out) {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const RLBM_GLOBAL f4* p4 = reinterpret_cast<const RLBM_GLOBAL f4*>(scale_at(L, q, n));
-#pragma unroll
-        for (int v = 0; v < NS4; ++v) {
-            const f4 w = p4[v];
-            if (4 * v + 0 < NS) out[4 * v + 0] = w.x;
-            if (4 * v + 1 < NS) out[4 * v + 1] = w.y;
-            if (4 * v + 2 < NS) out[4 * v + 2] = w.z;
-            if (4 * v + 3 < NS) out[4 * v + 3] = w.w;
-        }
-    };
-    auto reader = [&](int c0, int c1, int c2) {
-        return node + sel3(c0, o.x[2], 0, o.x[0]) + sel3(c1, o.y[2], 0, o.y[0]) + sel3(c2, o.z[2], 0, o.z[0]);
-    };
-
     S fin[NL];
     const int i_first = 9 * (c2 + 1);
     if (valid) load(i_first, offz + o.y[0] + o.x[0], fin);
@@ -1088,6 +1094,15 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
     }
     __syncthreads();
     if (!valid) return;
+    if constexpr (sizeof(S) == 4) {
+        // every wave has staged this node's own scales: the step's species
+        // densities replace them
+        if (wave == 1) {
+            RLBM_GLOBAL float* so = as_global(L.rscale[par]) + (size_t)node * L.rss;
+#pragma unroll
+            for (int j = 0; j < NSP; ++j) so[j] = __double2float_rn(sp[PRM_SP + 6 * j][lane]);
+        }
+    }
 
     const int GR = prm_grad(M);
     // per-node values used by every velocity are re-read from LDS where they
@@ -1151,7 +1166,7 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
             // consumed after the species work below), issued before the
             // prefetch so that waiting for them leaves the prefetch in flight
             float srd[NS];
-            if constexpr (sizeof(S) == 4) load_scales(par ^ 1, reader(c0, c1, c2), srd);
+            if constexpr (sizeof(S) == 4) scales_of<NL>(L, par ^ 1, reader_at(node, o, c0, c1, c2), srd);
             // prefetch the next velocity of this thread
             S fnx[NL];
             if constexpr (c0 < 1) {
@@ -1245,6 +1260,706 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
         body(std::integral_constant<int, -1>{});
         body(std::integral_constant<int, 0>{});
         body(std::integral_constant<int, 1>{});
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_species: everything a node does with the species (sections 2.2, 2.3, 3.1,
+// 3.5), in one pass over their populations.  A block takes 64 nodes with four
+// waves.  Waves 0..2 hold one c_z layer each, nine velocities of every species
+// lattice in registers, from the pull to the collision; the fourth wave reads
+// the momentum and energy lattices (for their moments only) and solves the
+// node: temperature, relaxation rates, Stefan-Maxwell system.  The reactions
+// are dealt to the first three waves.
+//   Bound: FP64 issue and its latency (two waves per SIMD; about 15,000 vector
+// instructions per tile, which the SIMDs issue 48% of the time) in FP32
+// storage, those and the traffic in FP64: 2.1 and 4.1 KB per node, against
+// 4.0 and 7.5 for a moments pass and a collision that each read every
+// population.  Three waves hold what one cannot, 216 registers of populations
+// per node (FP32) beside the collision's working set, and they divide the
+// node's serial chain, which is what a lattice too small to fill the chip
+// waits for.  With k_flow against the passes it replaced (moments, gradients,
+// collision of all lattices), 512x64x64: 1.79 + 0.42 against 0.93 + 0.18 + 1.28
+// ms in FP32 storage, 2.05 + 0.53 against 1.19 + 0.18 + 2.00 in FP64; 1024
+// nodes: 23 + 14 against 38 + 9 + 23 us.
+//   The order of the barriers is the same on both sides of the role branch:
+// partial sums written, partial sums read, node state, per sub-step
+// (concentrations, rates), collision coefficients.
+// ---------------------------------------------------------------------------
+constexpr int SPC_NODES = 64;
+constexpr int SPC_THREADS = 4 * SPC_NODES;
+
+// Rows (64 doubles each) of the block's LDS.  Species quantities are in slot
+// order (the stored species in lattice order, then the slaved one) except the
+// chemistry's, which are in species order.
+template <int M, int W>
+struct SpcRows {
+    static constexpr int NSP = Lat<M, W>::NSP;
+    // slot q: 4 q + {0: rho_q, 1..3: j_q - rho_q u, then u + V_q}
+    static constexpr int ST = 0;
+    static constexpr int CG = 4 * M;                 // concentration and Gibbs function of species a: CG + 2 a, CG + 2 a + 1
+    static constexpr int WD = CG + 2 * (M + 1);      // three waves' partial rates [3][M]
+    static constexpr int U = WD + 3 * M, T = U + 3, RHO = U + 4, RHOY = U + 5, UINT = U + 6;
+    static constexpr int A = U + 7, K = A + NSP;     // collision coefficients
+    static constexpr int B = WD;                     // the last of them, once the chemistry is done
+    // the fourth wave's own, during its solve: q - u.(P - P^eq) - rho u^2/2 u, theta, omega, omega_1
+    static constexpr int AX = K + NSP;
+    static constexpr int SC = AX + 6;                // FP32 storage: A times this node's scales
+    // partial sums of lattice l, layer w: row PS + 9 l + 3 k + w, k = {zeroth, x, y}; read before the rows above are written
+    static constexpr int PS = 0;
+    static_assert(PS + 9 * NSP <= U, "the node's velocity is written beside the partial sums");
+    static constexpr int N = SC + NSP;
+};
+
+// Interface slot of a node, or -1.  The index is loaded only by waves with a
+// node on a non-periodic face (wave-uniform), so the loads of the others do
+// not wait for it.
+__device__ __forceinline__ int interface_slot(const LatDev& L, int node, int x, int y, int z) {
+    const bool on = (!L.per[0] && (x == 0 || x == L.nx - 1)) || (!L.per[1] && (y == 0 || y == L.ny - 1)) ||
+                    (!L.per[2] && (z == 0 || z == L.nz - 1));
+    if (__builtin_amdgcn_ballot_w64(on) == 0) return -1;
+    return as_global(L.if_index)[node];
+}
+
+// Waves 0..2: partial moments, reactions, collision.
+template <int M, typename S, int W>
+__device__ __forceinline__ void species_layer(const LatDev& L, int par, int layer, int lane, int node, bool valid,
+                                              double (&sp)[SpcRows<M, W>::N][SPC_NODES]) {
+    using R = SpcRows<M, W>;
+    constexpr int NSP = Lat<M, W>::NSP, NL = Lat<M, W>::NL;
+    constexpr bool F32 = sizeof(S) == 4;
+    const int s = W ? M : L.slaved;
+    const int c2 = layer - 1;
+    const size_t N = (size_t)L.N, P = (size_t)L.P;
+    const RLBM_GLOBAL S* src = as_global(static_cast<const S*>(L.pop[par]));
+    RLBM_GLOBAL S* dst = as_global(static_cast<S*>(L.pop[par ^ 1]));
+    MechC mc0 = *as_const(L.mech);
+    const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
+    PullOff o;
+    pull_offsets(L, x, y, z, o);
+    S raw[NSP][9];
+    const unsigned nb = plane_bytes(L.P, sizeof(S));
+    {
+        const int k = interface_slot(L, node, x, y, z);
+        const int nz = node + sel3(c2, o.z[0], 0, o.z[2]);
+        int idx[9];
+#pragma unroll
+        for (int j = 0; j < 9; ++j) idx[j] = k >= 0 ? (int)N + k : nz + o.x[j % 3] + o.y[j / 3];
+        const RLBM_GLOBAL S* win = src + (size_t)(9 * layer) * P;
+#pragma unroll
+        for (int l = 0; l < NSP; ++l) {
+#pragma unroll
+            for (int j = 0; j < 9; ++j) raw[l][j] = ld_win(win, nb, j, idx[j]);
+            win += (size_t)Q * P;
+            opaque(win);
+        }
+    }
+#pragma unroll
+    for (int l = 0; l < NSP; ++l) {
+        double v[9];
+#pragma unroll
+        for (int j = 0; j < 9; ++j) v[j] = (double)raw[l][j];
+        const double lo = v[0] + v[1] + v[2], mid = v[3] + v[4] + v[5], hi = v[6] + v[7] + v[8];
+        double* ps = &sp[R::PS + 9 * l + layer][lane];
+        ps[0] = lo + mid + hi;
+        ps[3 * SPC_NODES] = (v[2] + v[5] + v[8]) - (v[0] + v[3] + v[6]);
+        ps[6 * SPC_NODES] = hi - lo;
+    }
+    __syncthreads();   // partial sums
+    // densities and j_a - rho_a u (eqs. density1, momentum1) of a third of the
+    // species each, while the fourth wave solves for T
+    {
+        constexpr int NT = (NSP + 2) / 3;
+        const double ux = sp[R::U][lane], uy = sp[R::U + 1][lane], uz = sp[R::U + 2][lane];
+        double ra[NT], X[NT][3];
+#pragma unroll
+        for (int e = 0; e < NT; ++e) {
+            const int l = 3 * e + layer;
+            if (l < NSP) {
+                const double* ps = &sp[R::PS + 9 * l][lane];
+                const double m0 = ps[0], m1 = ps[SPC_NODES], m2 = ps[2 * SPC_NODES];
+                ra[e] = m0 + m1 + m2;
+                if constexpr (F32) ra[e] += (double)scale_at(L, par, node)[l] * as_const(L.ref)[REF_M0<NL> + l];
+                X[e][0] = fma(-ra[e], ux, ps[3 * SPC_NODES] + ps[4 * SPC_NODES] + ps[5 * SPC_NODES]);
+                X[e][1] = fma(-ra[e], uy, ps[6 * SPC_NODES] + ps[7 * SPC_NODES] + ps[8 * SPC_NODES]);
+                X[e][2] = fma(-ra[e], uz, m2 - m0);
+            }
+        }
+        __syncthreads();   // partial sums read
+#pragma unroll
+        for (int e = 0; e < NT; ++e) {
+            const int l = 3 * e + layer;
+            if (l < NSP) {
+                sp[R::ST + 4 * l][lane] = ra[e];
+#pragma unroll
+                for (int d = 0; d < 3; ++d) sp[R::ST + 4 * l + 1 + d][lane] = X[e][d];
+            }
+        }
+    }
+    __syncthreads();   // node state
+
+    // reaction increment (section 2.3, eq. R3): forward Euler sub-steps at
+    // frozen U; every wave follows the densities, and takes a third of the
+    // reactions and of the species' concentrations and Gibbs functions
+    double cur[M];
+#pragma unroll
+    for (int a = 0; a < M; ++a) cur[a] = sp[R::ST + 4 * (W ? a : (a == s ? M - 1 : a - (a > s ? 1 : 0)))][lane];
+    if (mc0.R > 0) {
+        const double inv_rho = recip(sp[R::RHOY][lane]), U = sp[R::UINT][lane];
+        double T = sp[R::T][lane];
+        const double inv_l = 1.0 / (double)L.substeps;
+        int fail = 0;
+        for (int st = 0;; ++st) {
+            reload_barrier();
+            MechC mc = in_loop(mc0);
+            const double lnT = ln(T), invT = recip(T);
+#pragma unroll
+            for (int a = 0; a < M; ++a)
+                if (a % 3 == layer) {
+                    sp[R::CG + 2 * a][lane] = fmax(cur[a], 0.0) * mc.inv_m[a];
+                    sp[R::CG + 2 * a + 1][lane] = gibbs_RT(mc, a, T, lnT, invT);
+                }
+            if (layer == 0) {
+                sp[R::CG + 2 * M][lane] = 1.0;
+                sp[R::CG + 2 * M + 1][lane] = 0.0;
+            }
+            __syncthreads();   // concentrations
+            double w[M];
+#pragma unroll
+            for (int a = 0; a < M; ++a) w[a] = 0.0;
+            reaction_rates<M, SPC_NODES>(mc0, &sp[R::CG][lane], lnT, invT, layer, 3, w);
+#pragma unroll
+            for (int a = 0; a < M; ++a) sp[R::WD + layer * M + a][lane] = w[a];
+            __syncthreads();   // rates
+            if (st + 1 == L.substeps && layer != 0) break;
+#pragma unroll
+            for (int a = 0; a < M; ++a)
+                cur[a] = fma(sp[R::WD + a][lane] + sp[R::WD + M + a][lane] + sp[R::WD + 2 * M + a][lane],
+                             mc.m[a] * inv_l, cur[a]);
+            if (st + 1 == L.substeps) break;
+            double Y[M];
+#pragma unroll
+            for (int a = 0; a < M; ++a) Y[a] = cur[a] * inv_rho;
+            T = solve_T<M>(mc, Y, U, T, &fail);
+        }
+        if (layer == 0 && fail && valid) atomicOr(L.flag, 1);
+    } else {
+        __syncthreads();   // concentrations
+        __syncthreads();   // rates
+    }
+    if (layer == 0) {
+        // half of 2 beta rho + Delta rho, with 2 beta = 1 - A
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+            if (W || a != s) {
+                const int q = W ? a : a - (a > s ? 1 : 0);
+                const double rq = sp[R::ST + 4 * q][lane];
+                sp[R::B + q][lane] = 0.5 * fma(1.0 - sp[R::A + q][lane], rq, cur[a] - rq);
+            }
+    }
+    if constexpr (F32) {
+        if (layer == 2) {
+            float sc[NSP];
+            species_scales<NSP>(L, par, node, sc);
+#pragma unroll
+            for (int j = 0; j < NSP; ++j) sp[R::SC + j][lane] = sp[R::A + j][lane] * (double)sc[j];
+        }
+    }
+    __syncthreads();   // collision coefficients
+    if (!valid) return;
+
+    // Collision, a row of three velocities (fixed c_y, c_z) at a time.  With
+    // Psi_0 = 1 - P and Psi_{+-1} = (P +- xi)/2 a product form over the row is
+    // given by z = Y Z, s = Y Z P_x and o = Y Z xi_x: its values are z - s and
+    // (s +- o)/2.  The sums over the species are linear, so they run over
+    // (z, s, o) of D_b = f_b^eq - f_b^* and the row is formed once per species:
+    //   f' = A f + (2 beta rho + Delta rho) W + 2 K sum_b K_ab D_b,
+    // A = 1 - 2 beta, 2 K = (beta - 1) common Y (eqs. betaa, taua).
+    const double T = sp[R::T][lane];
+    const double ux = sp[R::U][lane], uy = sp[R::U + 1][lane], uz = sp[R::U + 2][lane];
+    const PsiCoef pz = psi_coef(c2);
+    // one copy of the row's code (three would not fit the instruction cache
+    // beside the rest): the next row's populations move down after each
+    RLBM_GLOBAL S* win0 = dst + (size_t)(9 * layer) * P;
+    unsigned off = (unsigned)node * (unsigned)sizeof(S);
+    asm volatile("" : "+v"(off));   // a 32-bit offset, not folded into 64-bit addresses
+    const RLBM_CONST double* ref0 = F32 ? as_const(L.ref) + REF_T<NL> + 9 * layer * NL : nullptr;
+#pragma unroll 1
+    for (int c1 = -1; c1 <= 1; ++c1) {
+        const PsiCoef py = psi_coef(c1);
+        double Fz[NSP], Fs[NSP], Fo[NSP], yz[NSP];
+#pragma unroll
+        for (int q = 0; q < M; ++q) {
+            reload_barrier();
+            const RLBM_CONST double* slotc = as_const(L.slotc) + opaque_zero();
+            const RLBM_CONST double* Kq = slotc + M + q * M;   // symmetric
+            const double rq = sp[R::ST + 4 * q][lane];
+            const double vx = sp[R::ST + 4 * q + 1][lane], vy = sp[R::ST + 4 * q + 2][lane], vz = sp[R::ST + 4 * q + 3][lane];
+            const double tq = slotc[q] * T;
+            const double e = psi_u(py, uy, fma(uy, uy, tq)) * psi_u(pz, uz, fma(uz, uz, tq));
+            const double v = psi_u(py, vy, fma(vy, vy, tq)) * psi_u(pz, vz, fma(vz, vz, tq));
+            if (q < NSP) yz[q] = e;
+            const double re = rq * e, rv = rq * v;
+            const double dz = re - rv;
+            const double ds = fma(re, fma(ux, ux, tq), -(rv * fma(vx, vx, tq)));
+            const double d_o = fma(re, ux, -(rv * vx));
+#pragma unroll
+            for (int j = 0; j < NSP; ++j)
+                if (j != q) {
+                    const bool first = q == 0 || (q == 1 && j == 0);
+                    Fz[j] = first ? Kq[j] * dz : fma(Kq[j], dz, Fz[j]);
+                    Fs[j] = first ? Kq[j] * ds : fma(Kq[j], ds, Fs[j]);
+                    Fo[j] = first ? Kq[j] * d_o : fma(Kq[j], d_o, Fo[j]);
+                }
+        }
+        reload_barrier();
+        // the row's values without the old populations, in place: Fz = the
+        // value at c_x = 0, (Fs, Fo) = those at c_x = -1, +1
+#pragma unroll
+        for (int j = 0; j < NSP; ++j) {
+            reload_barrier();
+            const RLBM_CONST double* slotc = as_const(L.slotc) + opaque_zero();
+            const double K = sp[R::K + j][lane];
+            const double g = sp[R::B + j][lane] * yz[j];
+            const double hs = fma(K, Fs[j], g * fma(ux, ux, slotc[j] * T));
+            const double ho = fma(K, Fo[j], g * ux);
+            Fz[j] = 2.0 * (fma(K, Fz[j], g) - hs);
+            Fs[j] = hs - ho;
+            Fo[j] = hs + ho;
+        }
+        auto put = [&](auto c0t, const double (&eq)[NSP]) {
+            constexpr int c0 = decltype(c0t)::value;
+            float srd[NSP];
+            if constexpr (F32) species_scales<NSP>(L, par ^ 1, reader_at(node, o, c0, c1, c2), srd);
+            RLBM_GLOBAL S* win = win0 + (size_t)(c0 + 1) * P;
+            const RLBM_CONST double* G = ref0 + (F32 ? NL * (c0 + 1) + opaque_zero() : 0);
+#pragma unroll
+            for (int j = 0; j < NSP; ++j) {
+                const double A = sp[R::A + j][lane];
+                const double f = (double)raw[j][c0 + 1];
+                opaque(win);
+                if constexpr (F32)
+                    // A (f + s G) + eq - s_reader G
+                    st_off(win, off, __double2float_rn(fma(A, f, fma(sp[R::SC + j][lane] - (double)srd[j], G[j], eq[j]))));
+                else
+                    st_off(win, off, fma(A, f, eq[j]));
+                win += (size_t)Q * P;
+            }
+        };
+        put(std::integral_constant<int, -1>{}, Fs);
+        put(std::integral_constant<int, 0>{}, Fz);
+        put(std::integral_constant<int, 1>{}, Fo);
+        win0 += 3 * P;
+        if constexpr (F32) ref0 += 3 * NL;
+#pragma unroll
+        for (int j = 0; j < NSP; ++j)
+#pragma unroll
+            for (int k = 0; k < 6; ++k) raw[j][k] = raw[j][k + 3];
+    }
+}
+
+// The rest of the fourth wave's work, after its solve: the energy flux, the
+// neighbour-facing fields (Phi and the enthalpy moments for the gradient
+// stencil, T for the next step's Newton start; rho, u and Y only where an
+// outlet reads them, at the first interior node of the x+ face) and k_flow's
+// record.  flux = sum_a H_a Y_a V_a.
+template <int M, typename S, int W>
+__device__ __forceinline__ void write_record(const LatDev& L, int lane, int node, int x, bool valid, const double (&Y)[M],
+                                             const double (&flux)[3], const double (&sp)[SpcRows<M, W>::N][SPC_NODES]) {
+    using R = SpcRows<M, W>;
+    if (!valid) return;
+    reload_barrier();
+    const int s = W ? M : L.slaved;
+    const size_t N = (size_t)L.N;
+    RLBM_GLOBAL double* prm = as_global(L.prm);
+    RLBM_GLOBAL double* aux = as_global(L.aux);
+    MechC mc = in_loop(*as_const(L.mech));
+    auto sp_of = [&](int q) { return W ? q : (q < M - 1 ? q + (q >= s ? 1 : 0) : s); };
+    const double u[3] = {sp[R::U][lane], sp[R::U + 1][lane], sp[R::U + 2][lane]};
+    const double T = sp[R::T][lane], rho = sp[R::RHO][lane], U = sp[R::UINT][lane];
+    const double th = sp[R::AX + 3][lane], omega = sp[R::AX + 4][lane], omega1 = sp[R::AX + 5][lane];
+    // enthalpy-weighted composition moments sum_a H_a(T') Y_a = sum_kk T'^kk Pk
+    double Pk[6];
+#pragma unroll
+    for (int kk = 0; kk < 6; ++kk) Pk[kk] = 0.0;
+#pragma unroll
+    for (int sl = 0; sl < M; ++sl) {
+        const RLBM_CONST double* h = mc.hc[sp_of(sl)];
+#pragma unroll
+        for (int kk = 0; kk < 6; ++kk) Pk[kk] = fma(h[kk], Y[sl], Pk[kk]);
+    }
+    // local part of the energy flux, Qb = (omega - omega1)(q - u.(P - P^eq) - q^eq),
+    // with the diffusion term omega1 rho sum_a H_a Y_a V_a
+    const double hr = rho * poly5(T, Pk);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double Qb = (omega - omega1) * fma(-hr, u[a], sp[R::AX + a][lane]);
+        st_corr<sizeof(S) == 4>(prm, PRM_QB + a, N, node, fma(omega1 * rho, flux[a], Qb));
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+        st_at(aux + (AUX_PHI + d) * N, node, rho * u[d] * (1.0 - 3.0 * th) - rho * u[d] * u[d] * u[d]);
+    st_at(aux + AUX_T * N, node, T);
+#pragma unroll
+    for (int kk = 0; kk < 6; ++kk) st_at(aux + (AUX_Y + M + kk) * N, node, Pk[kk]);
+    if (L.n_out > 0 && x == L.nx - 2) {
+        st_at(aux + AUX_RHO * N, node, rho);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) st_at(aux + (AUX_U + d) * N, node, u[d]);
+#pragma unroll
+        for (int sl = 0; sl < M; ++sl) st_at(aux + (size_t)(AUX_Y + sp_of(sl)) * N, node, Y[sl]);
+    }
+    st_at(prm + PRM_RHO * N, node, rho);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) st_at(prm + (PRM_U + d) * N, node, u[d]);
+    st_at(prm + PRM_UINT * N, node, U);
+    st_at(prm + PRM_TH * N, node, th);
+    st_at(prm + PRM_OMEGA * N, node, omega);
+    st_at(prm + PRM_OMEGA1 * N, node, omega1);
+}
+
+// Wave 3: the momentum and energy lattices' moments and the node's solve.
+template <int M, typename S, int W>
+__device__ __forceinline__ void node_solve(const LatDev& L, int par, int lane, int node, bool valid,
+                                           double (&sp)[SpcRows<M, W>::N][SPC_NODES]) {
+    using R = SpcRows<M, W>;
+    constexpr int NSP = Lat<M, W>::NSP, LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
+    constexpr bool F32 = sizeof(S) == 4;
+    const int s = W ? M : L.slaved;
+    const size_t N = (size_t)L.N, P = (size_t)L.P;
+    const RLBM_GLOBAL S* src = as_global(static_cast<const S*>(L.pop[par]));
+    RLBM_GLOBAL double* prm = as_global(L.prm);
+    RLBM_GLOBAL double* aux = as_global(L.aux);
+    MechC mc0 = *as_const(L.mech);
+    const RLBM_CONST double* slotc = as_const(L.slotc);
+    const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
+    auto sp_of = [&](int q) { return W ? q : (q < M - 1 ? q + (q >= s ? 1 : 0) : s); };
+    double rho = 0.0, rhoE = 0.0, j[3] = {0.0, 0.0, 0.0}, q[3] = {0.0, 0.0, 0.0};
+    double Pd[3] = {0.0, 0.0, 0.0}, Po[3] = {0.0, 0.0, 0.0};
+    float fs[2] = {0.0f, 0.0f}, sc[NSP];
+    double T_prev;
+    {
+        PullOff o;
+        pull_offsets(L, x, y, z, o);
+        const int k = interface_slot(L, node, x, y, z);
+        const unsigned nb = plane_bytes(L.P, sizeof(S));
+        S f[Q], g[Q];
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int idx = k >= 0 ? (int)N + k : node + o.x[cx_of(i) + 1] + o.y[cy_of(i) + 1] + o.z[cz_of(i) + 1];
+            f[i] = ld_win(src + (size_t)(LF * Q + 9 * (i / 9)) * P, nb, i % 9, idx);
+            g[i] = ld_win(src + (size_t)(LG * Q + 9 * (i / 9)) * P, nb, i % 9, idx);
+        }
+        if constexpr (F32) {
+            flow_scales(L, par, node, fs);
+            species_scales<NSP>(L, par, node, sc);
+        }
+        T_prev = ld_at(aux + AUX_T * N, node);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int cx = cx_of(i), cy = cy_of(i), cz = cz_of(i);
+            const double a = (double)f[i], b = (double)g[i];
+            rho += a;
+            rhoE += b;
+            if (cx) { j[0] += cx > 0 ? a : -a; Pd[0] += a; q[0] += cx > 0 ? b : -b; }
+            if (cy) { j[1] += cy > 0 ? a : -a; Pd[1] += a; q[1] += cy > 0 ? b : -b; }
+            if (cz) { j[2] += cz > 0 ? a : -a; Pd[2] += a; q[2] += cz > 0 ? b : -b; }
+            if (cx * cy) Po[0] += cx * cy > 0 ? a : -a;
+            if (cx * cz) Po[1] += cx * cz > 0 ? a : -a;
+            if (cy * cz) Po[2] += cy * cz > 0 ? a : -a;
+        }
+    }
+    if constexpr (F32) {
+        const RLBM_CONST double* G = as_const(L.ref);
+        const double sf = (double)fs[0];
+        rho += sf * G[REF_M0<NL> + LF];
+        rhoE += (double)fs[1] * G[REF_M0<NL> + LG] + sf * G[REF_K0<NL>];
+        const double p2 = sf * G[REF_M2<NL>];
+        Pd[0] += p2; Pd[1] += p2; Pd[2] += p2;
+        if (valid) store_fscale(L, par ^ 1, node, rho, rhoE);
+    }
+    const double inv_rho = recip(rho);
+    const double u[3] = {j[0] * inv_rho, j[1] * inv_rho, j[2] * inv_rho};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) sp[R::U + d][lane] = u[d];
+    sp[R::RHO][lane] = rho;
+    __syncthreads();   // partial sums
+
+    // composition (eq. density1; the slaved species by difference, eq.
+    // strongest) and temperature (eq. temperature; Newton from the previous
+    // step's value)
+    double Y[M], rY = 0.0;
+    {
+        double rs = rho;
+#pragma unroll
+        for (int l = 0; l < NSP; ++l) {
+            const double* ps = &sp[R::PS + 9 * l][lane];
+            double ra = ps[0] + ps[SPC_NODES] + ps[2 * SPC_NODES];
+            if constexpr (F32) ra += (double)sc[l] * as_const(L.ref)[REF_M0<NL> + l];
+            Y[l] = ra;
+            rY += ra;
+            rs -= ra;
+        }
+        if constexpr (!W) Y[M - 1] = rs;
+    }
+    __syncthreads();   // partial sums read
+    if constexpr (!W) {
+        sp[R::ST + 4 * (M - 1)][lane] = Y[M - 1];
+        rY = rho;
+    }
+    const double inv_rY = W ? recip(rY) : inv_rho;
+#pragma unroll
+    for (int sl = 0; sl < M; ++sl) Y[sl] *= inv_rY;
+    const double usq = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+    const double U = rhoE * inv_rho - 0.5 * usq;
+    int fail = 0;
+    const double T = solve_T<M>(mc0, sp_of, Y, U, T_prev, &fail);
+    if (fail && valid) atomicOr(L.flag, 1);
+    sp[R::T][lane] = T;
+    sp[R::RHOY][lane] = rY;
+    sp[R::UINT][lane] = U;
+    __syncthreads();   // node state
+
+    // relaxation rates
+    double Rmix = 0.0;
+#pragma unroll
+    for (int sl = 0; sl < M; ++sl) Rmix = fma(Y[sl], slotc[sl], Rmix);
+    const double th = Rmix * T, Pr = rho * th;
+    double common, omega, omega1;
+    relax_rates(mc0, T, Pr, Rmix, common, omega, omega1);
+    // what only the energy flux and the record need waits in LDS while the
+    // solve takes the registers
+    {
+        const double Pt[3][3] = {{Pd[0], Po[0], Po[1]}, {Po[0], Pd[1], Po[2]}, {Po[1], Po[2], Pd[2]}};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            double uP = 0.5 * rho * usq * u[a];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) uP += u[c] * (Pt[c][a] - rho * ((a == c ? th : 0.0) + u[c] * u[a]));
+            sp[R::AX + a][lane] = q[a] - uP;
+        }
+    }
+    sp[R::AX + 3][lane] = th;
+    sp[R::AX + 4][lane] = omega;
+    sp[R::AX + 5][lane] = omega1;
+
+    __syncthreads();   // concentrations
+
+    // Stefan-Maxwell system (section 2.3, eq. transform1; dt = 1)
+    //   (1 + 1/(2 tau_a)) V_a - 1/2 sum_{b != a} Y_b V_b / tau_ab = u_a - u,
+    // 1/tau_ab = common K_ab, for the three components.  Off the diagonal the
+    // matrix is -m_ab Y_b with m symmetric, and elimination keeps that form
+    // (m_ij += m_ik m_kj Y_k / d_k), so only the upper triangle of m is formed:
+    // half the products of a general elimination and no division by Y.  The
+    // matrix is strictly row diagonally dominant with margin 1, so no pivoting.
+    double flux[3] = {0.0, 0.0, 0.0};   // sum_a H_a Y_a V_a
+    {
+        const RLBM_CONST double* Ks = slotc + M;
+        const double h = 0.5 * common;
+        double m[M][M], t[M], idg[M], V[M][3];   // m: upper triangle; t = Y_k / d_k
+        double js[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            reload_barrier();
+            const RLBM_CONST double* Ki = Ks + i * M + opaque_zero();
+            double dg = 0.0;
+#pragma unroll
+            for (int c = 0; c < M; ++c)
+                if (c != i) dg = fma(Ki[c], Y[c], dg);
+            dg = fma(h, dg, 1.0);   // 1 + 1/(2 tau_i)
+            if (i < NSP) {
+                // the collision's coefficients, with beta = 1 / (2 tau + 1) = 1 - 1 / dg
+                const double b1 = recip(dg);   // 1 - beta
+                sp[R::A + i][lane] = fma(2.0, b1, -1.0);
+                sp[R::K + i][lane] = -0.5 * b1 * (common * Y[i]);
+            }
+#pragma unroll
+            for (int c = i + 1; c < M; ++c) m[i][c] = h * Ki[c];
+            // u_a - u (u_a := u for an absent species); the slaved one's from
+            // sum_a (j_a - rho_a u) = 0 (eq. strongest)
+            const double ra = sp[R::ST + 4 * i][lane];
+            const double inv = ra <= 1e-14 * rho ? 0.0 : recip(ra);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                double X;
+                if (W || i < M - 1) {
+                    X = sp[R::ST + 4 * i + 1 + d][lane];
+                    js[d] -= X;
+                } else {
+                    X = js[d];
+                }
+                V[i][d] = X * inv;
+            }
+#pragma unroll
+            for (int k = 0; k < i; ++k) {
+                const double e = m[k][i] * t[k];
+                dg = fma(-e * m[k][i], Y[i], dg);
+#pragma unroll
+                for (int c = i + 1; c < M; ++c) m[i][c] = fma(e, m[k][c], m[i][c]);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) V[i][d] = fma(e, V[k][d], V[i][d]);
+            }
+            idg[i] = recip(dg);
+            t[i] = Y[i] * idg[i];
+        }
+#pragma unroll
+        for (int i = M - 1; i >= 0; --i) {
+            reload_barrier();
+            MechC mc = in_loop(mc0);
+            const double hy = species_U(mc, sp_of(i), T) + slotc[i] * T;   // H_a
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                double v = V[i][d];
+#pragma unroll
+                for (int c = i + 1; c < M; ++c) v = fma(m[i][c], V[c][d], v);   // V_c holds Y_c V_c here
+                v *= idg[i];
+                sp[R::ST + 4 * i + 1 + d][lane] = sp[R::U + d][lane] + v;
+                V[i][d] = Y[i] * v;
+                flux[d] = fma(hy, V[i][d], flux[d]);
+            }
+        }
+    }
+    __syncthreads();   // rates
+    write_record<M, S, W>(L, lane, node, x, valid, Y, flux, sp);
+    if (mc0.R > 0) {
+        for (int st = 1; st < L.substeps; ++st) {
+            __syncthreads();
+            __syncthreads();
+        }
+    }
+    __syncthreads();   // collision coefficients (the node's scales have been read)
+    if constexpr (F32) {
+        if (!valid) return;
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        RLBM_GLOBAL f4* so = reinterpret_cast<RLBM_GLOBAL f4*>(as_global(L.rscale[par]) + (size_t)node * L.rss);
+#pragma unroll
+        for (int v = 0; v < (NSP + 3) / 4; ++v) {
+            f4 w = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (4 * v + e < NSP) w[e] = __double2float_rn(sp[R::ST + 4 * (4 * v + e)][lane]);
+            so[v] = w;
+        }
+    }
+}
+
+template <int M, typename S, int W>
+__global__ __launch_bounds__(SPC_THREADS) __attribute__((amdgpu_waves_per_eu(M > 4 && sizeof(S) == 8 ? 2 : 2))) void k_species(
+    const LatDev* __restrict__ lats, const int* __restrict__ blk, int n_lat, const long long* __restrict__ tp, long long toff) {
+    __shared__ double sp[SpcRows<M, W>::N][SPC_NODES];
+    const long long t = step_time(tp, toff);
+    const int b = xcd_block();
+    const int lj = find_lattice(blk, n_lat, b);
+    const LatDev& L = lats[lj];
+    if (t >= L.t_end || L.reaction != RLBM_REACTION_EXPLICIT) return;   // the whole block
+    const int lane = (int)threadIdx.x % SPC_NODES;
+    // the roles rotate with the block, so that the lighter fourth one does not
+    // always fall to the same SIMD
+    const int role = (__builtin_amdgcn_readfirstlane((int)threadIdx.x / SPC_NODES) + (int)blockIdx.x) & 3;
+    const int n = (b - blk[lj]) * SPC_NODES + lane;
+    const bool valid = n < (int)L.N;
+    const int node = valid ? n : (int)L.N - 1;   // beyond the end: a placeholder that writes nothing
+    const int par = (int)((L.parity0 + t) & 1);
+    if (role == 3) node_solve<M, S, W>(L, par, lane, node, valid, sp);
+    else species_layer<M, S, W>(L, par, role, lane, node, valid, sp);
+}
+
+// ---------------------------------------------------------------------------
+// k_flow: the same-time gradients, then the collisions of the momentum and the
+// energy lattice (section 3.2 eq. f, section 3.3 eq. g).  One wave per 64
+// nodes, FLOW_TILES independent tiles per block.  Bound by its traffic: 54
+// populations in and out, the record, and the stencil's reads of nine fields
+// from L2.  The gradients stay in registers: as a kernel of their own they
+// wrote and read six rows per node.
+// ---------------------------------------------------------------------------
+constexpr int FLOW_TILES = 4;
+template <int M, typename S, int W>
+__global__ __launch_bounds__(FLOW_TILES * NODE_TILE) void k_flow(const LatDev* __restrict__ lats, const int* __restrict__ blk,
+                                                                 int n_lat, const long long* __restrict__ tp, long long toff) {
+    constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
+    const long long t = step_time(tp, toff);
+    const int tile = xcd_block() * FLOW_TILES + __builtin_amdgcn_readfirstlane((int)threadIdx.x / NODE_TILE);
+    if (tile >= blk[n_lat]) return;
+    const int lj = find_lattice(blk, n_lat, tile);
+    const LatDev& L = lats[lj];
+    if (t >= L.t_end || L.reaction != RLBM_REACTION_EXPLICIT) return;
+    const int lane = (int)threadIdx.x % NODE_TILE;
+    const int node = (tile - blk[lj]) * NODE_TILE + lane;
+    if (node >= (int)L.N) return;
+    const size_t N = (size_t)L.N, P = (size_t)L.P;
+    const int par = (int)((L.parity0 + t) & 1);
+    const RLBM_GLOBAL S* src = as_global(static_cast<const S*>(L.pop[par]));
+    RLBM_GLOBAL S* dst = as_global(static_cast<S*>(L.pop[par ^ 1]));
+    const RLBM_GLOBAL double* prm = as_global(L.prm);
+    double gr[6];
+    tile_gradients<M>(L, node, lane, gr);
+
+    const double rho = ld_at(prm + PRM_RHO * N, node), U = ld_at(prm + PRM_UINT * N, node), th = ld_at(prm + PRM_TH * N, node);
+    const double omega = ld_at(prm + PRM_OMEGA * N, node), omega1 = ld_at(prm + PRM_OMEGA1 * N, node);
+    double u[3], Qv[3];
+    const double exf = (2.0 - omega) / (2.0 * rho * omega);
+    const double cc = 0.5 * (2.0 - omega1) * (rho * th), wq = 0.5 * (omega - omega1);
+    double E[3][3], Wa[3][3], ka[3][3];   // per axis and c + 1: eq. Pex, eq. geq_i
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        u[d] = ld_at(prm + (PRM_U + d) * N, node);
+        Qv[d] = 0.5 * (ld_corr<sizeof(S) == 4>(prm, PRM_QB + d, N, node) - wq * u[d] * gr[d] + cc * gr[3 + d]);
+        const double P0 = fma(u[d], u[d], th), Px = fma(exf, gr[d], P0);
+        E[d][0] = 0.5 * (Px - u[d]);
+        E[d][1] = 1.0 - Px;
+        E[d][2] = 0.5 * (Px + u[d]);
+        GeqAxis g;
+        geq_axis(u[d], th, g);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) { Wa[d][c] = g.W[c]; ka[d][c] = g.k[c]; }
+    }
+    const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
+    PullOff o;
+    pull_offsets(L, x, y, z, o);
+    const int k = interface_slot(L, node, x, y, z);
+    const unsigned nb = plane_bytes(L.P, sizeof(S));
+    float fs[2] = {0.0f, 0.0f};
+    if constexpr (sizeof(S) == 4) flow_scales(L, par, node, fs);
+#pragma unroll
+    for (int row = 0; row < 9; ++row) {
+        const int c1 = row % 3, c2 = row / 3;
+        const double Eyz = rho * E[1][c1] * E[2][c2];
+        const double Wyz = Wa[1][c1] * Wa[2][c2], kyz = ka[1][c1] * Wa[2][c2] + Wa[1][c1] * ka[2][c2];
+        S fi[3], gi[3];
+        float srd[3][2];
+#pragma unroll
+        for (int c0 = 0; c0 < 3; ++c0) {
+            const int idx = k >= 0 ? (int)N + k : node + o.x[c0] + o.y[c1] + o.z[c2];
+            fi[c0] = ld_win(src + (size_t)(LF * Q + 9 * c2) * P, nb, 3 * c1 + c0, idx);
+            gi[c0] = ld_win(src + (size_t)(LG * Q + 9 * c2) * P, nb, 3 * c1 + c0, idx);
+            if constexpr (sizeof(S) == 4) flow_scales(L, par ^ 1, reader_at(node, o, c0 - 1, c1 - 1, c2 - 1), srd[c0]);
+        }
+#pragma unroll
+        for (int c0 = 0; c0 < 3; ++c0) {
+            const int i = 3 * row + c0;
+            double f = (double)fi[c0], g = (double)gi[c0];
+            const RLBM_CONST double* ref = as_const(L.ref) + opaque_zero();
+            if constexpr (sizeof(S) == 4) {
+                f += ref_of(fs[0], ref[LF * Q + i]);
+                g += ref_g(fs[1], fs[0], ref[LG * Q + i], ref[REF_K<NL> + i]);
+            }
+            const double fo = f + omega * (E[0][c0] * Eyz - f);
+            const double geq = rho * (Wyz * (U * Wa[0][c0] + ka[0][c0]) + Wa[0][c0] * kyz);
+            double go = g + omega * (geq - g);
+            // the singularity-free flux term on the six |c| = 1 velocities
+            if (c2_of(i) == 1) {
+                const int ax = cx_of(i) ? 0 : (cy_of(i) ? 1 : 2);
+                go += (cx_of(i) + cy_of(i) + cz_of(i)) > 0 ? Qv[ax] : -Qv[ax];
+            }
+            if constexpr (sizeof(S) == 4) {
+                st_at(dst + (size_t)(LF * Q + i) * P, node, __double2float_rn(fo - ref_of(srd[c0][0], ref[LF * Q + i])));
+                st_at(dst + (size_t)(LG * Q + i) * P, node,
+                      __double2float_rn(go - ref_g(srd[c0][1], srd[c0][0], ref[LG * Q + i], ref[REF_K<NL> + i])));
+            } else {
+                st_at(dst + (size_t)(LF * Q + i) * P, node, fo);
+                st_at(dst + (size_t)(LG * Q + i) * P, node, go);
+            }
+        }
     }
 }
 
@@ -1427,9 +2142,8 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
     // source f'_{opp(i)}(x)
     float sl = 0.0f, sf = 0.0f;
     if constexpr (sizeof(S) == 4) {
-        const RLBM_GLOBAL float* sc = scale_at(L, par, node);
-        sl = sc[l];
-        sf = sc[LF];
+        sl = scale_l(L, par, node, l, LF);
+        sf = fscale_at(L, par, node)[0];
     }
     // population (l, i) after advection, or with bb on an incoming link the
     // bounce-back source (every lattice at a bounce-back wall, species and
@@ -1442,8 +2156,7 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
         if (bb && ((Dm >> i) & 1u)) {
             v = (double)ld_at(src + (size_t)(l * Q + io) * P, node);
             if constexpr (sizeof(S) == 4) {
-                const RLBM_GLOBAL float* sc = scale_at(L, par, off);
-                const float sb = sc[l], sfb = sc[LF];
+                const float sb = scale_l(L, par, off, l, LF), sfb = fscale_at(L, par, off)[0];
                 v += l == LG ? ref_g(sb, sfb, G[l * Q + io], G[REF_K<NL> + io]) : ref_of(sb, G[l * Q + io]);
             }
         } else {
@@ -1504,7 +2217,7 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
             raw[i] = ld_at(tms && in ? pio : pi, in ? node : off);
             if constexpr (sizeof(S) == 4) {
                 sbv[i] = 0.0f;
-                if (tms && in) sbv[i] = scale_at(L, par, off)[l];   // the reader's scale
+                if (tms && in) sbv[i] = scale_l(L, par, off, l, LF);   // the reader's scale
             }
         });
         for_q<0>([&](auto ic) {
@@ -1738,27 +2451,6 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
 constexpr int IO_NODES = 64;
 constexpr int IO_THREADS = 3 * IO_NODES;
 
-// Node that pulls the population stored at slot (node, i): node + c_i,
-// wrapped on every axis (the placeholder rule of the pull offsets o).
-__device__ __forceinline__ int reader_at(int node, const PullOff& o, int c0, int c1, int c2) {
-    return node + sel3(c0, o.x[2], 0, o.x[0]) + sel3(c1, o.y[2], 0, o.y[0]) + sel3(c2, o.z[2], 0, o.z[0]);
-}
-
-// The NL reference scales of node n in buffer q (FP32 storage), as whole
-// 16-byte loads (rss is a multiple of four floats).
-template <int NL>
-__device__ __forceinline__ void scales_of(const LatDev& L, int q, int n, float (&out)[NL]) {
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    const RLBM_GLOBAL f4* p4 = reinterpret_cast<const RLBM_GLOBAL f4*>(scale_at(L, q, n));
-#pragma unroll
-    for (int v = 0; v < (NL + 3) / 4; ++v) {
-        const f4 w = p4[v];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (4 * v + e < NL) out[4 * v + e] = w[e];
-    }
-}
-
 // Moments of the stored populations of one node over the c_z = c2 layer: rho,
 // rho u, rho E and the stored species' rho_a.  Every load of a row of three
 // velocities is in flight together (NL populations and the reader's scales as
@@ -1848,22 +2540,23 @@ __global__ __launch_bounds__(256) void k_scale_init(const LatDev* __restrict__ l
     if (node >= L.N) return;
     MechC mc = *as_const(L.mech);
     const size_t N = (size_t)L.N;
-    constexpr int NSP = Lat<M, W>::NSP, LF = Lat<M, W>::LF, LG = Lat<M, W>::LG;
+    constexpr int NSP = Lat<M, W>::NSP;
     const int s = W ? M : L.slaved;
     const double rho = rho_in[node];
-    float* so = L.rscale[L.parity0] + (size_t)node * L.rss;
     double Y[M];
 #pragma unroll
     for (int a = 0; a < M; ++a) Y[a] = Y_in[a * N + node];
     for (int l = 0; l < NSP; ++l) {
         const int a = W ? l : l + (l >= s ? 1 : 0);
-        so[l] = __double2float_rn(rho * Y_in[a * N + node]);
+        // both buffers: the populations' own, and what the first step encodes with
+        const float v = __double2float_rn(rho * Y_in[a * N + node]);
+        L.rscale[0][(size_t)node * L.rss + l] = v;
+        L.rscale[1][(size_t)node * L.rss + l] = v;
     }
-    so[LF] = __double2float_rn(rho);
     double usq = 0.0;
 #pragma unroll
     for (int dd = 0; dd < 3; ++dd) usq += u_in[dd * N + node] * u_in[dd * N + node];
-    so[LG] = __double2float_rn(rho * (mix_U<M>(mc, Y, T_in[node]) + 0.5 * usq));
+    store_fscale(L, L.parity0, (int)node, rho, rho * (mix_U<M>(mc, Y, T_in[node]) + 0.5 * usq));
 }
 
 // Initial populations: the equilibria of the given state, k_update's split
@@ -1930,8 +2623,8 @@ __global__ __launch_bounds__(IO_THREADS) void k_init(const LatDev* __restrict__ 
             RLBM_GLOBAL S* pl = dst + (size_t)(l * Q + i) * P;
             if constexpr (sizeof(S) == 4) {
                 const int rd = reader_at(node, o, c0 - 1, c1 - 1, c2);
-                const RLBM_GLOBAL float* sc = scale_at(L, L.parity0, rd);
-                const double ref = l == LG ? ref_g(sc[LG], sc[LF], G[l * Q + i], G[REF_K<NL> + i]) : ref_of(sc[l], G[l * Q + i]);
+                const float sl = scale_l(L, L.parity0, rd, l, LF), sf = fscale_at(L, L.parity0, rd)[0];
+                const double ref = l == LG ? ref_g(sl, sf, G[l * Q + i], G[REF_K<NL> + i]) : ref_of(sl, G[l * Q + i]);
                 st_at(pl, node, __double2float_rn(v - ref));
             } else {
                 st_at(pl, node, v);
@@ -1987,6 +2680,7 @@ __global__ __launch_bounds__(512) void k_refs(const LatDev* __restrict__ lat, do
         if (l < NSP) th = mc.Ra[W ? l : l + (l >= L.slaved ? 1 : 0)] * T;
         // shapes are rounded to FP32 values (see ref_of)
         ref[li] = (double)(float)(psi(c0, 0.0, th) * psi(c1, 0.0, th) * psi(c2, 0.0, th));
+        ref[REF_T<NL> + i * NL + l] = ref[li];
         if (l == LG) {
             const double Wx = psi(c0, 0.0, th), Wy = psi(c1, 0.0, th), Wz = psi(c2, 0.0, th);
             const double k0 = -th * th, k1 = 0.5 * th * th;
@@ -2089,8 +2783,9 @@ __global__ __launch_bounds__(256) void k_pops(const LatDev* __restrict__ lat, lo
         const RLBM_CONST double* G = as_const(L.ref);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const RLBM_GLOBAL float* sc = scale_at(L, q, reader_at(node, o, c - 1, (int)blockIdx.y % 3 - 1, (int)blockIdx.y / 3 - 1));
-            ref[c] = l == LG ? ref_g(sc[LG], sc[LF], G[l * Q + i0 + c], G[REF_K<NL> + i0 + c]) : ref_of(sc[l], G[l * Q + i0 + c]);
+            const int rd = reader_at(node, o, c - 1, (int)blockIdx.y % 3 - 1, (int)blockIdx.y / 3 - 1);
+            const float sl = scale_l(L, q, rd, l, LF), sf = fscale_at(L, q, rd)[0];
+            ref[c] = l == LG ? ref_g(sl, sf, G[l * Q + i0 + c], G[REF_K<NL> + i0 + c]) : ref_of(sl, G[l * Q + i0 + c]);
         }
     }
 #pragma unroll
@@ -2288,22 +2983,30 @@ template <typename S>
 static hipError_t launch_step_phase(int phase, int M, int weak, const StepLaunch& a) {
     if (a.blocks <= 0) return hipSuccess;
     (void)hipGetLastError();   // report this launch's error only
+    const bool explicit_ = a.schemes & (1u << RLBM_REACTION_EXPLICIT);
+    const bool implicit_ = a.schemes & (1u << RLBM_REACTION_LINEARLY_IMPLICIT);
     if (phase == 0) {
         RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_boundary<MM, S, WW>), dim3(a.blocks), dim3(bc_threads<MM, WW>()), 0,
                                                     a.stream, a.lats, a.blk, a.n_lat, a.tp, a.toff))
     } else if (phase == 1) {
-        RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_local<MM, S, WW>), dim3(a.blocks), dim3(NODE_TILE), 0, a.stream,
-                                                    a.lats, a.blk, a.n_lat, a.tp, a.toff))
+        if (explicit_)
+            RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_species<MM, S, WW>), dim3(a.blocks), dim3(SPC_THREADS), 0, a.stream,
+                                                        a.lats, a.blk, a.n_lat, a.tp, a.toff))
+        if (implicit_)
+            RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_local<MM, S, WW>), dim3(a.blocks), dim3(NODE_TILE), 0, a.stream,
+                                                        a.lats, a.blk, a.n_lat, a.tp, a.toff))
     } else if (phase == 2) {
-        if (a.schemes & (1u << RLBM_REACTION_EXPLICIT))
-            RLBM_DISPATCH(M, hipLaunchKernelGGL((k_gradients<MM>), dim3((a.blocks + GRAD_TILES - 1) / GRAD_TILES), dim3(GRAD_TILES * NODE_TILE), 0, a.stream, a.lats,
-                                                    a.blk, a.n_lat, a.tp, a.toff))
-        if (a.schemes & (1u << RLBM_REACTION_LINEARLY_IMPLICIT))
+        if (implicit_)
             RLBM_DISPATCH(M, hipLaunchKernelGGL((k_chem_implicit<MM>), dim3(a.blocks), dim3(NODE_TILE), 0, a.stream, a.lats,
-                                                    a.blk, a.n_lat, a.tp, a.toff))
+                                                a.blk, a.n_lat, a.tp, a.toff))
     } else {
-        RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_update<MM, S, WW>), dim3(a.blocks), dim3(UPD_THREADS), 0,
-                                                    a.stream, a.lats, a.blk, a.n_lat, a.tp, a.toff))
+        if (explicit_)
+            RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_flow<MM, S, WW>), dim3((a.blocks + FLOW_TILES - 1) / FLOW_TILES),
+                                                        dim3(FLOW_TILES * NODE_TILE), 0, a.stream, a.lats, a.blk, a.n_lat,
+                                                        a.tp, a.toff))
+        if (implicit_)
+            RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_update<MM, S, WW>), dim3(a.blocks), dim3(UPD_THREADS), 0,
+                                                        a.stream, a.lats, a.blk, a.n_lat, a.tp, a.toff))
     }
     return hipGetLastError();
 }

@@ -16,7 +16,7 @@ struct StepLaunch {
     const long long* tp;  // device step counter of the launch series, or NULL (counter 0)
     long long toff;       // step of this launch: *tp + toff
     hipStream_t stream;
-    unsigned schemes;     // bit r set if a lattice uses RLBM_REACTION r (phase 2 launches one kernel per scheme)
+    unsigned schemes;     // bit r set if a lattice uses RLBM_REACTION r (phases 1 to 3 launch one kernel per scheme)
 };
 
 // Interface nodes per boundary block (one wave, one lane per node).
@@ -28,10 +28,12 @@ constexpr int BC_NODES = 64;
 #endif
 constexpr int NODE_TILE = RLBM_NODE_TILE;
 
-// phase 0: boundary (BC_NODES interface nodes per block); phases 1 and 2:
-// moments, diffusion and forward-Euler chemistry, then gradients (with the
-// linearly implicit chemistry first where selected) (NODE_TILE-thread blocks
-// over nodes); phase 3: update (one block per 64 nodes).
+// phase 0: boundary (BC_NODES interface nodes per block); phase 1: moments,
+// diffusion, forward-Euler chemistry and the species' collision (lattices with
+// the linearly implicit update: moments and diffusion only); phase 2: the
+// linearly implicit chemistry and its gradients, where selected; phase 3:
+// gradients and the collisions of f and g (linearly implicit: every
+// collision).  Phases 1 to 3 take 64 nodes per block entry.
 hipError_t launch_phase(int phase, int M, int storage, int weak, const StepLaunch& a);
 // weak: the weakly coupled storage (all M species lattices, no slaved species)
 hipError_t launch_init(int M, int storage, int weak, const LatDev* lat, long long N, const double* rho,

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "rlbm.h"
 
 namespace rlbm {
@@ -30,13 +32,23 @@ __host__ __device__ constexpr int c2_of(int i) {
 struct RxnDev {
     double lnA, beta, Ta, dnu_sum;
     int rev, nf, nr, pad_;
-    int fac_f[MAXO], fac_r[MAXO];   // species per molecule; entries past nf / nr hold 0
+    int fac_f[MAXO], fac_r[MAXO];   // species per molecule; entries past nf / nr hold M, the neutral row
     double dnu[MAXM];
 };
 
+// exp(r) = 1 + r + r^2/2 + r^3 (e_0 + e_1 r + ... + e_8 r^8) on |r| <= ln(2)/2:
+// e from a Remez exchange on the relative error, which is 2.4e-17.  Kept with
+// the mechanism, whose constants are scalar loads: as literals each would cost
+// a vector move per use.
+constexpr int EXP_COEF = 9;
+constexpr double EXP_E[EXP_COEF] = {0x1.5555555554eaep-3,  0x1.5555555553af1p-5,  0x1.11111112d4085p-7,
+                                    0x1.6c16c17a09e36p-10, 0x1.a019f7c0f05dep-13, 0x1.a019b37426f14p-16,
+                                    0x1.71f4b709e3d97p-19, 0x1.28979356d3041p-22, 0x1.8abb946ab6a7ep-26};
+
 // Mechanism in the layout the kernels read (uniform addresses: scalar loads).
 struct MechDev {
-    int M, R, E, pad_;
+    int M, R, E;
+    int max_side;               // most molecules on one side of a reaction
     double m[MAXM];             // molar masses
     double inv_m[MAXM];
     double Ra[MAXM];            // R_univ / m_a
@@ -47,6 +59,7 @@ struct MechDev {
     double R_univ, ln_cstd;
     // reactions, one contiguous record each (one scalar base per reaction)
     RxnDev rx[MAXR];
+    double ec[EXP_COEF];        // coefficients of expo()
     // transport
     double T_ref, inv_T_ref, P_ref, inv_P_ref, mu_ref, mu_exp, inv_Pr, D_exp;
     double Kab[MAXM][MAXM];     // 1 / (D_ref[a][b] m_a m_b)
@@ -75,9 +88,10 @@ struct LatDev {
     const double* if_T;         // [n_if] wall target temperature
     const int* if_out;          // [n_if] outlet slot or -1
     double* out_state;          // [5 + M][n_out]: rho, ux, uy, uz, T, Y
-    const double* ref;          // [L * 27] reference shapes G_li, then [L] sum_i G_li, then sum_i G_fi c_ix^2 (FP32 storage)
-    float* rscale[2];           // [N][rss] reference scales s_l of the populations in pop[q] (FP32 storage)
-    int rss, pad2;              // floats per node in rscale (L rounded up to 4)
+    const double* ref;          // reference shapes and their moments (FP32 storage; REF_* in kernels.hip)
+    float* rscale[2];           // [N][rss] reference scales s_l of the species populations in pop[q] (FP32 storage)
+    float* fscale[2];           // [N][2] the same of the momentum and the energy populations (rho, rho E)
+    int rss, pad2;              // floats per node in rscale (the stored species, rounded up to 4)
     const double* slotc;        // [M + M * M] R_a and 1/(D_ref m_a m_b) in slot order (slaved species last)
     double rho_in, u_in, T_in, P_inf, sigma;
     double Y_in[MAXM];
@@ -96,6 +110,7 @@ constexpr int AUX_RHO = 0, AUX_U = 1, AUX_T = 4, AUX_PHI = 5, AUX_Y = 8;
 // derives them once per node and keeps them in its LDS copy of the record.
 constexpr int PRM_RHO = 0, PRM_U = 1, PRM_T = 4, PRM_UINT = 5, PRM_TH = 6, PRM_OMEGA = 7, PRM_COMMON = 8,
               PRM_QB = 9, PRM_WQ = 12, PRM_CC = 13, PRM_SP = 14;
+constexpr int PRM_OMEGA1 = PRM_COMMON;   // the row holds omega_1 in the record that k_flow reads
 // species rows: PRM_SP + 6 a + {0: rho_a, 1..3: V_a, 4: beta_a, 5: drho_a}
 __host__ __device__ constexpr int prm_grad(int M) { return PRM_SP + 6 * M; }   // d (3), sum H grad Y (3)
 __host__ __device__ constexpr int prm_rows(int M) { return PRM_SP + 6 * M + 6; }
@@ -147,6 +162,12 @@ __device__ __forceinline__ int opaque_zero() {
     asm volatile("s_mov_b32 %0, 0" : "=s"(z));
     return z;
 }
+// Hides the value of a uniform pointer: addresses stepped from it are formed
+// where they are used (two scalar adds) instead of all kept in registers.
+template <typename P>
+__device__ __forceinline__ void opaque(P& p) {
+    asm volatile("" : "+s"(p));
+}
 template <typename T>
 __device__ __forceinline__ const RLBM_CONST T& in_loop(const RLBM_CONST T& r) {
     return *(&r + opaque_zero());
@@ -184,11 +205,48 @@ __device__ __forceinline__ void geq_axis(double u, double th, GeqAxis& a) {
     a.k[2] = 0.5 * (o2 + o1);
 }
 
-__device__ __forceinline__ double geq_i(int i, double rho, double U, const GeqAxis& X,
-                                        const GeqAxis& Yy, const GeqAxis& Z) {
-    const int a = cx_of(i) + 1, b = cy_of(i) + 1, c = cz_of(i) + 1;
-    const double wyz = Yy.W[b] * Z.W[c];
-    return rho * (U * X.W[a] * wyz + X.k[a] * wyz + X.W[a] * (Yy.k[b] * Z.W[c] + Yy.W[b] * Z.k[c]));
+// 1/x to within an ulp: the hardware estimate and two Newton steps (8 cycles
+// each of a wave's issue time, 32 in all, where the IEEE division with its
+// scaling takes 60).  For normal x away from overflow; 1/0 gives NaN.
+__device__ __forceinline__ double recip(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// Natural logarithm of a positive normal x to within about an ulp of max(1,
+// |ln x|): x = 2^k m with m in [sqrt(1/2), sqrt(2)), ln m = 2 artanh s with
+// s = (m - 1)/(m + 1), |s| < 0.172, by its power series to s^23 (the first
+// term left out is below 2^-66).  About 130 cycles where the library's log, which
+// carries twice the precision inside, takes 400.  Zero and negative x give a
+// finite value, NaN gives NaN.
+__device__ __forceinline__ double ln(double x) {
+    double m = __builtin_amdgcn_frexp_mant(x);   // [1/2, 1)
+    int k = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.70710678118654752;
+    m = low ? 2.0 * m : m;
+    k = low ? k - 1 : k;
+    const double s = (m - 1.0) * recip(m + 1.0), z = s * s;
+    double p = 1.0 / 23.0;
+#pragma unroll
+    for (int n = 21; n >= 3; n -= 2) p = fma(p, z, 1.0 / n);
+    // ln 2 in two parts, the first with trailing zeros so that k times it is exact
+    const double hi = 0x1.62e42fefap-1, lo = 0x1.cf79abc9e3b39p-40;
+    const double t = s + s;
+    return fma((double)k, hi, fma((double)k, lo, fma(t * z, p, t)));
+}
+
+// exp(x) to about an ulp, e the coefficients above: x = n ln 2 + r.  Beyond
+// |x| = 1000 the result is 0 or infinity already.
+__device__ __forceinline__ double expo(const RLBM_CONST double* e, double x) {
+    x = fmin(fmax(x, -1000.0), 1000.0);
+    const double n = __builtin_rint(x * 0x1.71547652b82fep+0);
+    const double r = fma(-n, 0x1.cf79abc9e3b39p-40, fma(-n, 0x1.62e42fefap-1, x));
+    double p = e[EXP_COEF - 1];
+#pragma unroll
+    for (int k = EXP_COEF - 2; k >= 0; --k) p = fma(p, r, e[k]);
+    p = fma(fma(fma(p, r, 0.5), r, 1.0), r, 1.0);
+    return __builtin_amdgcn_ldexp(p, (int)n);
 }
 
 // ---------------------------------------------------------------------------
@@ -203,15 +261,15 @@ __device__ __forceinline__ double mix_inv_m(MechC mc, const double* Y) {
 }
 
 // Collapse sum_a Y_a U_a(T) into one quintic and solve for T by Newton.
-template <int M>
-__device__ __forceinline__ double solve_T(MechC mc, const double* Y, double U,
-                                          double T, int* fail) {
+// Y[q] belongs to species sp(q).
+template <int M, typename Sp>
+__device__ __forceinline__ double solve_T(MechC mc, Sp&& sp, const double* Y, double U, double T, int* fail) {
     // species-major, so that one species' six coefficients are live at a
     // time (each c[k] still sums over a in order)
     double c[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int a = 0; a < M; ++a) {
-        const RLBM_CONST double* u = mc.uc[a];
+        const RLBM_CONST double* u = mc.uc[sp(a)];
 #pragma unroll
         for (int k = 0; k < 6; ++k) c[k] += Y[a] * u[k];
     }
@@ -219,12 +277,16 @@ __device__ __forceinline__ double solve_T(MechC mc, const double* Y, double U,
     for (int it = 0; it < 100; ++it) {
         const double F = c[0] + T * (c[1] + T * (c[2] + T * (c[3] + T * (c[4] + T * c[5]))));
         const double dF = c[1] + T * (2.0 * c[2] + T * (3.0 * c[3] + T * (4.0 * c[4] + T * 5.0 * c[5])));
-        const double dT = F / dF;
+        const double dT = F * recip(dF);
         T -= dT;
         if (fabs(dT) <= 1e-12 * fabs(T)) return T;
     }
     *fail = 1;
     return T;
+}
+template <int M>
+__device__ __forceinline__ double solve_T(MechC mc, const double* Y, double U, double T, int* fail) {
+    return solve_T<M>(mc, [](int a) { return a; }, Y, U, T, fail);
 }
 
 template <int M>
@@ -270,7 +332,7 @@ template <int NT>
 struct ChemLds {
     double* c;   // &c[0][tid]
     double* g;   // &g[0][tid]
-    double* dq;  // &dq[0][tid], or nullptr without the Jacobian
+    double* dq;  // &dq[0][tid]
 };
 
 // Adds k prod_{g != f} c[g] to dq[fac[f]] for every factor f < n (c[f] = 1
@@ -290,7 +352,52 @@ __device__ __forceinline__ void scatter_factor_derivs(const ChemLds<NT>& ls, con
     for (int f = 0; f < MAXO; ++f) ls.dq[fac[f] * NT] += f < n ? pre[f] * suf[f] : 0.0;
 }
 
-// Production rates rho_dot_a and, with JAC, the Jacobian J[a][b] =
+// Molar production rates of the reactions r0, r0 + dr, r0 + 2 dr, ...:
+// w_a += dnu_a q_r, from the node's column cg, rows 2 a and 2 a + 1 the
+// concentration and the Gibbs function of species a (M + 1 pairs, the last one
+// neutral).
+template <int M, int NT>
+__device__ __forceinline__ void reaction_rates(MechC mc0, const double* cg, double lnT, double invT, int r0, int dr,
+                                               double* w) {
+    const int R = mc0.R;
+    const double lnc = mc0.ln_cstd - lnT;
+    const RLBM_CONST double* ec = mc0.ec;
+    // Unused factor slots name the neutral row M (c = 1, g = 0), so no slot
+    // needs a mask; mechanisms with at most two molecules on every side (the
+    // usual ones) read two slots per side.  No branches: a reaction is one
+    // dependent chain (record, LDS factors, exp), and two of them are
+    // interleaved because a wave has nothing else to issue meanwhile.
+    auto rate = [&](const RLBM_CONST RxnDev& x, auto slots) -> double {
+        constexpr int NS = decltype(slots)::value;
+        const double lnkf = x.lnA + x.beta * lnT - x.Ta * invT;
+        double pf = 1.0, pr = 1.0, sg = 0.0;
+#pragma unroll
+        for (int f = 0; f < NS; ++f) {
+            const double* a = cg + x.fac_f[f] * (2 * NT);
+            const double* b = cg + x.fac_r[f] * (2 * NT);
+            pf = f ? pf * a[0] : a[0];
+            pr = f ? pr * b[0] : b[0];
+            sg = f ? sg + (b[NT] - a[NT]) : b[NT] - a[NT];
+        }
+        // k_r = k_f / K_c, ln K_c = -sum_a dnu_a g_a/(R T) + (sum_a dnu_a) ln c_std
+        const double kf = expo(ec, lnkf), kr = expo(ec, lnkf + sg - x.dnu_sum * lnc);
+        return fma(kf, pf, x.rev ? -kr * pr : 0.0);
+    };
+    auto all = [&](auto slots) {
+        for (int r = r0; r < R; r += 2 * dr) {
+            MechC mc = in_loop(mc0);
+            const bool two = r + dr < R;
+            const RLBM_CONST RxnDev &x = mc.rx[r], &x2 = mc.rx[two ? r + dr : r];
+            const double q = rate(x, slots), v = rate(x2, slots), q2 = two ? v : 0.0;
+#pragma unroll
+            for (int a = 0; a < M; ++a) w[a] = fma(x2.dnu[a], q2, fma(x.dnu[a], q, w[a]));
+        }
+    };
+    if (mc0.max_side <= 2) all(std::integral_constant<int, 2>{});
+    else all(std::integral_constant<int, MAXO>{});
+}
+
+// Production rates rho_dot_a and the Jacobian J[a][b] =
 // d rho_dot_a / d rho_b at fixed T in the reduced form used by the linearly
 // implicit step (K = M - 1 is the last species):
 //   Jr[a][b] = J[a][b] - J[a][K],   a, b < K.
@@ -298,21 +405,19 @@ __device__ __forceinline__ void scatter_factor_derivs(const ChemLds<NT>& ls, con
 // of the product is the sum, over the factors that are species b, of the
 // product of the other factors; the clip max(c, 0) is differentiated as the
 // identity.
-template <int M, int NT, bool JAC>
+template <int M, int NT>
 __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double T, const ChemLds<NT>& ls,
                                           double* wdot, double (*Jr)[M - 1]) {
     constexpr int K = M - 1;
     MechC mc = mc0;
 #pragma unroll
     for (int a = 0; a < M; ++a) wdot[a] = 0.0;
-    if constexpr (JAC) {
 #pragma unroll
-        for (int a = 0; a < M; ++a) ls.dq[a * NT] = 0.0;
+    for (int a = 0; a < M; ++a) ls.dq[a * NT] = 0.0;
 #pragma unroll
-        for (int a = 0; a < K; ++a)
+    for (int a = 0; a < K; ++a)
 #pragma unroll
-            for (int b = 0; b < K; ++b) Jr[a][b] = 0.0;
-    }
+        for (int b = 0; b < K; ++b) Jr[a][b] = 0.0;
     const int R = mc.R;
     if (R == 0) return;
     const double lnT = log(T);
@@ -329,7 +434,7 @@ __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double
         const int nf = x.nf, nr = x.nr;
         const double lnkf = x.lnA + x.beta * lnT - x.Ta * invT;
         // forward rate k_f prod_b c_b^nu'_b
-        // Every factor slot is read (unused slots name species 0) and masked
+        // Every factor slot is read (unused slots name the row M) and masked
         // to 1 or 0, so the factor loops have no branches: the index loads
         // merge into wide scalar loads and the LDS reads issue together.
         double cf[MAXO];
@@ -342,7 +447,7 @@ __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double
         double fwd = kf;
 #pragma unroll
         for (int f = 0; f < MAXO; ++f) fwd *= cf[f];
-        if constexpr (JAC) scatter_factor_derivs<NT>(ls, x.fac_f, nf, cf, kf);
+        scatter_factor_derivs<NT>(ls, x.fac_f, nf, cf, kf);
         double q = fwd;
         if (x.rev) {
             // k_r = k_f / K_c, ln K_c = -sum_a dnu_a g_a/(R T) + (sum_a dnu_a) ln c_std
@@ -365,12 +470,12 @@ __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double
             double bwd = kr;
 #pragma unroll
             for (int f = 0; f < MAXO; ++f) bwd *= cr[f];
-            if constexpr (JAC) scatter_factor_derivs<NT>(ls, x.fac_r, nr, cr, -kr);
+            scatter_factor_derivs<NT>(ls, x.fac_r, nr, cr, -kr);
             q -= bwd;
         }
 #pragma unroll
         for (int a = 0; a < M; ++a) wdot[a] = fma(x.dnu[a], q, wdot[a]);
-        if constexpr (JAC) {
+        {
             // d rho_dot_a / d rho_b = m_a dnu_a dq_b / m_b summed over the
             // reactions; Jr[a][b] += dnu_a (dq_b / m_b - dq_K / m_K), m_a below
             const double dK = ls.dq[K * NT] * mc.inv_m[K];
@@ -386,18 +491,10 @@ __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double
     }
 #pragma unroll
     for (int a = 0; a < M; ++a) wdot[a] *= mc.m[a];
-    if constexpr (JAC) {
 #pragma unroll
-        for (int a = 0; a < K; ++a)
+    for (int a = 0; a < K; ++a)
 #pragma unroll
-            for (int b = 0; b < K; ++b) Jr[a][b] *= mc.m[a];
-    }
-}
-
-template <int M, int NT>
-__device__ __forceinline__ void production_rates(MechC mc, const double* rho_a, double T, const ChemLds<NT>& ls,
-                                                 double* wdot) {
-    rates_jac<M, NT, false>(mc, rho_a, T, ls, wdot, nullptr);
+        for (int b = 0; b < K; ++b) Jr[a][b] *= mc.m[a];
 }
 
 // Solves A x = b in place (x returned in b) by Gaussian elimination with
@@ -439,14 +536,13 @@ __device__ __forceinline__ void solve_pivoted(double (*A)[M], double* b) {
     }
 }
 
-// Densities after one step of l sub-steps at frozen U: forward Euler
-// (eq. R3) or, with IMPL, linearly implicit sub-steps
+// Densities after one step of l linearly implicit sub-steps at frozen U,
 // (I - dt^r J) Delta = dt^r rho_dot.  Every reaction conserves mass (checked
 // when the mechanism is created), so the columns of J sum to zero, and so do
 // rho_dot and Delta: the last row of the system is the negative sum of the
 // others.  It is dropped, with Delta_K = -sum_{a<K} Delta_a substituted, which
 // leaves (I - dt^r Jr) Delta_{<K} = dt^r rho_dot_{<K} of size M - 1.
-template <int M, int NT, bool IMPL>
+template <int M, int NT>
 __device__ __forceinline__ void reaction_increment(MechC mc0, const double* rho_a, double rho, double U, double T,
                                                    int l, const ChemLds<NT>& ls, double* out, int* fail) {
     constexpr int K = M - 1;
@@ -469,28 +565,22 @@ __device__ __forceinline__ void reaction_increment(MechC mc0, const double* rho_
             for (int a = 0; a < M; ++a) Y[a] = cur[a] * inv_rho;
             Ts = solve_T<M>(mc, Y, U, Ts, fail);
         }
-        if constexpr (IMPL) {
-            double A[K][K];
-            rates_jac<M, NT, true>(mc, cur, Ts, ls, w, A);
+        double A[K][K];
+        rates_jac<M, NT>(mc, cur, Ts, ls, w, A);
 #pragma unroll
-            for (int a = 0; a < K; ++a) {
+        for (int a = 0; a < K; ++a) {
 #pragma unroll
-                for (int b = 0; b < K; ++b) A[a][b] = (a == b ? 1.0 : 0.0) - inv_l * A[a][b];
-                w[a] *= inv_l;
-            }
-            solve_pivoted<K>(A, w);
-            double sum = 0.0;
-#pragma unroll
-            for (int a = 0; a < K; ++a) {
-                cur[a] += w[a];
-                sum += w[a];
-            }
-            cur[K] -= sum;
-        } else {
-            production_rates<M, NT>(mc, cur, Ts, ls, w);
-#pragma unroll
-            for (int a = 0; a < M; ++a) cur[a] += w[a] * inv_l;
+            for (int b = 0; b < K; ++b) A[a][b] = (a == b ? 1.0 : 0.0) - inv_l * A[a][b];
+            w[a] *= inv_l;
         }
+        solve_pivoted<K>(A, w);
+        double sum = 0.0;
+#pragma unroll
+        for (int a = 0; a < K; ++a) {
+            cur[a] += w[a];
+            sum += w[a];
+        }
+        cur[K] -= sum;
     }
 #pragma unroll
     for (int a = 0; a < M; ++a) out[a] = cur[a];

@@ -43,7 +43,7 @@ constexpr int NPHASE = 4;   // boundary, moments + diffusion, chemistry + gradie
 struct Plan {
     size_t off_lat, off_mech, off_blk, off_flag, off_ref, off_pop0, off_pop1, off_aux, off_prm, off_ifindex, off_ifnode,
         off_ifmask, off_iftype, off_ifT, off_ifout, off_out, off_partial, off_invout, off_slot,
-        off_rscale0, off_rscale1, total;
+        off_rscale0, off_rscale1, off_fscale0, off_fscale1, total;
 };
 
 struct Geometry {
@@ -205,6 +205,16 @@ int check_planes(const rlbm_lattice_desc* d, const Geometry& g) {
     return RLBM_OK;
 }
 
+// Floats per node of a buffer's species scales (FP32 storage): the stored
+// species, rounded up to whole 16-byte loads.
+int scale_stride(int L, int storage) { return storage == RLBM_STORAGE_F32_DEV ? (L - 2 + 3) / 4 * 4 : 0; }
+
+// Reference table of L stored lattices: shapes [L][27], their moments [L], one
+// second moment, the energy lattice's K [27] and its sum; then the shapes once
+// more as [27][L].
+size_t ref_doubles_v1(int L) { return (size_t)L * Q + L + Q + 2; }
+size_t ref_doubles(int L) { return ref_doubles_v1(L) + (size_t)L * Q; }
+
 Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     Plan p{};
     const int L = stored_lattices(d, M);
@@ -218,7 +228,7 @@ Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     p.off_mech = take(sizeof(MechDev));
     p.off_blk = take(6 * sizeof(int));
     p.off_flag = take(sizeof(int));
-    p.off_ref = take(((size_t)L * Q + L + Q + 2) * sizeof(double));
+    p.off_ref = take(ref_doubles(L) * sizeof(double));
     p.off_slot = take((size_t)(M + M * M) * sizeof(double));
     const size_t P = plane_stride(g);
     p.off_pop0 = take((size_t)L * Q * P * s);
@@ -234,9 +244,11 @@ Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     p.off_out = take((size_t)(5 + M) * g.n_out * sizeof(double));
     p.off_partial = take(nblocks * (6 + E) * sizeof(double));
     p.off_invout = take((6 + E) * sizeof(double));
-    const size_t rss = d->storage == RLBM_STORAGE_F32_DEV ? (size_t)((L + 3) / 4 * 4) : 0;
+    const size_t rss = (size_t)scale_stride(L, d->storage), fss = d->storage == RLBM_STORAGE_F32_DEV ? 2 : 0;
     p.off_rscale0 = take(rss * N * sizeof(float));
     p.off_rscale1 = take(rss * N * sizeof(float));
+    p.off_fscale0 = take(fss * N * sizeof(float));
+    p.off_fscale1 = take(fss * N * sizeof(float));
     p.total = o;
     return p;
 }
@@ -303,6 +315,7 @@ int rlbm_mech_create(const rlbm_mech_desc* d, rlbm_mech** out) {
     md.M = M; md.R = R; md.E = E;
     md.R_univ = d->R_univ;
     md.ln_cstd = d->ln_cstd;
+    for (int k = 0; k < EXP_COEF; ++k) md.ec[k] = EXP_E[k];
     for (int a = 0; a < M; ++a) {
         const double ma = d->molar_mass[a];
         if (!(ma > 0)) { delete m; return fail(RLBM_EINVAL, "molar masses must be > 0"); }
@@ -355,6 +368,9 @@ int rlbm_mech_create(const rlbm_mech_desc* d, rlbm_mech** out) {
             for (int k = 0; k < f; ++k) x.fac_f[x.nf++] = a;
             for (int k = 0; k < b; ++k) x.fac_r[x.nr++] = a;
         }
+        md.max_side = std::max(md.max_side, std::max(x.nf, x.nr));
+        for (int k = x.nf; k < RLBM_MAX_ORDER; ++k) x.fac_f[k] = M;   // the neutral row
+        for (int k = x.nr; k < RLBM_MAX_ORDER; ++k) x.fac_r[k] = M;
         x.dnu_sum = s;
         // sum_a m_a dnu_a = 0: the rates conserve mass (eq. sumRhoDot)
         double net = 0.0, gross = 0.0;
@@ -458,9 +474,13 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
     h.if_out = (const int*)(base + p.off_ifout);
     h.out_state = (double*)(base + p.off_out);
     h.ref = d->storage == RLBM_STORAGE_F32_DEV ? (const double*)(base + p.off_ref) : nullptr;
-    h.rss = d->storage == RLBM_STORAGE_F32_DEV ? (lat->L + 3) / 4 * 4 : 0;
-    h.rscale[0] = d->storage == RLBM_STORAGE_F32_DEV ? (float*)(base + p.off_rscale0) : nullptr;
-    h.rscale[1] = d->storage == RLBM_STORAGE_F32_DEV ? (float*)(base + p.off_rscale1) : nullptr;
+    h.rss = scale_stride(lat->L, d->storage);
+    if (d->storage == RLBM_STORAGE_F32_DEV) {
+        h.rscale[0] = (float*)(base + p.off_rscale0);
+        h.rscale[1] = (float*)(base + p.off_rscale1);
+        h.fscale[0] = (float*)(base + p.off_fscale0);
+        h.fscale[1] = (float*)(base + p.off_fscale1);
+    }
     const rlbm_face& fi = d->faces[0];
     if (is_inlet(fi.type)) {
         h.rho_in = fi.rho_in; h.u_in = fi.u_in; h.T_in = fi.T_in;
@@ -634,6 +654,7 @@ static int step_one(rlbm_lattice* lat, long long t) {
         a.stream = lat->stream;
         a.schemes = 1u << lat->host.reaction;
         if (a.blocks == 0) continue;
+        if (phase == 2 && lat->host.reaction == RLBM_REACTION_EXPLICIT) continue;   // the update takes the gradients
         Timing* ev = nullptr;
         if (lat->timing >> phase & 1u) {
             if (lat->n_events == lat->events.size()) {
@@ -762,23 +783,33 @@ struct StateHeader {
     int32_t M, L, storage, slaved, rss, pad;
     int64_t N, n_out;
 };
+// Version 2 holds the species scales of both buffers (the populations' own and
+// those the next step encodes with) and the scales of f and g.  Version 1 held
+// one vector per node (species, rho, rho E; L rounded up to four floats) of
+// the populations' own scales; it is still loaded, and the next step then
+// encodes with those too.
+constexpr uint32_t STATE_VERSION = 2u;
 struct StateLayout {
-    size_t ref, pops, scale, aux, out, total;
-    size_t n_ref, n_pops, n_scale, n_aux, n_out;   // bytes of each section
+    size_t ref, pops, scale, scale_next, fscale, aux, out, total;
+    size_t n_ref, n_pops, n_scale, n_fscale, n_aux, n_out;   // bytes of each section
 };
-StateLayout state_layout(const rlbm_lattice* lat) {
+size_t v1_stride(const rlbm_lattice* lat) { return (size_t)(lat->L + 3) / 4 * 4; }
+StateLayout state_layout(const rlbm_lattice* lat, uint32_t version = STATE_VERSION) {
     StateLayout s{};
     const size_t N = (size_t)lat->geo.N, L = (size_t)lat->L, M = (size_t)lat->M;
     const bool f32 = lat->storage == RLBM_STORAGE_F32_DEV;
-    s.n_ref = f32 ? (L * Q + L + Q + 2) * sizeof(double) : 0;
+    s.n_ref = f32 ? (version == 1u ? ref_doubles_v1(lat->L) : ref_doubles(lat->L)) * sizeof(double) : 0;
     s.n_pops = L * Q * (size_t)lat->host.P * (f32 ? 4 : 8);
-    s.n_scale = f32 ? (size_t)lat->host.rss * N * sizeof(float) : 0;
+    s.n_scale = f32 ? (version == 1u ? v1_stride(lat) : (size_t)lat->host.rss) * N * sizeof(float) : 0;
+    s.n_fscale = f32 && version != 1u ? 2 * N * sizeof(float) : 0;
     s.n_aux = ((size_t)AUX_Y + M + 6) * N * sizeof(double);
     s.n_out = (5 + M) * (size_t)lat->geo.n_out * sizeof(double);
     size_t o = align256(sizeof(StateHeader));
     s.ref = o; o = align256(o + s.n_ref);
     s.pops = o; o = align256(o + s.n_pops);
     s.scale = o; o = align256(o + s.n_scale);
+    s.scale_next = o; o = align256(o + (version == 1u ? 0 : s.n_scale));
+    s.fscale = o; o = align256(o + s.n_fscale);
     s.aux = o; o = align256(o + s.n_aux);
     s.out = o; o = align256(o + s.n_out);
     s.total = o;
@@ -800,13 +831,17 @@ int rlbm_save_state(rlbm_lattice* lat, void* buf, int on_device) {
     (void)on_device;   // hipMemcpyDefault resolves host or device pointers
     const StateLayout sl = state_layout(lat);
     const int q = (int)((lat->host.parity0 + lat->steps_done) & 1);
-    StateHeader h{STATE_MAGIC, 1u, lat->M, lat->L, lat->storage, lat->host.slaved, lat->host.rss, 0,
+    StateHeader h{STATE_MAGIC, STATE_VERSION, lat->M, lat->L, lat->storage, lat->host.slaved, lat->host.rss, 0,
                   lat->geo.N, lat->geo.n_out};
     char* b = (char*)buf;
     HIP_TRY(hipMemcpy(b, &h, sizeof(h), hipMemcpyDefault), "save state");
     if (sl.n_ref) HIP_TRY(hipMemcpy(b + sl.ref, lat->d_ref, sl.n_ref, hipMemcpyDefault), "save state");
     HIP_TRY(hipMemcpy(b + sl.pops, lat->host.pop[q], sl.n_pops, hipMemcpyDefault), "save state");
-    if (sl.n_scale) HIP_TRY(hipMemcpy(b + sl.scale, lat->host.rscale[q], sl.n_scale, hipMemcpyDefault), "save state");
+    if (sl.n_scale) {
+        HIP_TRY(hipMemcpy(b + sl.scale, lat->host.rscale[q], sl.n_scale, hipMemcpyDefault), "save state");
+        HIP_TRY(hipMemcpy(b + sl.scale_next, lat->host.rscale[q ^ 1], sl.n_scale, hipMemcpyDefault), "save state");
+        HIP_TRY(hipMemcpy(b + sl.fscale, lat->host.fscale[q], sl.n_fscale, hipMemcpyDefault), "save state");
+    }
     HIP_TRY(hipMemcpy(b + sl.aux, lat->host.aux, sl.n_aux, hipMemcpyDefault), "save state");
     if (sl.n_out) HIP_TRY(hipMemcpy(b + sl.out, lat->host.out_state, sl.n_out, hipMemcpyDefault), "save state");
     return RLBM_OK;
@@ -817,13 +852,15 @@ int rlbm_load_state(rlbm_lattice* lat, const void* buf, int on_device) {
     HIP_TRY(hipSetDevice(lat->device), "hipSetDevice");
     HIP_TRY(hipStreamSynchronize(lat->stream), "hipStreamSynchronize");
     (void)on_device;
-    const StateLayout sl = state_layout(lat);
     const char* b = (const char*)buf;
     StateHeader h{};
     HIP_TRY(hipMemcpy(&h, b, sizeof(h), hipMemcpyDefault), "load state");
-    if (h.magic != STATE_MAGIC || h.version != 1u) return fail(RLBM_EINVAL, "not a lattice state snapshot");
+    if (h.magic != STATE_MAGIC || (h.version != 1u && h.version != STATE_VERSION))
+        return fail(RLBM_EINVAL, "not a lattice state snapshot");
+    const StateLayout sl = state_layout(lat, h.version);
+    const int rss = lat->storage != RLBM_STORAGE_F32_DEV ? 0 : (h.version == 1u ? (int)v1_stride(lat) : lat->host.rss);
     if (h.M != lat->M || h.L != lat->L || h.storage != lat->storage || h.N != lat->geo.N ||
-        h.n_out != lat->geo.n_out || h.rss != lat->host.rss || h.slaved < 0 || h.slaved >= lat->M + lat->host.weak ||
+        h.n_out != lat->geo.n_out || h.rss != rss || h.slaved < 0 || h.slaved >= lat->M + lat->host.weak ||
         (lat->host.weak && h.slaved != lat->M))
         return fail(RLBM_EINVAL, "snapshot taken on a lattice of another shape, species count or storage");
     lat->host.slaved = h.slaved;
@@ -834,8 +871,27 @@ int rlbm_load_state(rlbm_lattice* lat, const void* buf, int on_device) {
     }
     const int q = (int)((lat->host.parity0 + lat->steps_done) & 1);
     if (sl.n_ref) HIP_TRY(hipMemcpy(lat->d_ref, b + sl.ref, sl.n_ref, hipMemcpyDefault), "load state");
+    if (sl.n_ref && h.version == 1u)   // the second copy of the shapes: [L][27] to [27][L]
+        for (int l = 0; l < lat->L; ++l)
+            HIP_TRY(hipMemcpy2D(lat->d_ref + ref_doubles_v1(lat->L) + l, (size_t)lat->L * sizeof(double),
+                                lat->d_ref + (size_t)l * Q, sizeof(double), sizeof(double), Q, hipMemcpyDeviceToDevice),
+                    "load state");
     HIP_TRY(hipMemcpy(lat->host.pop[q], b + sl.pops, sl.n_pops, hipMemcpyDefault), "load state");
-    if (sl.n_scale) HIP_TRY(hipMemcpy(lat->host.rscale[q], b + sl.scale, sl.n_scale, hipMemcpyDefault), "load state");
+    if (sl.n_scale && h.version == 1u) {
+        // rows of v1_stride floats: the stored species, then rho and rho E
+        const size_t N = (size_t)lat->geo.N, nsp = (size_t)lat->L - 2, row = v1_stride(lat) * sizeof(float);
+        for (int e = 0; e < 2; ++e)
+            HIP_TRY(hipMemcpy2D(lat->host.rscale[e], (size_t)lat->host.rss * sizeof(float), b + sl.scale, row,
+                                nsp * sizeof(float), N, hipMemcpyDefault),
+                    "load state");
+        HIP_TRY(hipMemcpy2D(lat->host.fscale[q], 2 * sizeof(float), b + sl.scale + nsp * sizeof(float), row,
+                            2 * sizeof(float), N, hipMemcpyDefault),
+                "load state");
+    } else if (sl.n_scale) {
+        HIP_TRY(hipMemcpy(lat->host.rscale[q], b + sl.scale, sl.n_scale, hipMemcpyDefault), "load state");
+        HIP_TRY(hipMemcpy(lat->host.rscale[q ^ 1], b + sl.scale_next, sl.n_scale, hipMemcpyDefault), "load state");
+        HIP_TRY(hipMemcpy(lat->host.fscale[q], b + sl.fscale, sl.n_fscale, hipMemcpyDefault), "load state");
+    }
     HIP_TRY(hipMemcpy(lat->host.aux, b + sl.aux, sl.n_aux, hipMemcpyDefault), "load state");
     if (sl.n_out) HIP_TRY(hipMemcpy(lat->host.out_state, b + sl.out, sl.n_out, hipMemcpyDefault), "load state");
     lat->state_set = true;

@@ -93,3 +93,99 @@ def test_invariants_flag_any_velocity(storage, mech9):
         assert lat.invariants()[-1] == 1.0, (l, i, n)
     lat.write_populations(pops)
     assert lat.invariants()[-1] == 0.0
+
+
+def _three_body(mech):
+    """The one-reaction mechanism with a reversible three-molecule reaction
+    A + B + C <-> 3 C and one that is switched off (ln A = -inf)."""
+    m = dict(mech)
+    m["nu_f"] = [*mech["nu_f"], [1, 1, 1], [1, 1, 0]]
+    m["nu_r"] = [*mech["nu_r"], [0, 0, 3], [0, 0, 2]]
+    m["lnA"] = [*mech["lnA"], mech["lnA"][0] - 1.0, -np.inf]
+    m["beta"] = [*mech["beta"], 0.5, 0.0]
+    m["Ta"] = [*mech["Ta"], 0.5 * mech["Ta"][0], 100.0]
+    m["reversible"] = [*mech["reversible"], 1, 1]
+    return m
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("species,coupling,dims,substeps", [
+    (9, "strong", (1, 1, 1), 1), (9, "strong", (63, 1, 1), 3), (9, "weak", (65, 1, 1), 2), (9, "strong", (64, 2, 1), 2),
+    (9, "strong", (5, 13, 3), 2), (3, "strong", (257, 1, 1), 1), (3, "weak", (11, 3, 2), 4), (2, "strong", (66, 1, 1), 1),
+    (2, "weak", (3, 5, 7), 1), (4, "strong", (64, 1, 1), 3), (4, "weak", (17, 4, 1), 1)])
+def test_step_at_tile_edges(species, coupling, dims, substeps, storage, mech9):
+    """One and four steps with every species count, both couplings and
+    several sub-step counts; the three-species mechanism with more than two
+    molecules on a side.  FP64: 1e-10, the rounding differences of the
+    readout times the steps; FP32: 1e-5 in Y and T."""
+    rlbm = _rlbm()
+    print(f"case step M={species} {coupling} {dims} l={substeps} {storage}", flush=True)
+    case = _case(species, dims, mech9, coupling, substeps=substeps)
+    if species == 3:
+        case["mech"] = _three_body(case["mech"])
+        case["init"]["Y"][2] = 0.05
+        case["init"]["Y"][1] -= 0.05
+    lat, ora = rlbm.Lattice(case, storage=storage).set_state(), Oracle(case)
+    done = 0
+    for n in (1, 4):
+        lat.step(n - done)
+        ora.step(n - done)
+        done = n
+        gf, of = lat.fields(), ora.fields()
+        if storage == "f64":
+            gp, op = lat.populations(), ora.populations()
+            for l in range(op.shape[0]):
+                assert _nerr(gp[l], op[l]) <= 1e-10, (n, l)
+        tol = 1e-10 if storage == "f64" else TOL[storage]
+        assert _nerr(gf["T"], of["T"]) <= tol
+        for a in range(species):
+            assert _nerr(gf["Y"][a], of["Y"][a], 1e-6) <= tol, a
+    assert lat.status() == 0
+
+
+@pytest.mark.parametrize("storage,coupling", [("f64", "strong"), ("f32dev", "strong"), ("f32dev", "weak")])
+def test_first_snapshot_format_still_loads(storage, coupling, mech9):
+    """A snapshot in the first format (one scale vector per node, no second
+    copy of the reference shapes) holds the same populations, and a run
+    resumed from it stays with the run it was taken from."""
+    rlbm = _rlbm()
+    print(f"case snapshot v1 {storage} {coupling}", flush=True)
+    case = wl.make_case("channel2d", nx=33, ny=9, nz=1, mech=mech9, coupling=coupling)
+    lat = rlbm.Lattice(case, storage=storage).set_state()
+    lat.step(5)
+    snap, N, L, M = lat.save_state(), lat.N, lat.L, 9
+    pops = lat.populations()
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    head = snap[:256].copy()
+    ints = head.view(np.int32)
+    assert ints[1] == 2
+    ints[1] = 1
+    if storage == "f64":
+        old = snap.copy()
+        old[:256] = head
+    else:
+        rss, rss1, nsp = int(ints[6]), (L + 3) // 4 * 4, L - 2
+        n_ref1 = (L * 27 + L + 27 + 2) * 8
+        n_ref = n_ref1 + L * 27 * 8
+        P = (N + lat.n_interface + 63) // 64 * 64
+        n_pops, n_sc = L * 27 * P * 4, rss * N * 4
+        o = up(256 - 255)
+        ref = snap[o:o + n_ref1]; o = up(o + n_ref)
+        body = snap[o:o + n_pops]; o = up(o + n_pops)
+        sc = snap[o:o + n_sc].view(np.float32).reshape(N, rss); o = up(up(o + n_sc) + n_sc)
+        fs = snap[o:o + 8 * N].view(np.float32).reshape(N, 2); o = up(o + 8 * N)
+        rest = snap[o:]
+        one = np.zeros((N, rss1), np.float32)
+        one[:, :nsp], one[:, nsp:L] = sc[:, :nsp], fs
+        ints[6] = rss1
+        pad = lambda b: np.concatenate([b, np.zeros(up(len(b)) - len(b), np.uint8)])  # noqa: E731
+        old = np.concatenate([pad(head), pad(ref), pad(body), pad(one.reshape(-1).view(np.uint8)), rest])
+    back = rlbm.Lattice(case, storage=storage).load_state(old)
+    assert np.array_equal(back.populations(), pops)
+    back.step(6)
+    lat.step(6)
+    a, b = back.fields(), lat.fields()
+    for k in ("T", "rho"):
+        assert _nerr(a[k], b[k]) <= TOL[storage], k
+    for s in range(M):
+        assert _nerr(a["Y"][s], b["Y"][s], 1e-6) <= TOL[storage], s
