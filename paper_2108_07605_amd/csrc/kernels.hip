@@ -1968,9 +1968,10 @@ __global__ __launch_bounds__(FLOW_TILES * NODE_TILE) void k_flow(const LatDev* _
 // ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // k_boundary: reconstruction at interface nodes (section 4).  A block takes
-// 64 consecutive entries of the interface list (grouped by boundary type and
-// ordered by node within a type, so mostly a run of a wall row or plane),
-// one lane per node, and one wave per stored lattice: every population load
+// up to 64 consecutive entries of the interface list (grouped by boundary type
+// and ordered by node within a type, so mostly a run of a wall row or plane),
+// one lane per node, and one wave per stored lattice (the energy lattice's
+// layers are dealt to two or three): every population load
 // and store of a wave is coalesced and its lattice, with the lattice's
 // constants, is the same for the whole wave.  Each wave loads its lattice's
 // populations once, in one pass with all 27 loads in flight, and keeps them
@@ -1978,46 +1979,54 @@ __global__ __launch_bounds__(FLOW_TILES * NODE_TILE) void k_flow(const LatDev* _
 // interface list are scattered over the lattice, so a second pass over them
 // costs as much as the first); lattices beyond what the LDS holds beside the
 // node states read them again per pass.  The output goes to the interface
-// slots N + k of the planes of the buffer the step reads.  The node's state goes between the waves
-// through LDS: the lattices' moments, and the imposed and local states that
-// the first wave forms from them (temperature by the bounded Newton
-// iteration, the LODI outlet state).  All barriers are at the top level of
-// the kernel, so every wave meets all of them.
+// slots N + k of the planes of the buffer the step reads.  The node's state
+// goes between the waves through LDS: the lattices' moments, and the imposed
+// and local states that the first wave forms from them (temperature by the
+// bounded Newton iteration, the LODI outlet state).  All barriers are at the
+// top level of the kernel, so every wave meets all of them.
+//   Two passes walk the three layers of nine velocities in a loop: unrolled over
+// all 27 velocities the kernel was 75 KB of code (FP32 storage), more than the
+// instruction cache, and a launch with few blocks spent its time fetching it.
+//   Bound by latency: four dependent phases of one block per CU, and for inlet
+// and outlet planes by the cache lines their scattered nodes touch (see the
+// block rule in the host library).  Unrolled with 64-node blocks throughout
+// against this form: two nodes of a 1024-node tube 35 -> 20 us, a 1024x64
+// channel in FP64 storage 48 -> 23 us, 512x64x64 285 -> 224 us (FP32) and 250
+// -> 227 us (FP64).
 // ---------------------------------------------------------------------------
 static_assert(BC_NODES == 64, "one lane per node in a wave");
 
-// An equilibrium of one lattice at velocity i: s (U Wx Wy Wz + kx Wy Wz +
-// Wx (ky Wz + Wy kz)), with W[d][c + 1] the product-form factor of axis d.
-// The species and momentum lattices have U = 1 and k = 0; the energy lattice
-// has the factors of eq. geq_i (section 3.3) and U the internal energy.
+// An equilibrium of one lattice, s (U Wx Wy Wz + kx Wy Wz + Wx (ky Wz + Wy kz)),
+// with W the product-form factors of the axes.  The species and momentum
+// lattices have U = 1 and k = 0; the energy lattice has the factors of eq.
+// geq_i (section 3.3) and U the internal energy.  The x and y factors are kept
+// for c + 1; layer() forms the z factors of c_z (wave-uniform), s included.
 struct LatEq {
-    double s, U;
-    double W[3][3], k[3][3];
-};
-
-__device__ __forceinline__ void eq_axis(double w, double th, bool energy, double* Wa, double* ka) {
-    const double w2 = w * w;
-    const double P = th + w2;
-    Wa[0] = 0.5 * (P - w);
-    Wa[1] = 1.0 - P;
-    Wa[2] = 0.5 * (P + w);
-    if (energy) {
-        const double o1 = th * w + 0.5 * w2 * w;
-        const double o2 = th * th + 2.5 * th * w2 + 0.5 * w2 * w2;
-        ka[0] = 0.5 * (o2 - o1);
-        ka[1] = 0.5 * w2 - o2;
-        ka[2] = 0.5 * (o2 + o1);
-    } else {
-        ka[0] = ka[1] = ka[2] = 0.0;
+    double s, U, th, uz;
+    double Wx[3], kx[3], Wy[3], ky[3];
+    double Wz, kz;
+    __device__ __forceinline__ void layer(bool energy, int c2) {
+        if (energy) {
+            geq_wk(c2, uz, th, Wz, kz);
+            Wz *= s;
+            kz *= s;
+        } else {
+            Wz = s * psi_u(psi_coef(c2), uz, fma(uz, uz, th));
+        }
     }
-}
-
-template <int C0, int C1, int C2>
-__device__ __forceinline__ double lat_eq(const LatEq& e) {
-    const double wx = e.W[0][C0 + 1], wy = e.W[1][C1 + 1], wz = e.W[2][C2 + 1];
-    const double wyz = wy * wz;
-    return e.s * (e.U * wx * wyz + e.k[0][C0 + 1] * wyz + wx * (e.k[1][C1 + 1] * wz + wy * e.k[2][C2 + 1]));
-}
+    // values at c_x + 1 = 0, 1, 2 of the layer's row c_y + 1 = j
+    __device__ __forceinline__ void row(bool energy, int j, double (&v)[3]) const {
+        const double w = Wy[j] * Wz;
+        if (energy) {
+            const double q = fma(ky[j], Wz, Wy[j] * kz);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[c] = fma(w, fma(U, Wx[c], kx[c]), Wx[c] * q);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[c] = w * Wx[c];
+        }
+    }
+};
 
 // Node state of an equilibrium (sections 4.1-4.4), one LDS column per node:
 // density, temperature, mixture theta, internal energy, velocity, mass
@@ -2039,23 +2048,31 @@ __device__ __forceinline__ void state_store(MechC mc0, double (*st)[BC_NODES], i
     for (int c = 0; c < M; ++c) st[ST_Y + c][lane] = Y[c];
 }
 
-// Equilibrium factors of stored lattice l (the wave's) for the state in
-// column `lane` of st; a species lattice takes the velocity w (its own in
-// the wall's local state, eq. locua), the others the mixture velocity.
+// Equilibrium of stored lattice l (the wave's) for the density and composition
+// in column `lane` of st and the given T, theta, U and velocity.
 template <int M, int W>
-__device__ __forceinline__ void lat_prepare(MechC mc0, const double (*st)[BC_NODES], int lane, int l, int slaved,
-                                            bool spv, const double (&w)[3], LatEq& q) {
+__device__ __forceinline__ void lat_prepare(MechC mc0, const double (*st)[BC_NODES], int lane, int l, int slaved, double T,
+                                            double thm, double U, double u0, double u1, double u2, LatEq& q) {
     constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG;
     reload_barrier();
     MechC mc = in_loop(mc0);
-    const bool lg = l == LG, sp = l < LF;
+    const bool sp = l < LF;
     const int a = sp ? (W ? l : l + (l >= slaved ? 1 : 0)) : 0;
     const double rho = st[ST_RHO][lane];
-    const double th = sp ? mc.Ra[a] * st[ST_T][lane] : st[ST_TH][lane];
+    q.th = sp ? mc.Ra[a] * T : thm;
     q.s = sp ? rho * st[ST_Y + a][lane] : rho;
-    q.U = lg ? st[ST_U][lane] : 1.0;
+    q.U = l == LG ? U : 1.0;
+    q.uz = u2;
+    GeqAxis gx, gy;
+    geq_axis(u0, q.th, gx);
+    geq_axis(u1, q.th, gy);
 #pragma unroll
-    for (int d = 0; d < 3; ++d) eq_axis(sp && spv ? w[d] : st[ST_V + d][lane], th, lg, q.W[d], q.k[d]);
+    for (int c = 0; c < 3; ++c) {
+        q.Wx[c] = gx.W[c];
+        q.kx[c] = gx.k[c];
+        q.Wy[c] = gy.W[c];
+        q.ky[c] = gy.k[c];
+    }
 }
 
 // Compile-time loop over the 27 velocities.
@@ -2067,8 +2084,13 @@ __device__ __forceinline__ void for_q(F&& f) {
     }
 }
 
+// Waves that share the energy lattice, whose equilibrium is the dearest: three
+// (one c_z layer each) where a block then still has at most twelve waves, the
+// most that leaves each 168 registers, else two.
 template <int M, int W>
-constexpr int bc_threads() { return BC_NODES * Lat<M, W>::NL; }
+constexpr int bc_energy_waves() { return Lat<M, W>::NL + 2 <= 12 ? 3 : 2; }
+template <int M, int W>
+constexpr int bc_threads() { return BC_NODES * (Lat<M, W>::NL - 1 + bc_energy_waves<M, W>()); }
 
 // How many of a block's lattices keep their advected populations (27 * 64
 // stored values each) in LDS beside the node states and moments, within the
@@ -2076,7 +2098,7 @@ constexpr int bc_threads() { return BC_NODES * Lat<M, W>::NL; }
 template <int M, typename S, int W>
 constexpr int bc_stash() {
     constexpr int NL = Lat<M, W>::NL;
-    constexpr long state = (long)(NL * 4 + 3 * (ST_Y + M)) * BC_NODES * (long)sizeof(double) + BC_NODES * 4L;
+    constexpr long state = (long)(NL * 4 + 2 * (ST_Y + M) + 2) * BC_NODES * (long)sizeof(double) + BC_NODES * 4L;
     constexpr long n = (160L * 1024 - state) / ((long)Q * BC_NODES * (long)sizeof(S));
     return n < 0 ? 0 : (n < NL ? (int)n : NL);
 }
@@ -2086,15 +2108,16 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
     const LatDev* __restrict__ lats, const int* __restrict__ blk, int n_lat, const long long* __restrict__ tp,
     long long toff) {
     constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
+    constexpr bool F32 = sizeof(S) == 4;
     __shared__ double mom[NL][4][BC_NODES];             // moments per lattice and node
     __shared__ double stA[ST_Y + M][BC_NODES];          // imposed state
     __shared__ double stL[ST_Y + M][BC_NODES];          // local state
-    __shared__ double stT[ST_Y + M][BC_NODES];          // the full inlet's target
+    __shared__ double stT[2][BC_NODES];                 // theta and U of the full inlet's target
     __shared__ int flg[BC_NODES];
     // the advected populations of the first NS lattices as stored, loaded
-    // once and read by all three passes (NS = NL where they fit beside the
-    // state; one block per CU runs anyway, as the kernel's registers allow no
-    // second one)
+    // once and read by all passes (NS = NL where they fit beside the state;
+    // one block per CU runs anyway, as the kernel's registers allow no second
+    // one)
     constexpr int NS = bc_stash<M, S, W>();
     __shared__ S stash[NS > 0 ? NS : 1][Q][BC_NODES];
     const long long t = step_time(tp, toff);
@@ -2109,10 +2132,16 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
     const LatDev& L = lats[lj];
     if (t >= L.t_end) return;                       // the whole block
     const int lane = (int)threadIdx.x % BC_NODES;
-    const int l = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BC_NODES);   // this wave's lattice
-    const int k = (b - blk[lj]) * BC_NODES + lane;
-    const bool live = k < L.n_if;
-    const int kk = live ? k : 0;                    // nodes past the end mirror entry 0 and write nothing
+    constexpr int EW = bc_energy_waves<M, W>();
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BC_NODES);
+    const int l = wave < LG ? wave : LG;            // this wave's lattice
+    const int ew = wave - l;                        // and its share of the c_z layers
+    const int lay0 = l < LG ? 0 : (EW == 3 ? ew : 2 * ew), lay1 = l < LG ? 3 : (EW == 3 ? ew + 1 : 2 + ew);
+    // the block's run of the interface list
+    const int k0 = as_global(L.if_blk)[b - blk[lj]], k1 = as_global(L.if_blk)[b - blk[lj] + 1];
+    const int k = k0 + lane;
+    const bool live = k < k1;
+    const int kk = live ? k : k0;                   // lanes past the end mirror the first node and write nothing
     MechC mc0 = *as_const(L.mech);
     const int par = (L.parity0 + t) & 1;
     const RLBM_GLOBAL S* src = as_global(static_cast<const S*>(L.pop[par]));
@@ -2121,9 +2150,9 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
     RLBM_GLOBAL S* bc = as_global(static_cast<S*>(L.pop[par])) + L.N;
     const size_t N = (size_t)L.N;
     const size_t P = (size_t)L.P;
-    const int node = L.if_node[kk];
-    const unsigned Dm = L.if_mask[kk];
-    const int type = L.if_type[kk];
+    const int node = as_global(L.if_node)[kk];
+    const unsigned Dm = as_global(L.if_mask)[kk];
+    const int type = as_global(L.if_type)[kk];
     const int s = W ? M : L.slaved;
     const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
     PullOff o;
@@ -2132,116 +2161,102 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
     const bool bback = type == RLBM_FACE_BOUNCEBACK;
     const bool outlet = type == RLBM_FACE_OUTLET;
     const bool inlet_full = type == RLBM_FACE_INLET;
+    const bool energy = l == LG;
     const RLBM_CONST double* G = as_const(L.ref);
-    const double zero3[3] = {0.0, 0.0, 0.0};
     if (l == 0) flg[lane] = 0;
 
     // FP32 deviation storage: references belong to the node that reads a
     // value, this node for an advected value and for what is written to the
-    // boundary buffer, the pull source x - c_i (wrapped) for a bounce-back
+    // interface slots, the pull source x - c_i (wrapped) for a bounce-back
     // source f'_{opp(i)}(x)
     float sl = 0.0f, sf = 0.0f;
-    if constexpr (sizeof(S) == 4) {
-        sl = scale_l(L, par, node, l, LF);
+    // this wave's lattice' scale of node n: sbase[n * sstep]
+    const RLBM_GLOBAL float* sbase = nullptr;
+    int sstep = 0;
+    if constexpr (F32) {
+        sbase = l < LF ? as_global(L.rscale[par]) + l : as_global(L.fscale[par]) + (l - LF);
+        sstep = l < LF ? L.rss : 2;
+        sl = sbase[(size_t)node * sstep];
         sf = fscale_at(L, par, node)[0];
     }
-    // population (l, i) after advection, or with bb on an incoming link the
-    // bounce-back source (every lattice at a bounce-back wall, species and
-    // momentum at a TMS wall)
-    auto pop = [&](auto ic, bool bb) -> double {
-        constexpr int i = decltype(ic)::value;
-        constexpr int c0 = cx_of(i), c1 = cy_of(i), c2 = cz_of(i), io = Q - 1 - i;
-        const int off = node + sel3(c0, o.x[0], 0, o.x[2]) + sel3(c1, o.y[0], 0, o.y[2]) + sel3(c2, o.z[0], 0, o.z[2]);
-        double v;
-        if (bb && ((Dm >> i) & 1u)) {
-            v = (double)ld_at(src + (size_t)(l * Q + io) * P, node);
-            if constexpr (sizeof(S) == 4) {
-                const float sb = scale_l(L, par, off, l, LF), sfb = fscale_at(L, par, off)[0];
-                v += l == LG ? ref_g(sb, sfb, G[l * Q + io], G[REF_K<NL> + io]) : ref_of(sb, G[l * Q + io]);
-            }
-        } else {
-            v = (double)ld_at(src + (size_t)(l * Q + i) * P, off);
-            if constexpr (sizeof(S) == 4)
-                v += l == LG ? ref_g(sl, sf, G[l * Q + i], G[REF_K<NL> + i]) : ref_of(sl, G[l * Q + i]);
-        }
-        return v;
+    auto ref = [&](int i, float sc, float scf) -> double {   // reference of (l, i) with the given scales
+        if constexpr (!F32) return 0.0;
+        else if (energy) return ref_g(sc, scf, G[LG * Q + i], G[REF_K<NL> + i]);
+        else return ref_of(sc, G[l * Q + i]);
     };
     const bool stashed = NS == NL || l < NS;   // wave-uniform
-    // the advected population (l, i), from the stash where there is one
-    auto adv = [&](auto ic) -> double {
-        if (NS > 0 && stashed) {
-            constexpr int i = decltype(ic)::value;
-            double v = (double)stash[l][i][lane];
-            if constexpr (sizeof(S) == 4)
-                v += l == LG ? ref_g(sl, sf, G[l * Q + i], G[REF_K<NL> + i]) : ref_of(sl, G[l * Q + i]);
-            return v;
-        } else {
-            return pop(ic, false);
-        }
-    };
-    auto put = [&](auto ic, double v) {
-        constexpr int i = decltype(ic)::value;
-        if (!live) return;
-        RLBM_GLOBAL S* pl = bc + (size_t)(l * Q + i) * P;
-        if constexpr (sizeof(S) == 4) {
-            const double ref = l == LG ? ref_g(sl, sf, G[l * Q + i], G[REF_K<NL> + i]) : ref_of(sl, G[l * Q + i]);
-            st_at(pl, k, __double2float_rn(v - ref));
-        } else {
-            st_at(pl, k, v);
-        }
+    // the advected population (l, i) as stored, i uniform
+    auto adv = [&](int i, int c0, int c1, int c2) -> double {
+        if (NS > 0 && stashed) return (double)stash[NS > 0 ? l : 0][i][lane];
+        const int off = node + sel3(c0, o.x[0], 0, o.x[2]) + sel3(c1, o.y[0], 0, o.y[2]) + sel3(c2, o.z[0], 0, o.z[2]);
+        return (double)ld_at(src + (size_t)(l * Q + i) * P, off);
     };
 
-    // step 1.  Bounce-back wall (section 4.2.1, eq. bb): incoming links carry
-    // the opposite population of the same node, outgoing links their own.
-    // TMS wall (section 4.2.2): the bounce-back densities (eqs. BBrho, BBY),
-    // zeroth moments with the bounce-back sources on D.
-    if (bback) {
-        for_q<0>([&](auto ic) { put(ic, pop(ic, true)); });
-    } else if (NS > 0 && stashed) {
-        // one pass of loads, every one issued before the first store to LDS:
-        // the advected populations of outgoing links and, at a TMS wall, the
-        // bounce-back sources of incoming ones (species and momentum); any
-        // other incoming link loads this node's own slot, an in-range
-        // stand-in that no pass reads
-        const bool tms = wall && l <= LF;
+    // step 1: one pass of loads, all in flight together: the advected
+    // populations of outgoing links and, at a bounce-back wall (section 4.2.1,
+    // eq. bb; every lattice) or a TMS wall (section 4.2.2; species and
+    // momentum), the bounce-back sources of incoming ones; any other incoming
+    // link loads the plane's first value, a stand-in that no pass reads (the
+    // same cache line for every lane: the nodes of an inlet or outlet plane
+    // have a line each)
+    const bool bbs = bback || (wall && l <= LF);
+    {
         S raw[Q];
-        float sbv[Q];
         for_q<0>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            constexpr int c0 = cx_of(i), c1 = cy_of(i), c2 = cz_of(i), io = Q - 1 - i;
-            const int off = node + sel3(c0, o.x[0], 0, o.x[2]) + sel3(c1, o.y[0], 0, o.y[2]) +
-                            sel3(c2, o.z[0], 0, o.z[2]);
+            constexpr int i = decltype(ic)::value, io = Q - 1 - i;
+            constexpr int c0 = cx_of(i), c1 = cy_of(i), c2 = cz_of(i);
+            raw[i] = S(0);
+            if (i / 9 < lay0 || i / 9 >= lay1) return;   // wave-uniform
             const bool in = (Dm >> i) & 1u;
-            const RLBM_GLOBAL S* pi = src + (size_t)(l * Q + i) * P;
-            const RLBM_GLOBAL S* pio = src + (size_t)(l * Q + io) * P;
-            raw[i] = ld_at(tms && in ? pio : pi, in ? node : off);
-            if constexpr (sizeof(S) == 4) {
-                sbv[i] = 0.0f;
-                if (tms && in) sbv[i] = scale_l(L, par, off, l, LF);   // the reader's scale
+            const int off = node + sel3(c0, o.x[0], 0, o.x[2]) + sel3(c1, o.y[0], 0, o.y[2]) + sel3(c2, o.z[0], 0, o.z[2]);
+            raw[i] = ld_at(src + (size_t)(l * Q + i) * P + (bbs && in ? (long long)(io - i) * (long long)P : 0LL),
+                           in ? (bbs ? node : 0) : off);
+        });
+        // the sources, decoded: their sum gives the TMS wall's bounce-back
+        // densities (eqs. BBrho, BBY); a bounce-back wall's output is them
+        if (__builtin_amdgcn_ballot_w64(bbs) != 0) {
+            float sb[F32 ? Q : 1], sbf[F32 ? Q : 1];
+            if constexpr (F32) {
+                auto readers = [&](float own, const RLBM_GLOBAL float* base, int step, float* out) {
+                    for_q<0>([&](auto ic) {
+                        constexpr int i = decltype(ic)::value;
+                        constexpr int c0 = cx_of(i), c1 = cy_of(i), c2 = cz_of(i);
+                        const int off = node + sel3(c0, o.x[0], 0, o.x[2]) + sel3(c1, o.y[0], 0, o.y[2]) +
+                                        sel3(c2, o.z[0], 0, o.z[2]);
+                        out[i] = own;
+                        if (bbs && ((Dm >> i) & 1u)) out[i] = base[(size_t)off * step];
+                    });
+                };
+                readers(sl, sbase, sstep, sb);
+                if (energy) readers(sf, as_global(L.fscale[par]), 2, sbf);
             }
-        });
-        for_q<0>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            stash[l][i][lane] = raw[i];
-        });
-        if (tms) {
-            // TMS wall (section 4.2.2): the bounce-back densities (eqs.
-            // BBrho, BBY), zeroth moments with the bounce-back sources on D
             double m0 = 0.0;
             for_q<0>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                constexpr int io = Q - 1 - i;
+                constexpr int i = decltype(ic)::value, io = Q - 1 - i;
                 double v = (double)raw[i];
-                if constexpr (sizeof(S) == 4)
-                    v += ((Dm >> i) & 1u) ? ref_of(sbv[i], G[l * Q + io]) : ref_of(sl, G[l * Q + i]);
+                if constexpr (F32) {
+                    const bool in = (Dm >> i) & 1u;
+                    v += in ? ref(io, sb[i], sbf[i]) : ref(i, sl, sf);
+                    if (bback && in) raw[i] = __double2float_rn(v - ref(i, sl, sf));
+                }
                 m0 += v;
             });
-            mom[l][0][lane] = m0;
+            if (wall && l <= LF) mom[l][0][lane] = m0;
         }
-    } else if (wall && l <= LF) {
-        double m0 = 0.0;
-        for_q<0>([&](auto ic) { m0 += pop(ic, true); });
-        mom[l][0][lane] = m0;
+        if (NS > 0 && stashed) {
+            for_q<0>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                if (i / 9 < lay0 || i / 9 >= lay1) return;
+                stash[NS > 0 ? l : 0][i][lane] = raw[i];
+            });
+        }
+        if (bback && live) {
+            for_q<0>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                if (i / 9 < lay0 || i / 9 >= lay1) return;
+                st_at(bc + (size_t)(l * Q + i) * P, k, raw[i]);
+            });
+        }
     }
     __syncthreads();
     // step 2: the imposed state, formed by the first wave: the TMS target
@@ -2336,20 +2351,36 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
     // inlet and outlet counterparts)
     LatEq eA;
     if (!bback) {
-        lat_prepare<M, W>(mc0, stA, lane, l, s, false, zero3, eA);
+        lat_prepare<M, W>(mc0, stA, lane, l, s, stA[ST_T][lane], stA[ST_TH][lane], stA[ST_U][lane], stA[ST_V][lane],
+                          stA[ST_V + 1][lane], stA[ST_V + 2][lane], eA);
         double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0;
-        for_q<0>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            constexpr int c0 = cx_of(i), c1 = cy_of(i), c2 = cz_of(i);
-            double v;
-            if ((Dm >> i) & 1u) v = lat_eq<c0, c1, c2>(eA);
-            else v = adv(ic);
-            m0 += v;
-            if (c0) m1 += c0 > 0 ? v : -v;
-            if (c1) m2 += c1 > 0 ? v : -v;
-            if (c2) m3 += c2 > 0 ? v : -v;
-        });
-        mom[l][0][lane] = m0; mom[l][1][lane] = m1; mom[l][2][lane] = m2; mom[l][3][lane] = m3;
+#pragma unroll 1
+        for (int lay = lay0; lay < lay1; ++lay) {
+            const int c2 = lay - 1, i0 = 9 * lay;
+            const unsigned in = Dm >> i0;
+            eA.layer(energy, c2);
+            double f[9], sum = 0.0;
+#pragma unroll
+            for (int j = 0; j < 9; ++j) f[j] = adv(i0 + j, j % 3 - 1, j / 3 - 1, c2) + ref(i0 + j, sl, sf);
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                double v[3];
+                eA.row(energy, j, v);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) v[c] = (in >> (3 * j + c)) & 1u ? v[c] : f[3 * j + c];
+                const double rs = v[0] + v[1] + v[2];
+                sum += rs;
+                m1 += v[2] - v[0];
+                if (j != 1) m2 += j ? rs : -rs;
+            }
+            m0 += sum;
+            m3 = fma((double)c2, sum, m3);
+        }
+        if (energy) {
+            mom[LG][ew][lane] = m0;   // its waves' shares of rho E
+        } else {
+            mom[l][0][lane] = m0; mom[l][1][lane] = m1; mom[l][2][lane] = m2; mom[l][3][lane] = m3;
+        }
     }
     __syncthreads();
     // the local state (first wave): rho and u from the momentum lattice, the
@@ -2379,65 +2410,83 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
         for (int c = 0; c < M; ++c) Y[c] *= iry;
 #pragma unroll
         for (int d = 0; d < 3; ++d) u[d] = mom[LF][1 + d][lane] * irl;
-        const double Ul = mom[LG][0][lane] * irl - 0.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+        double rE = mom[LG][0][lane];
+#pragma unroll
+        for (int e = 1; e < EW; ++e) rE += mom[LG][e][lane];
+        const double Ul = rE * irl - 0.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
         int fail = 0;
         reload_barrier();
         const double Tl = solve_T<M>(in_loop(mc0), Y, Ul, stA[ST_T][lane], &fail);
         flg[lane] = fail;
         state_store<M>(mc0, stL, lane, rl, u, Y, Tl);
         if (inlet_full) {
-            const double uin[3] = {L.u_in, 0.0, 0.0};
-            state_store<M>(mc0, stT, lane, rl, uin, Y, L.T_in);
+            reload_barrier();
+            MechC mc = in_loop(mc0);
+            stT[0][lane] = mc.R_univ * mix_inv_m<M>(mc, Y) * L.T_in;
+            stT[1][lane] = mix_U<M>(mc, Y, L.T_in);
         }
     }
     __syncthreads();
-    // step 4: reconstruction of this wave's lattice
+    // step 4: reconstruction of this wave's lattice.  The wall's local species
+    // equilibria take the species' own velocity u_a = j_a / rho_a (u where
+    // rho_a <= 1e-14 rho, eq. locua).
+    //   TMS wall (eqs. ftms, gtms, fatms) and outlet (eqs. f_outlet, g_outlet,
+    // fa_outlet): 2 A - loc on incoming links, A + f - loc on outgoing ones;
+    //   full inlet (eqs. f_inlet, g_inlet, fa_inlet): tgt + A - loc and
+    // tgt + f - loc;
+    //   simplified inlet (eqs. in_loc_*): loc on every link.
+    // An advected value's reference is that of the slot it goes to.
     if (!bback) {
-        // the wall's local species equilibria take the species' own velocity
-        // u_a = j_a / rho_a (u where rho_a <= 1e-14 rho, eq. locua)
-        double w[3] = {0.0, 0.0, 0.0};
-        const bool spv = wall && l < LF;
-        if (spv) {
-            const double ra = mom[l][0][lane];
-            const bool small = ra <= 1e-14 * stL[ST_RHO][lane];
-            const double ir = small ? 0.0 : 1.0 / ra;
+        double w[3];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) w[d] = small ? stL[ST_V + d][lane] : mom[l][1 + d][lane] * ir;
+        for (int d = 0; d < 3; ++d) w[d] = stL[ST_V + d][lane];
+        if (wall && l < LF) {
+            const double ra = mom[l][0][lane];
+            if (!(ra <= 1e-14 * stL[ST_RHO][lane])) {
+                const double ir = 1.0 / ra;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) w[d] = mom[l][1 + d][lane] * ir;
+            }
         }
-        LatEq eL;
-        lat_prepare<M, W>(mc0, stL, lane, l, s, spv, w, eL);
-        if (type == RLBM_FACE_INLET_LOCAL) {
-            // the simplified inlet: every population at the local equilibria
-            // (eqs. in_loc_*)
-            for_q<0>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                put(ic, lat_eq<cx_of(i), cy_of(i), cz_of(i)>(eL));
-            });
-        } else if (inlet_full) {
-            // eqs. f_inlet, g_inlet, fa_inlet
-            LatEq eT;
-            lat_prepare<M, W>(mc0, stT, lane, l, s, false, zero3, eT);
-            for_q<0>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                constexpr int c0 = cx_of(i), c1 = cy_of(i), c2 = cz_of(i);
-                double fi;
-                if ((Dm >> i) & 1u) fi = lat_eq<c0, c1, c2>(eA);
-                else fi = adv(ic);
-                put(ic, lat_eq<c0, c1, c2>(eT) + fi - lat_eq<c0, c1, c2>(eL));
-            });
-        } else {
-            // TMS wall (eqs. ftms, gtms, fatms) and outlet (eqs. f_outlet,
-            // g_outlet, fa_outlet): 2 A - loc on incoming links, A + f - loc
-            // on outgoing ones
-            for_q<0>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                constexpr int c0 = cx_of(i), c1 = cy_of(i), c2 = cz_of(i);
-                const double ea = lat_eq<c0, c1, c2>(eA), el = lat_eq<c0, c1, c2>(eL);
-                double fi;
-                if ((Dm >> i) & 1u) fi = ea;
-                else fi = adv(ic);
-                put(ic, ea + fi - el);
-            });
+        LatEq eL, eT;
+        lat_prepare<M, W>(mc0, stL, lane, l, s, stL[ST_T][lane], stL[ST_TH][lane], stL[ST_U][lane], w[0], w[1], w[2], eL);
+        const bool any_inlet = __builtin_amdgcn_ballot_w64(inlet_full) != 0;
+        if (any_inlet)
+            lat_prepare<M, W>(mc0, stL, lane, l, s, L.T_in, stT[0][lane], stT[1][lane], L.u_in, 0.0, 0.0, eT);
+        const bool local = type == RLBM_FACE_INLET_LOCAL;
+#pragma unroll 1
+        for (int lay = lay0; lay < lay1; ++lay) {
+            const int c2 = lay - 1, i0 = 9 * lay;
+            const unsigned in = Dm >> i0;
+            eA.layer(energy, c2);
+            eL.layer(energy, c2);
+            if (any_inlet) eT.layer(energy, c2);
+            double f[9];
+#pragma unroll
+            for (int j = 0; j < 9; ++j) f[j] = adv(i0 + j, j % 3 - 1, j / 3 - 1, c2);
+            RLBM_GLOBAL S* pl = bc + (size_t)(l * Q + i0) * P;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                double va[3], vl[3], vt[3];
+                eA.row(energy, j, va);
+                eL.row(energy, j, vl);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) vt[c] = va[c];
+                if (any_inlet) {
+                    double e[3];
+                    eT.row(energy, j, e);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) vt[c] = inlet_full ? e[c] : vt[c];
+                }
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const double rf = ref(i0 + 3 * j + c, sl, sf);
+                    const double d = vt[c] - vl[c];
+                    double v = (in >> (3 * j + c)) & 1u ? d + (va[c] - rf) : d + f[3 * j + c];
+                    if (local) v = vl[c] - rf;
+                    if (live) st_at(pl + (size_t)(3 * j + c) * P, k, (S)v);
+                }
+            }
         }
     }
     if (l == 0 && live && flg[lane]) atomicOr(L.flag, 1);

@@ -87,6 +87,7 @@ struct LatDev {
     const int* if_type;         // [n_if] RLBM_FACE_WALL / INLET / OUTLET
     const double* if_T;         // [n_if] wall target temperature
     const int* if_out;          // [n_if] outlet slot or -1
+    const int* if_blk;          // [blocks + 1] first interface slot of every boundary block
     double* out_state;          // [5 + M][n_out]: rho, ux, uy, uz, T, Y
     const double* ref;          // reference shapes and their moments (FP32 storage; REF_* in kernels.hip)
     float* rscale[2];           // [N][rss] reference scales s_l of the species populations in pop[q] (FP32 storage)

@@ -42,7 +42,7 @@ constexpr int NPHASE = 4;   // boundary, moments + diffusion, chemistry + gradie
 
 struct Plan {
     size_t off_lat, off_mech, off_blk, off_flag, off_ref, off_pop0, off_pop1, off_aux, off_prm, off_ifindex, off_ifnode,
-        off_ifmask, off_iftype, off_ifT, off_ifout, off_out, off_partial, off_invout, off_slot,
+        off_ifmask, off_iftype, off_ifT, off_ifout, off_ifblk, off_out, off_partial, off_invout, off_slot,
         off_rscale0, off_rscale1, off_fscale0, off_fscale1, total;
 };
 
@@ -52,6 +52,8 @@ struct Geometry {
     std::vector<unsigned> if_mask;
     std::vector<double> if_T;
     int n_out = 0;
+    std::vector<int> if_blk;   // first slot of every boundary block, then the number of slots (empty without slots)
+    int if_blocks() const { return if_blk.empty() ? 0 : (int)if_blk.size() - 1; }
 };
 
 bool face_valid(int t) { return t >= RLBM_FACE_PERIODIC && t <= RLBM_FACE_INLET_LOCAL; }
@@ -184,6 +186,27 @@ void build_geometry(const rlbm_lattice_desc* d, Geometry& g) {
         s.if_out.push_back(g.if_type[o] == RLBM_FACE_OUTLET ? s.n_out++ : -1);
     }
     g = std::move(s);
+    // Boundary blocks: BC_NODES consecutive slots, except that a lattice that
+    // leaves CUs idle cuts runs of inlet and outlet nodes finer.  Neighbours in
+    // such a run are a row (or a plane's row) of nodes apart, so each lane's
+    // populations lie in cache lines of their own, about 180 lines per node and
+    // lattice group, and the block's CU fetches them at some 36 bytes a cycle:
+    // 64 nodes take 30 us of a 1024x64 channel's launch, 16 take 8.  With a
+    // block for every CU already (MI355X: 256) more blocks only add their fixed
+    // cost.
+    const int full = (int)((nif + BC_NODES - 1) / BC_NODES);
+    const int cut = full <= 64 ? BC_NODES / 4 : (full <= 256 ? BC_NODES / 2 : BC_NODES);
+    for (size_t j = 0; j < nif;) {
+        const bool far = is_inlet(g.if_type[j]) || g.if_type[j] == RLBM_FACE_OUTLET;
+        const size_t most = far ? (size_t)cut : (size_t)BC_NODES;
+        g.if_blk.push_back((int)j);
+        size_t e = j + 1;
+        while (e < nif && e - j < most &&
+               (is_inlet(g.if_type[e]) || g.if_type[e] == RLBM_FACE_OUTLET) == far)
+            ++e;
+        j = e;
+    }
+    if (nif) g.if_blk.push_back((int)nif);
 }
 
 // Stored lattices: M - 1 species (one slaved), or all M in the weakly coupled
@@ -241,6 +264,7 @@ Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     p.off_iftype = take(nif * sizeof(int));
     p.off_ifT = take(nif * sizeof(double));
     p.off_ifout = take(nif * sizeof(int));
+    p.off_ifblk = take(g.if_blk.size() * sizeof(int));
     p.off_out = take((size_t)(5 + M) * g.n_out * sizeof(double));
     p.off_partial = take(nblocks * (6 + E) * sizeof(double));
     p.off_invout = take((6 + E) * sizeof(double));
@@ -472,6 +496,7 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
     h.if_type = (const int*)(base + p.off_iftype);
     h.if_T = (const double*)(base + p.off_ifT);
     h.if_out = (const int*)(base + p.off_ifout);
+    h.if_blk = (const int*)(base + p.off_ifblk);
     h.out_state = (double*)(base + p.off_out);
     h.ref = d->storage == RLBM_STORAGE_F32_DEV ? (const double*)(base + p.off_ref) : nullptr;
     h.rss = scale_stride(lat->L, d->storage);
@@ -498,7 +523,7 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
     lat->d_partial = (double*)(base + p.off_partial);
     lat->d_invout = (double*)(base + p.off_invout);
     const int nb_nodes = (int)((g.N + NODE_TILE - 1) / NODE_TILE);
-    const int nb_if = (int)((nif + BC_NODES - 1) / BC_NODES);
+    const int nb_if = g.if_blocks();
     const int nb64 = (int)((g.N + 63) / 64);
     const int blk[6] = {0, nb_nodes, 0, nb_if, 0, nb64};
     const int zero = 0;
@@ -518,6 +543,7 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
         UP(base + p.off_iftype, g.if_type.data(), nif * sizeof(int));
         UP(base + p.off_ifT, g.if_T.data(), nif * sizeof(double));
         UP(base + p.off_ifout, g.if_out.data(), nif * sizeof(int));
+        UP(base + p.off_ifblk, g.if_blk.data(), g.if_blk.size() * sizeof(int));
     }
 #undef UP
     if (is_inlet(fi.type)) lat->Y_in.assign(fi.Y_in, fi.Y_in + M);
@@ -641,7 +667,7 @@ int rlbm_set_state(rlbm_lattice* lat, const double* rho, const double* u, const 
 
 static int step_one(rlbm_lattice* lat, long long t) {
     const int nb_nodes = (int)((lat->geo.N + NODE_TILE - 1) / NODE_TILE);
-    const int nb_if = (int)((lat->geo.if_node.size() + BC_NODES - 1) / BC_NODES);
+    const int nb_if = lat->geo.if_blocks();
     const int nb64 = (int)((lat->geo.N + 63) / 64);
     for (int phase = 0; phase < NPHASE; ++phase) {
         StepLaunch a;
@@ -1135,8 +1161,7 @@ int rlbm_batch_create(rlbm_lattice* const* lats, int32_t k, void* dev_mem, size_
         const rlbm_lattice* lat = lats[j];
         b->schemes |= 1u << lat->host.reaction;
         b->host_blk[j + 1] = b->host_blk[j] + (int)((lat->geo.N + NODE_TILE - 1) / NODE_TILE);
-        b->host_blk[(k + 1) + j + 1] =
-            b->host_blk[(k + 1) + j] + (int)((lat->geo.if_node.size() + BC_NODES - 1) / BC_NODES);
+        b->host_blk[(k + 1) + j + 1] = b->host_blk[(k + 1) + j] + lat->geo.if_blocks();
         b->host_blk[2 * (k + 1) + j + 1] = b->host_blk[2 * (k + 1) + j] + (int)((lat->geo.N + 63) / 64);
         flagp[j] = lat->d_flag;
     }
@@ -1259,7 +1284,7 @@ int rlbm_step_group(rlbm_lattice* const* lats, int32_t k, const int64_t* steps) 
             c.parity[j] = (int)((lat->host.parity0 + lat->steps_done) & 1);
             schemes |= 1u << lat->host.reaction;
             pre[0] += (int)((lat->geo.N + NODE_TILE - 1) / NODE_TILE);
-            pre[1] += (int)((lat->geo.if_node.size() + BC_NODES - 1) / BC_NODES);
+            pre[1] += lat->geo.if_blocks();
             pre[2] += (int)((lat->geo.N + 63) / 64);
         }
         HIP_TRY(launch_group_gather(sc, c, l0->stream), "group table kernel");

@@ -189,3 +189,28 @@ def test_first_snapshot_format_still_loads(storage, coupling, mech9):
         assert _nerr(a[k], b[k]) <= TOL[storage], k
     for s in range(M):
         assert _nerr(a["Y"][s], b["Y"][s], 1e-6) <= TOL[storage], s
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("name,dims,coupling", [
+    ("channel2d", (20, 19, 1), "strong"),      # 17 inlet nodes: a block of 16 and one node
+    ("channel2d", (20, 18, 1), "weak"),        # 16: one block of 16
+    ("channel3d", (9, 11, 9), "strong"),       # an inlet plane of 9 x 7 nodes in four blocks
+    ("channel2d", (2100, 9, 1), "strong")])    # more than 64 wall blocks: inlet blocks of 32
+def test_boundary_blocks(name, dims, coupling, storage, mech9):
+    """Inlet and outlet runs cut into boundary blocks of 16 and 32 nodes."""
+    rlbm = _rlbm()
+    print(f"case boundary blocks {name} {dims} {coupling} {storage}", flush=True)
+    case = wl.make_case(name, nx=dims[0], ny=dims[1], nz=dims[2], mech=mech9, coupling=coupling)
+    lat, ora = rlbm.Lattice(case, storage=storage).set_state(), Oracle(case)
+    lat.step(3)
+    ora.step(3)
+    gf, of = lat.fields(), ora.fields()
+    if storage == "f64":
+        gp, op = lat.populations(), ora.populations()
+        for l in range(op.shape[0]):
+            assert _nerr(gp[l], op[l]) <= 1e-10, l
+    tol = 1e-10 if storage == "f64" else TOL[storage]
+    assert _nerr(gf["T"], of["T"]) <= tol
+    for a in range(9):
+        assert _nerr(gf["Y"][a], of["Y"][a], 1e-6) <= tol, a
