@@ -2756,10 +2756,13 @@ __global__ __launch_bounds__(512) void k_refs(const LatDev* __restrict__ lat, do
 // Macroscopic fields of the stored populations.  Bound by the populations'
 // read; the layers' sums meet in LDS and the first wave solves for T.
 // 512x64x64, FP32 storage: 2.41 -> 0.59 ms against one thread per node
-// looping over single velocities; 1024 nodes: 106 -> 8 us.
+// looping over single velocities; 1024 nodes: 106 -> 8 us.  status[0] takes
+// the failure flag as the steps left it, status[1] this kernel's own, in
+// pinned host memory: a copy of the flag after the kernel takes 11 us.
 template <int M, typename S, int W>
 __global__ __launch_bounds__(IO_THREADS) void k_fields(const LatDev* __restrict__ lat, long long t, double* rho_o,
-                                                       double* u_o, double* T_o, double* Y_o, double* P_o) {
+                                                       double* u_o, double* T_o, double* Y_o, double* P_o,
+                                                       int* __restrict__ status) {
     constexpr int NV = LayerSums<M, W>::N;
     __shared__ double part[2][NV][IO_NODES];
     const LatDev& L = *lat;
@@ -2769,6 +2772,7 @@ __global__ __launch_bounds__(IO_THREADS) void k_fields(const LatDev* __restrict_
     const size_t N = (size_t)L.N;
     const bool live = n < (int)N;
     const int node = live ? n : 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) status[0] = *(const volatile int*)L.flag;
     LayerSums<M, W> m;
     bool bad = false;
     layer_sums<M, S, W, false>(L, (int)((L.parity0 + t) & 1), node, w - 1, m, bad);
@@ -2796,7 +2800,10 @@ __global__ __launch_bounds__(IO_THREADS) void k_fields(const LatDev* __restrict_
     const double U = m.v[4] / rho - 0.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
     int fail = 0;
     const double T = solve_T<M>(mc, Y, U, L.aux[AUX_T * N + node], &fail);
-    if (fail) atomicOr(L.flag, 1);
+    if (fail) {
+        atomicOr(L.flag, 1);
+        status[1] = 1;
+    }
     if (rho_o) rho_o[node] = rho;
     if (u_o)
 #pragma unroll
@@ -3095,17 +3102,17 @@ hipError_t launch_refs(int M, int weak, const LatDev* lat, double* ref, double r
 
 template <typename S>
 static hipError_t launch_fields_t(int M, int weak, const LatDev* lat, long long N, long long t, double* rho,
-                                  double* u, double* T, double* Y, double* P, hipStream_t st) {
+                                  double* u, double* T, double* Y, double* P, int* status, hipStream_t st) {
     (void)hipGetLastError();   // report this launch's error only
     RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_fields<MM, S, WW>), dim3(io_blocks(N)), dim3(IO_THREADS), 0, st, lat, t,
-                                                rho, u, T, Y, P))
+                                                rho, u, T, Y, P, status))
     return hipGetLastError();
 }
 
 hipError_t launch_fields(int M, int storage, int weak, const LatDev* lat, long long N, long long t, double* rho,
-                         double* u, double* T, double* Y, double* P, hipStream_t st) {
-    return storage == RLBM_STORAGE_F32_DEV ? launch_fields_t<float>(M, weak, lat, N, t, rho, u, T, Y, P, st)
-                                           : launch_fields_t<double>(M, weak, lat, N, t, rho, u, T, Y, P, st);
+                         double* u, double* T, double* Y, double* P, int* status, hipStream_t st) {
+    return storage == RLBM_STORAGE_F32_DEV ? launch_fields_t<float>(M, weak, lat, N, t, rho, u, T, Y, P, status, st)
+                                           : launch_fields_t<double>(M, weak, lat, N, t, rho, u, T, Y, P, status, st);
 }
 
 hipError_t launch_pops(int M, int storage, int weak, const LatDev* lat, long long N, int l0, int nl, long long t,

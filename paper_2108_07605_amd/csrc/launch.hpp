@@ -41,7 +41,7 @@ hipError_t launch_init(int M, int storage, int weak, const LatDev* lat, long lon
 hipError_t launch_refs(int M, int weak, const LatDev* lat, double* ref, double rho, double T, const double* Y,
                        hipStream_t st);
 hipError_t launch_fields(int M, int storage, int weak, const LatDev* lat, long long N, long long t, double* rho,
-                         double* u, double* T, double* Y, double* P, hipStream_t st);
+                         double* u, double* T, double* Y, double* P, int* status, hipStream_t st);
 hipError_t launch_pops(int M, int storage, int weak, const LatDev* lat, long long N, int l0, int nl, long long t,
                        double* buf, int write, hipStream_t st);
 hipError_t launch_invariants(int M, int storage, int weak, const LatDev* lat, long long N, long long t,

@@ -277,15 +277,9 @@ class Lattice:
         _check(lib().rlbm_step(self.handle, int(n)))
 
     def fields(self):
-        torch = self.torch
         N, M = self.N, self.M
-        out = {k: torch.empty(s, dtype=torch.float64, device="cuda")
-               for k, s in (("rho", N), ("u", 3 * N), ("T", N), ("Y", M * N), ("P", N))}
-        _check(lib().rlbm_read_fields(self.handle, *[c_void_p(out[k].data_ptr())
-                                                     for k in ("rho", "u", "T", "Y", "P")], 1))
-        res = {k: v.cpu().numpy() for k, v in out.items()}
-        res["u"] = res["u"].reshape(3, N)
-        res["Y"] = res["Y"].reshape(M, N)
+        res = {k: np.empty(s) for k, s in (("rho", N), ("u", (3, N)), ("T", N), ("Y", (M, N)), ("P", N))}
+        _check(lib().rlbm_read_fields(self.handle, *[c_void_p(v.ctypes.data) for v in res.values()], 0))
         return res
 
     def populations(self):

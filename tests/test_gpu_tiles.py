@@ -214,3 +214,55 @@ def test_boundary_blocks(name, dims, coupling, storage, mech9):
     assert _nerr(gf["T"], of["T"]) <= tol
     for a in range(9):
         assert _nerr(gf["Y"][a], of["Y"][a], 1e-6) <= tol, a
+
+
+@pytest.mark.parametrize("nx", [1, 300, 4369, 4370])
+def test_host_and_device_transfers_agree(mech9, nx):
+    """Fields read to the host and to the device, all of them and a few, are
+    the same bits, and so are the populations set from host and from device
+    arrays: up to 4369 nodes of nine species the host's go through pinned
+    memory, beyond through the idle population buffer."""
+    rlbm = _rlbm()
+    import ctypes
+    import torch
+    case = wl.make_case("tube", seed=nx, mech=mech9, nx=max(nx, 4)) if nx > 1 else wl.make_case(
+        "reactor", seed=3, mech=mech9, nx=1, ny=1, nz=1)
+    print(f"case transfers nx={nx}", flush=True)
+    lat = rlbm.Lattice(case, storage="f32dev").set_state()
+    first = lat.populations()
+    keys = ("rho", "u", "T", "Y")
+    dev = [torch.as_tensor(np.ascontiguousarray(case["init"][k], dtype=np.float64), device="cuda") for k in keys]
+    lat.step(1)
+    rlbm._check(rlbm.lib().rlbm_set_state(lat.handle, *[ctypes.c_void_p(d.data_ptr()) for d in dev], 1))
+    np.testing.assert_array_equal(lat.populations(), first)
+    lat.step(3)
+    host = lat.fields()
+    on = {k: torch.empty(v.size, dtype=torch.float64, device="cuda") for k, v in host.items()}
+    rlbm._check(rlbm.lib().rlbm_read_fields(lat.handle, *[ctypes.c_void_p(v.data_ptr()) for v in on.values()], 1))
+    for k, v in host.items():
+        np.testing.assert_array_equal(v.ravel(), on[k].cpu().numpy())
+    T, P = np.full_like(host["T"], -1.0), np.full_like(host["P"], -1.0)
+    rlbm._check(rlbm.lib().rlbm_read_fields(lat.handle, None, None, ctypes.c_void_p(T.ctypes.data), None,
+                                            ctypes.c_void_p(P.ctypes.data), 0))
+    np.testing.assert_array_equal(T, host["T"])
+    np.testing.assert_array_equal(P, host["P"])
+
+
+@pytest.mark.parametrize("at", [0, 255, 256, 511, 600])
+@pytest.mark.parametrize("key,value,word", [("rho", -1.0, "rho and T"), ("T", np.inf, "rho and T"),
+                                            ("Y", np.nan, "mass fractions must be finite"),
+                                            ("Y", 0.5, "sum to 1"), ("u", np.nan, "velocity")])
+def test_set_state_refuses_a_bad_node(mech9, key, value, word, at):
+    """One bad value at the edges of the checked chunks is refused with its
+    own message, and the lattice keeps the state it had."""
+    rlbm = _rlbm()
+    case = wl.make_case("tube", seed=5, mech=mech9, nx=601)
+    lat = rlbm.Lattice(case, storage="f64").set_state()
+    before = lat.populations()
+    init = {k: np.array(v, dtype=np.float64) for k, v in case["init"].items()}
+    flat = init[key].reshape(-1, 601)
+    flat[-1, at] = flat[-1, at] + value if key == "Y" else value
+    with pytest.raises(rlbm.RlbmError) as e:
+        lat.set_state(init)
+    assert e.value.code == -1 and word in str(e.value)
+    np.testing.assert_array_equal(lat.populations(), before)
