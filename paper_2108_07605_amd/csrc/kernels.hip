@@ -1866,44 +1866,253 @@ __global__ __launch_bounds__(SPC_THREADS) __attribute__((amdgpu_waves_per_eu(M >
 
 // ---------------------------------------------------------------------------
 // k_flow: the same-time gradients, then the collisions of the momentum and the
-// energy lattice (section 3.2 eq. f, section 3.3 eq. g).  One wave per 64
-// nodes, FLOW_TILES independent tiles per block.  Bound by its traffic: 54
-// populations in and out, the record, and the stencil's reads of nine fields
-// from L2.  The gradients stay in registers: as a kernel of their own they
-// wrote and read six rows per node.
+// energy lattice (section 3.2 eq. f, section 3.3 eq. g).  Three waves per 64
+// nodes, one c_z layer each: a wave's share of the stencil is the layer's nine
+// neighbours, the partial gradients meet in LDS, then it collides the layer's
+// nine velocities.  Populations and the readers' scales are asked for ahead of
+// the barrier.  Bound by its traffic on large lattices (54 populations in and
+// out, the record, nine fields for the stencil: 512x64x64 moves 1.3 GB in FP32
+// storage, 0.36 ms) and by one tile's latency on small ones.  Against one wave
+// per 64 nodes: 1024 nodes 14.4 -> 6.3 us, 203x53x37 (weak coupling) 105 -> 88,
+// 512x64x64 419 -> 358 (FP32) and 530 -> 496 (FP64).  Three waves per SIMD: at
+// four the registers spill (423 and 582 us at 512x64x64 without the early
+// scales).
 // ---------------------------------------------------------------------------
-constexpr int FLOW_TILES = 4;
+constexpr int FLOW_THREADS = 3 * NODE_TILE;
+
+// Sums over c_y of one column of a layer: the enthalpy coefficients and
+// Phi_x, Phi_z with the weights w(c_y), and the coefficients and Phi_y with
+// c_y.
+struct LayerCol {
+    double a[6], b[6], ax, by, az;
+};
+__device__ __forceinline__ void layer_sums_y(const double (&v)[3][9], LayerCol& o) {
+    constexpr double w0 = 2.0 / 3.0, w1 = 1.0 / 6.0;
+    auto even = [&](int k) { return fma(w1, v[0][k] + v[2][k], w0 * v[1][k]); };
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        o.a[k] = even(k);
+        o.b[k] = v[2][k] - v[0][k];
+    }
+    o.ax = even(6);
+    o.by = v[2][7] - v[0][7];
+    o.az = even(8);
+}
+template <int M>
+__device__ __forceinline__ void layer_column(const RLBM_GLOBAL double* aux, size_t N, int nx, int zr, const int (&gy)[3],
+                                             int xc, LayerCol& o) {
+    double v[3][9];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int nb = (zr + gy[j]) * nx + xc;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v[j][k] = ld_at(aux + (AUX_Y + M + k) * N, nb);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[j][6 + k] = ld_at(aux + (AUX_PHI + k) * N, nb);
+    }
+    layer_sums_y(v, o);
+}
+
+// One layer's part of the gradients (see the factored weights above
+// column_sums): d_x and d_z from the even sums A, d_y from the odd ones B.
+// A tile inside one x-row (wave-uniform, all its nodes exist) takes the
+// columns beside its own from the adjacent lanes, which evaluate them at this
+// lane's temperature, and the two columns beyond the tile with one load of
+// 54 lanes (nine fields, three y, two sides) through LDS: loads by the first
+// and the last lane alone would double the stencil's load instructions, and
+// those bound the kernel.  Other tiles load all three columns.
+constexpr int EDGE = 27;   // values of one column of a layer
+template <int M>
+__device__ __forceinline__ void layer_gradients(const LatDev& L, int n0, int lane, int x, int y, int z, int node, int c2,
+                                                double (&edges)[2 * EDGE], double (&part)[6]) {
+    const int nx = L.nx, ny = L.ny, nz = L.nz;
+    const size_t N = (size_t)L.N;
+    const RLBM_GLOBAL double* aux = as_global(L.aux);
+    const bool px = L.per[0], py = L.per[1], pz = L.per[2];
+    const int gy[3] = {y == 0 ? (py ? ny - 1 : 0) : y - 1, y, y == ny - 1 ? (py ? 0 : y) : y + 1};
+    const int zc = c2 < 0 ? (z == 0 ? (pz ? nz - 1 : 0) : z - 1) : (c2 > 0 ? (z == nz - 1 ? (pz ? 0 : z) : z + 1) : z);
+    const int xm = x == 0 ? (px ? nx - 1 : 0) : x - 1, xp = x == nx - 1 ? (px ? 0 : x) : x + 1;
+    const int zr = zc * ny;
+    const double T = ld_at(aux + AUX_T * N, node);
+    constexpr double w0 = 2.0 / 3.0, w1 = 1.0 / 6.0;
+    const double hz = c2 ? 0.5 * w1 : 0.5 * w0, hc = 0.5 * (double)c2;
+    struct Column {   // the sums at a lane's temperature
+        double A, B, ax, by, az;
+    };
+    auto at = [](double t, const LayerCol& s) { return Column{poly5(t, s.a), poly5(t, s.b), s.ax, s.by, s.az}; };
+    // column x + c
+    auto add = [&](int c, const Column& v) {
+        const double w = c ? w1 : w0;
+        if (c) {
+            part[0] = c < 0 ? -v.ax : part[0] + v.ax;
+            part[3] = c < 0 ? -v.A : part[3] + v.A;
+        }
+        part[1] = c < 0 ? w * v.by : fma(w, v.by, part[1]);
+        part[2] = c < 0 ? w * v.az : fma(w, v.az, part[2]);
+        part[4] = c < 0 ? w * v.B : fma(w, v.B, part[4]);
+        part[5] = c < 0 ? w * v.A : fma(w, v.A, part[5]);
+    };
+    if (n0 % nx + NODE_TILE <= nx) {
+        {
+            const int side = lane >= EDGE ? 1 : 0, q = lane - side * EDGE, j = q / 9, k = q - 9 * j;
+            const int x0 = n0 % nx, x1 = x0 + NODE_TILE - 1;
+            const int xg = side ? (x1 == nx - 1 ? (px ? 0 : x1) : x1 + 1) : (x0 == 0 ? (px ? nx - 1 : 0) : x0 - 1);
+            if (lane < 2 * EDGE)
+                edges[lane] = aux[(k < 6 ? AUX_Y + M + k : AUX_PHI + k - 6) * N + (size_t)((zr + sel3(j - 1, gy[0], gy[1], gy[2])) * nx + xg)];
+        }
+        LayerCol s;
+        layer_column<M>(aux, N, nx, zr, gy, x, s);
+        Column edge = {0.0, 0.0, 0.0, 0.0, 0.0};
+        if (lane == 0 || lane == NODE_TILE - 1) {
+            const double* from = &edges[lane == 0 ? 0 : EDGE];
+            LayerCol g;
+            constexpr double w0 = 2.0 / 3.0, w1 = 1.0 / 6.0;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const double* e = from + 9 * j;
+                const double w = j == 1 ? w0 : w1;
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    g.a[k] = j ? fma(w, e[k], g.a[k]) : w * e[k];
+                    g.b[k] = j == 2 ? g.b[k] + e[k] : (j ? g.b[k] : -e[k]);
+                }
+                g.ax = j ? fma(w, e[6], g.ax) : w * e[6];
+                g.by = j == 2 ? g.by + e[7] : (j ? g.by : -e[7]);
+                g.az = j ? fma(w, e[8], g.az) : w * e[8];
+                reload_barrier();
+            }
+            edge = at(T, g);
+        }
+        Column v = at(__shfl_down(T, 1u), s);
+        auto pass = [&](int c, double e, double w) {   // from lane - 1 or lane + 1, or the column beyond the tile
+            const double r = c < 0 ? __shfl_up(w, 1u) : __shfl_down(w, 1u);
+            return (c < 0 ? lane == 0 : lane == NODE_TILE - 1) ? e : r;
+        };
+        add(-1, Column{pass(-1, edge.A, v.A), pass(-1, edge.B, v.B), pass(-1, edge.ax, v.ax), pass(-1, edge.by, v.by),
+                       pass(-1, edge.az, v.az)});
+        add(0, at(T, s));
+        v = at(__shfl_up(T, 1u), s);
+        add(1, Column{pass(1, edge.A, v.A), pass(1, edge.B, v.B), pass(1, edge.ax, v.ax), pass(1, edge.by, v.by),
+                      pass(1, edge.az, v.az)});
+    } else {
+#pragma unroll
+        for (int c = -1; c <= 1; ++c) {
+            reload_barrier();   // one column's loads at a time
+            LayerCol s;
+            layer_column<M>(aux, N, nx, zr, gy, c < 0 ? xm : (c > 0 ? xp : x), s);
+            add(c, at(T, s));
+        }
+    }
+    part[0] *= hz;
+    part[1] *= hz;
+    part[2] *= hc;
+    part[3] *= hz;
+    part[4] *= hz;
+    part[5] *= hc;
+}
+
+// The tile that takes the place `q` of a lattice's order.  Whole planes in
+// order have each XCD fetch the stencil's nine fields once per c_z once three
+// planes exceed its L2; strips of 64 tiles (0.9 MB for three planes), all z of
+// a strip after another, keep them there: 512x64x64 437 -> 419 us (FP32), 562
+// -> 547 us (FP64).  Planes that are no whole number of tiles stay in order.
+__device__ __forceinline__ int strip_tile(const LatDev& L, int q) {
+    constexpr int SW = 64;
+    const int plane = L.nx * L.ny, tp = plane / NODE_TILE;
+    if (plane % NODE_TILE || tp <= SW || L.nz == 1) return q;
+    const int s = q / (SW * L.nz), r = q - s * SW * L.nz;
+    const int w = min(SW, tp - s * SW), z = r / w;
+    return z * tp + s * SW + (r - z * w);
+}
+
 template <int M, typename S, int W>
-__global__ __launch_bounds__(FLOW_TILES * NODE_TILE) void k_flow(const LatDev* __restrict__ lats, const int* __restrict__ blk,
-                                                                 int n_lat, const long long* __restrict__ tp, long long toff) {
+__global__ __launch_bounds__(FLOW_THREADS) __attribute__((amdgpu_waves_per_eu(3))) void k_flow(const LatDev* __restrict__ lats, const int* __restrict__ blk, int n_lat,
+                                                       const long long* __restrict__ tp, long long toff) {
     constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
+    constexpr bool F32 = sizeof(S) == 4;
+    __shared__ double part[3][6][NODE_TILE], edges[3][2 * EDGE];
+    // k_flow's record, a third of its rows loaded by each wave
+    enum { R_RHO, R_U = 1, R_UINT = 4, R_TH, R_OMEGA, R_OMEGA1, R_QB, R_N = 11 };
+    __shared__ double rec[R_N][NODE_TILE];
     const long long t = step_time(tp, toff);
-    const int tile = xcd_block() * FLOW_TILES + __builtin_amdgcn_readfirstlane((int)threadIdx.x / NODE_TILE);
-    if (tile >= blk[n_lat]) return;
-    const int lj = find_lattice(blk, n_lat, tile);
+    const int b = xcd_block();
+    const int lj = find_lattice(blk, n_lat, b);
     const LatDev& L = lats[lj];
-    if (t >= L.t_end || L.reaction != RLBM_REACTION_EXPLICIT) return;
+    if (t >= L.t_end || L.reaction != RLBM_REACTION_EXPLICIT) return;   // the whole block
     const int lane = (int)threadIdx.x % NODE_TILE;
-    const int node = (tile - blk[lj]) * NODE_TILE + lane;
-    if (node >= (int)L.N) return;
+    const int layer = __builtin_amdgcn_readfirstlane((int)threadIdx.x / NODE_TILE), c2 = layer - 1;
+    const int n0 = strip_tile(L, b - blk[lj]) * NODE_TILE;
+    const bool valid = n0 + lane < (int)L.N;
+    const int node = valid ? n0 + lane : (int)L.N - 1;   // beyond the end: a placeholder that writes nothing
     const size_t N = (size_t)L.N, P = (size_t)L.P;
     const int par = (int)((L.parity0 + t) & 1);
     const RLBM_GLOBAL S* src = as_global(static_cast<const S*>(L.pop[par]));
     RLBM_GLOBAL S* dst = as_global(static_cast<S*>(L.pop[par ^ 1]));
     const RLBM_GLOBAL double* prm = as_global(L.prm);
+    const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
+    PullOff o;
+    pull_offsets(L, x, y, z, o);
+    S fi[9], gi[9];
+    {
+        const int k = interface_slot(L, node, x, y, z);
+        const unsigned nb = plane_bytes(L.P, sizeof(S));
+        const int nz = node + sel3(c2, o.z[0], 0, o.z[2]);
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const int idx = k >= 0 ? (int)N + k : nz + o.x[j % 3] + o.y[j / 3];
+            fi[j] = ld_win(src + (size_t)(LF * Q + 9 * layer) * P, nb, j, idx);
+            gi[j] = ld_win(src + (size_t)(LG * Q + 9 * layer) * P, nb, j, idx);
+        }
+    }
+    float fs[2] = {0.0f, 0.0f};
+    if constexpr (F32) flow_scales(L, par, node, fs);
+    double row[4];
+    if (layer == 0) {
+        row[0] = ld_at(prm + PRM_RHO * N, node);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) row[1 + d] = ld_at(prm + (PRM_U + d) * N, node);
+    } else if (layer == 1) {
+        row[0] = ld_at(prm + PRM_UINT * N, node);
+        row[1] = ld_at(prm + PRM_TH * N, node);
+        row[2] = ld_at(prm + PRM_OMEGA * N, node);
+        row[3] = ld_at(prm + PRM_OMEGA1 * N, node);
+    } else {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) row[d] = ld_corr<F32>(prm, PRM_QB + d, N, node);
+        row[3] = 0.0;
+    }
     double gr[6];
-    tile_gradients<M>(L, node, lane, gr);
+    layer_gradients<M>(L, n0, lane, x, y, z, node, c2, edges[layer], gr);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (4 * layer + k < R_N) rec[4 * layer + k][lane] = row[k];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) part[layer][k][lane] = gr[k];
+    // the scales of the nodes that pull from here
+    float srd[9][2];
+    if constexpr (F32) {
+#pragma unroll
+        for (int j = 0; j < 9; ++j) flow_scales(L, par ^ 1, reader_at(node, o, j % 3 - 1, j / 3 - 1, c2), srd[j]);
+    }
+    __syncthreads();
+    if (!valid) return;
+    const double rho = rec[R_RHO][lane], U = rec[R_UINT][lane], th = rec[R_TH][lane];
+    const double omega = rec[R_OMEGA][lane], omega1 = rec[R_OMEGA1][lane];
+    double u[3], Qb[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        u[d] = rec[R_U + d][lane];
+        Qb[d] = rec[R_QB + d][lane];
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) gr[k] = part[0][k][lane] + part[1][k][lane] + part[2][k][lane];
 
-    const double rho = ld_at(prm + PRM_RHO * N, node), U = ld_at(prm + PRM_UINT * N, node), th = ld_at(prm + PRM_TH * N, node);
-    const double omega = ld_at(prm + PRM_OMEGA * N, node), omega1 = ld_at(prm + PRM_OMEGA1 * N, node);
-    double u[3], Qv[3];
     const double exf = (2.0 - omega) / (2.0 * rho * omega);
     const double cc = 0.5 * (2.0 - omega1) * (rho * th), wq = 0.5 * (omega - omega1);
     double E[3][3], Wa[3][3], ka[3][3];   // per axis and c + 1: eq. Pex, eq. geq_i
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        u[d] = ld_at(prm + (PRM_U + d) * N, node);
-        Qv[d] = 0.5 * (ld_corr<sizeof(S) == 4>(prm, PRM_QB + d, N, node) - wq * u[d] * gr[d] + cc * gr[3 + d]);
+        Qb[d] = 0.5 * (Qb[d] - wq * u[d] * gr[d] + cc * gr[3 + d]);
         const double P0 = fma(u[d], u[d], th), Px = fma(exf, gr[d], P0);
         E[d][0] = 0.5 * (Px - u[d]);
         E[d][1] = 1.0 - Px;
@@ -1913,33 +2122,17 @@ __global__ __launch_bounds__(FLOW_TILES * NODE_TILE) void k_flow(const LatDev* _
 #pragma unroll
         for (int c = 0; c < 3; ++c) { Wa[d][c] = g.W[c]; ka[d][c] = g.k[c]; }
     }
-    const int x = node % L.nx, r = node / L.nx, y = r % L.ny, z = r / L.ny;
-    PullOff o;
-    pull_offsets(L, x, y, z, o);
-    const int k = interface_slot(L, node, x, y, z);
-    const unsigned nb = plane_bytes(L.P, sizeof(S));
-    float fs[2] = {0.0f, 0.0f};
-    if constexpr (sizeof(S) == 4) flow_scales(L, par, node, fs);
+    const double Ez = rho * sel3d(c2, E[2][0], E[2][1], E[2][2]);
+    const double Wz = sel3d(c2, Wa[2][0], Wa[2][1], Wa[2][2]), kz = sel3d(c2, ka[2][0], ka[2][1], ka[2][2]);
 #pragma unroll
-    for (int row = 0; row < 9; ++row) {
-        const int c1 = row % 3, c2 = row / 3;
-        const double Eyz = rho * E[1][c1] * E[2][c2];
-        const double Wyz = Wa[1][c1] * Wa[2][c2], kyz = ka[1][c1] * Wa[2][c2] + Wa[1][c1] * ka[2][c2];
-        S fi[3], gi[3];
-        float srd[3][2];
+    for (int c1 = 0; c1 < 3; ++c1) {
+        const double Eyz = Ez * E[1][c1], Wyz = Wa[1][c1] * Wz, kyz = ka[1][c1] * Wz + Wa[1][c1] * kz;
 #pragma unroll
         for (int c0 = 0; c0 < 3; ++c0) {
-            const int idx = k >= 0 ? (int)N + k : node + o.x[c0] + o.y[c1] + o.z[c2];
-            fi[c0] = ld_win(src + (size_t)(LF * Q + 9 * c2) * P, nb, 3 * c1 + c0, idx);
-            gi[c0] = ld_win(src + (size_t)(LG * Q + 9 * c2) * P, nb, 3 * c1 + c0, idx);
-            if constexpr (sizeof(S) == 4) flow_scales(L, par ^ 1, reader_at(node, o, c0 - 1, c1 - 1, c2 - 1), srd[c0]);
-        }
-#pragma unroll
-        for (int c0 = 0; c0 < 3; ++c0) {
-            const int i = 3 * row + c0;
-            double f = (double)fi[c0], g = (double)gi[c0];
+            const int j = 3 * c1 + c0, i = 9 * layer + j;
+            double f = (double)fi[j], g = (double)gi[j];
             const RLBM_CONST double* ref = as_const(L.ref) + opaque_zero();
-            if constexpr (sizeof(S) == 4) {
+            if constexpr (F32) {
                 f += ref_of(fs[0], ref[LF * Q + i]);
                 g += ref_g(fs[1], fs[0], ref[LG * Q + i], ref[REF_K<NL> + i]);
             }
@@ -1947,14 +2140,16 @@ __global__ __launch_bounds__(FLOW_TILES * NODE_TILE) void k_flow(const LatDev* _
             const double geq = rho * (Wyz * (U * Wa[0][c0] + ka[0][c0]) + Wa[0][c0] * kyz);
             double go = g + omega * (geq - g);
             // the singularity-free flux term on the six |c| = 1 velocities
-            if (c2_of(i) == 1) {
-                const int ax = cx_of(i) ? 0 : (cy_of(i) ? 1 : 2);
-                go += (cx_of(i) + cy_of(i) + cz_of(i)) > 0 ? Qv[ax] : -Qv[ax];
+            if (c0 == 1 && c1 == 1) {
+                if (c2 != 0) go += c2 > 0 ? Qb[2] : -Qb[2];
+            } else if ((c0 == 1 || c1 == 1) && c2 == 0) {
+                const double q = c0 != 1 ? Qb[0] : Qb[1];
+                go += c0 + c1 > 2 ? q : -q;
             }
-            if constexpr (sizeof(S) == 4) {
-                st_at(dst + (size_t)(LF * Q + i) * P, node, __double2float_rn(fo - ref_of(srd[c0][0], ref[LF * Q + i])));
+            if constexpr (F32) {
+                st_at(dst + (size_t)(LF * Q + i) * P, node, __double2float_rn(fo - ref_of(srd[j][0], ref[LF * Q + i])));
                 st_at(dst + (size_t)(LG * Q + i) * P, node,
-                      __double2float_rn(go - ref_g(srd[c0][1], srd[c0][0], ref[LG * Q + i], ref[REF_K<NL> + i])));
+                      __double2float_rn(go - ref_g(srd[j][1], srd[j][0], ref[LG * Q + i], ref[REF_K<NL> + i])));
             } else {
                 st_at(dst + (size_t)(LF * Q + i) * P, node, fo);
                 st_at(dst + (size_t)(LG * Q + i) * P, node, go);
@@ -3057,9 +3252,8 @@ static hipError_t launch_step_phase(int phase, int M, int weak, const StepLaunch
                                                 a.blk, a.n_lat, a.tp, a.toff))
     } else {
         if (explicit_)
-            RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_flow<MM, S, WW>), dim3((a.blocks + FLOW_TILES - 1) / FLOW_TILES),
-                                                        dim3(FLOW_TILES * NODE_TILE), 0, a.stream, a.lats, a.blk, a.n_lat,
-                                                        a.tp, a.toff))
+            RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_flow<MM, S, WW>), dim3(a.blocks), dim3(FLOW_THREADS), 0, a.stream,
+                                                        a.lats, a.blk, a.n_lat, a.tp, a.toff))
         if (implicit_)
             RLBM_DISPATCH_W(M, weak, hipLaunchKernelGGL((k_update<MM, S, WW>), dim3(a.blocks), dim3(UPD_THREADS), 0,
                                                         a.stream, a.lats, a.blk, a.n_lat, a.tp, a.toff))

@@ -266,3 +266,26 @@ def test_set_state_refuses_a_bad_node(mech9, key, value, word, at):
         lat.set_state(init)
     assert e.value.code == -1 and word in str(e.value)
     np.testing.assert_array_equal(lat.populations(), before)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("name,dims", [
+    ("reactor", (64, 5, 4)),       # a tile is a whole periodic row: both outer columns wrap
+    ("reactor", (128, 3, 2)),      # a wrapped and an inner column beside each tile
+    ("channel3d", (64, 9, 5)),     # an inlet and an outlet beside each tile
+    ("channel3d", (128, 5, 4)),
+    ("channel3d", (63, 9, 5)),     # a row one short of a tile
+    ("channel3d", (64, 65, 3)),    # planes of 65 tiles: a strip of 64 and one of a single tile
+    ("channel3d", (96, 64, 3))])   # planes of 96 tiles that cross rows
+def test_flow_tiles(name, dims, storage, mech9):
+    """Stencil and collision of f and g where tiles meet rows, faces and the
+    ends of strips."""
+    rlbm = _rlbm()
+    print(f"case flow tiles {name} {dims} {storage}", flush=True)
+    case = wl.make_case(name, seed=dims[0], nx=dims[0], ny=dims[1], nz=dims[2], mech=mech9)
+    lat, ora = rlbm.Lattice(case, storage=storage).set_state(), Oracle(case)
+    lat.step(2)
+    ora.step(2)
+    gp, op = lat.populations(), ora.populations()
+    for l in range(op.shape[0]):
+        assert _nerr(gp[l], op[l]) <= (1e-10 if storage == "f64" else TOL[storage]), l
