@@ -1272,16 +1272,21 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
 // node: temperature, relaxation rates, Stefan-Maxwell system.  The reactions
 // are dealt to the first three waves.
 //   Bound: FP64 issue and its latency (two waves per SIMD; about 15,000 vector
-// instructions per tile, which the SIMDs issue 48% of the time) in FP32
+// instructions per tile, which the SIMDs issue 55% of the time) in FP32
 // storage, those and the traffic in FP64: 2.1 and 4.1 KB per node, against
 // 4.0 and 7.5 for a moments pass and a collision that each read every
 // population.  Three waves hold what one cannot, 216 registers of populations
 // per node (FP32) beside the collision's working set, and they divide the
 // node's serial chain, which is what a lattice too small to fill the chip
 // waits for.  With k_flow against the passes it replaced (moments, gradients,
-// collision of all lattices), 512x64x64: 1.79 + 0.42 against 0.93 + 0.18 + 1.28
-// ms in FP32 storage, 2.05 + 0.53 against 1.19 + 0.18 + 2.00 in FP64; 1024
-// nodes: 23 + 14 against 38 + 9 + 23 us.
+// collision of all lattices), 512x64x64: 1.65 + 0.36 against 0.93 + 0.18 + 1.28
+// ms in FP32 storage, 2.00 + 0.50 against 1.19 + 0.18 + 2.00 in FP64; 1024
+// nodes: 21 + 6 against 38 + 9 + 23 us.
+//   Scalar loads return after about 200 cycles, more than the arithmetic of one
+// species, and out of order, so a wait for one is a wait for all, LDS loads
+// included: the rows of the collision and of the solve ask for the next
+// species' constants once this one's have arrived, and the stores' operands
+// come in one batch.  Each loaded where it is used: 1.79 and 2.05 ms.
 //   The order of the barriers is the same on both sides of the role branch:
 // partial sums written, partial sums read, node state, per sub-step
 // (concentrations, rates), collision coefficients.
@@ -1320,6 +1325,10 @@ __device__ __forceinline__ int interface_slot(const LatDev& L, int node, int x, 
     if (__builtin_amdgcn_ballot_w64(on) == 0) return -1;
     return as_global(L.if_index)[node];
 }
+
+// Has a scalar load and an LDS load, and all before them, waited for here: loads
+// that follow then are on their way while what arrived is used.
+__device__ __forceinline__ void arrived(double s, double v) { asm volatile("" : : "s"(s), "v"(v) : "memory"); }
 
 // Waves 0..2: partial moments, reactions, collision.
 template <int M, typename S, int W>
@@ -1484,18 +1493,37 @@ __device__ __forceinline__ void species_layer(const LatDev& L, int par, int laye
     unsigned off = (unsigned)node * (unsigned)sizeof(S);
     asm volatile("" : "+v"(off));   // a 32-bit offset, not folded into 64-bit addresses
     const RLBM_CONST double* ref0 = F32 ? as_const(L.ref) + REF_T<NL> + 9 * layer * NL : nullptr;
+    const RLBM_CONST double* slot0 = as_const(L.slotc);   // not loaded again behind every barrier
 #pragma unroll 1
     for (int c1 = -1; c1 <= 1; ++c1) {
         const PsiCoef py = psi_coef(c1);
+        float rd[F32 ? 3 : 1][NSP];   // scales of the nodes that pull the row from here
+        if constexpr (F32) {
+#pragma unroll
+            for (int c0 = 0; c0 < 3; ++c0) species_scales<NSP>(L, par ^ 1, reader_at(node, o, c0 - 1, c1, c2), rd[c0]);
+        }
         double Fz[NSP], Fs[NSP], Fo[NSP], yz[NSP];
+        // a species' constants and state are asked for one species ahead: the
+        // wait for a scalar load is longer than a species' arithmetic
+        double Kn[NSP], sn[4], Rn;
+        auto ask = [&](int q) {
+            const RLBM_CONST double* slotc = slot0 + opaque_zero();
+#pragma unroll
+            for (int j = 0; j < NSP; ++j) Kn[j] = slotc[M + q * M + j];   // symmetric
+            Rn = slotc[q];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sn[k] = sp[R::ST + 4 * q + k][lane];
+        };
+        ask(0);
 #pragma unroll
         for (int q = 0; q < M; ++q) {
+            double Kq[NSP];
+            arrived(Kn[0], sn[0]);
+#pragma unroll
+            for (int j = 0; j < NSP; ++j) Kq[j] = Kn[j];
+            const double rq = sn[0], vx = sn[1], vy = sn[2], vz = sn[3], tq = Rn * T;
+            if (q + 1 < M) ask(q + 1);
             reload_barrier();
-            const RLBM_CONST double* slotc = as_const(L.slotc) + opaque_zero();
-            const RLBM_CONST double* Kq = slotc + M + q * M;   // symmetric
-            const double rq = sp[R::ST + 4 * q][lane];
-            const double vx = sp[R::ST + 4 * q + 1][lane], vy = sp[R::ST + 4 * q + 2][lane], vz = sp[R::ST + 4 * q + 3][lane];
-            const double tq = slotc[q] * T;
             const double e = psi_u(py, uy, fma(uy, uy, tq)) * psi_u(pz, uz, fma(uz, uz, tq));
             const double v = psi_u(py, vy, fma(vy, vy, tq)) * psi_u(pz, vz, fma(vz, vz, tq));
             if (q < NSP) yz[q] = e;
@@ -1516,33 +1544,54 @@ __device__ __forceinline__ void species_layer(const LatDev& L, int par, int laye
         // the row's values without the old populations, in place: Fz = the
         // value at c_x = 0, (Fs, Fo) = those at c_x = -1, +1
 #pragma unroll
-        for (int j = 0; j < NSP; ++j) {
+        for (int j0 = 0; j0 < NSP; j0 += 4) {
+            double K[4], B[4], Rj[4];
+            const RLBM_CONST double* slotc = slot0 + opaque_zero();
+#pragma unroll
+            for (int e = 0; e < 4 && j0 + e < NSP; ++e) {
+                K[e] = sp[R::K + j0 + e][lane];
+                B[e] = sp[R::B + j0 + e][lane];
+                Rj[e] = slotc[j0 + e];
+            }
             reload_barrier();
-            const RLBM_CONST double* slotc = as_const(L.slotc) + opaque_zero();
-            const double K = sp[R::K + j][lane];
-            const double g = sp[R::B + j][lane] * yz[j];
-            const double hs = fma(K, Fs[j], g * fma(ux, ux, slotc[j] * T));
-            const double ho = fma(K, Fo[j], g * ux);
-            Fz[j] = 2.0 * (fma(K, Fz[j], g) - hs);
-            Fs[j] = hs - ho;
-            Fo[j] = hs + ho;
+#pragma unroll
+            for (int e = 0; e < 4 && j0 + e < NSP; ++e) {
+                const int j = j0 + e;
+                const double g = B[e] * yz[j];
+                const double hs = fma(K[e], Fs[j], g * fma(ux, ux, Rj[e] * T));
+                const double ho = fma(K[e], Fo[j], g * ux);
+                Fz[j] = 2.0 * (fma(K[e], Fz[j], g) - hs);
+                Fs[j] = hs - ho;
+                Fo[j] = hs + ho;
+            }
         }
+        double A[NSP], SC[F32 ? NSP : 1], G[F32 ? 3 : 1][NSP];
+        if constexpr (F32) {
+            const RLBM_CONST double* g = ref0 + opaque_zero();
+#pragma unroll
+            for (int c0 = 0; c0 < 3; ++c0)
+#pragma unroll
+                for (int j = 0; j < NSP; ++j) G[c0][j] = g[c0 * NL + j];
+        }
+#pragma unroll
+        for (int j = 0; j < NSP; ++j) {
+            A[j] = sp[R::A + j][lane];
+            if constexpr (F32) SC[j] = sp[R::SC + j][lane];
+        }
+        reload_barrier();
         auto put = [&](auto c0t, const double (&eq)[NSP]) {
             constexpr int c0 = decltype(c0t)::value;
-            float srd[NSP];
-            if constexpr (F32) species_scales<NSP>(L, par ^ 1, reader_at(node, o, c0, c1, c2), srd);
+            const float(&srd)[NSP] = rd[F32 ? c0 + 1 : 0];
             RLBM_GLOBAL S* win = win0 + (size_t)(c0 + 1) * P;
-            const RLBM_CONST double* G = ref0 + (F32 ? NL * (c0 + 1) + opaque_zero() : 0);
 #pragma unroll
             for (int j = 0; j < NSP; ++j) {
-                const double A = sp[R::A + j][lane];
                 const double f = (double)raw[j][c0 + 1];
                 opaque(win);
                 if constexpr (F32)
                     // A (f + s G) + eq - s_reader G
-                    st_off(win, off, __double2float_rn(fma(A, f, fma(sp[R::SC + j][lane] - (double)srd[j], G[j], eq[j]))));
+                    st_off(win, off, __double2float_rn(fma(A[j], f, fma(SC[j] - (double)srd[j], G[c0 + 1][j], eq[j]))));
                 else
-                    st_off(win, off, fma(A, f, eq[j]));
+                    st_off(win, off, fma(A[j], f, eq[j]));
                 win += (size_t)Q * P;
             }
         };
@@ -1758,10 +1807,24 @@ __device__ __forceinline__ void node_solve(const LatDev& L, int par, int lane, i
         const double h = 0.5 * common;
         double m[M][M], t[M], idg[M], V[M][3];   // m: upper triangle; t = Y_k / d_k
         double js[3] = {0.0, 0.0, 0.0};
+        double Kn[M], sn[4] = {0.0, 0.0, 0.0, 0.0};   // the next row's couplings and state, asked for one row ahead
+        auto ask = [&](int i) {
+            const RLBM_CONST double* k = Ks + i * M + opaque_zero();
+#pragma unroll
+            for (int c = 0; c < M; ++c) Kn[c] = k[c];
+#pragma unroll
+            for (int k4 = 0; k4 < (W || i < M - 1 ? 4 : 1); ++k4) sn[k4] = sp[R::ST + 4 * i + k4][lane];
+        };
+        ask(0);
 #pragma unroll
         for (int i = 0; i < M; ++i) {
+            arrived(Kn[0], sn[0]);
+            double Ki[M];
+#pragma unroll
+            for (int c = 0; c < M; ++c) Ki[c] = Kn[c];
+            const double ra = sn[0], X3[3] = {sn[1], sn[2], sn[3]};
+            if (i + 1 < M) ask(i + 1);
             reload_barrier();
-            const RLBM_CONST double* Ki = Ks + i * M + opaque_zero();
             double dg = 0.0;
 #pragma unroll
             for (int c = 0; c < M; ++c)
@@ -1777,13 +1840,12 @@ __device__ __forceinline__ void node_solve(const LatDev& L, int par, int lane, i
             for (int c = i + 1; c < M; ++c) m[i][c] = h * Ki[c];
             // u_a - u (u_a := u for an absent species); the slaved one's from
             // sum_a (j_a - rho_a u) = 0 (eq. strongest)
-            const double ra = sp[R::ST + 4 * i][lane];
             const double inv = ra <= 1e-14 * rho ? 0.0 : recip(ra);
 #pragma unroll
             for (int d = 0; d < 3; ++d) {
                 double X;
                 if (W || i < M - 1) {
-                    X = sp[R::ST + 4 * i + 1 + d][lane];
+                    X = X3[d];
                     js[d] -= X;
                 } else {
                     X = js[d];
@@ -1802,6 +1864,7 @@ __device__ __forceinline__ void node_solve(const LatDev& L, int par, int lane, i
             idg[i] = recip(dg);
             t[i] = Y[i] * idg[i];
         }
+        const double u3[3] = {sp[R::U][lane], sp[R::U + 1][lane], sp[R::U + 2][lane]};
 #pragma unroll
         for (int i = M - 1; i >= 0; --i) {
             reload_barrier();
@@ -1813,7 +1876,7 @@ __device__ __forceinline__ void node_solve(const LatDev& L, int par, int lane, i
 #pragma unroll
                 for (int c = i + 1; c < M; ++c) v = fma(m[i][c], V[c][d], v);   // V_c holds Y_c V_c here
                 v *= idg[i];
-                sp[R::ST + 4 * i + 1 + d][lane] = sp[R::U + d][lane] + v;
+                sp[R::ST + 4 * i + 1 + d][lane] = u3[d] + v;
                 V[i][d] = Y[i] * v;
                 flux[d] = fma(hy, V[i][d], flux[d]);
             }
