@@ -219,8 +219,7 @@ __device__ __forceinline__ double recip(double x) {
 // |ln x|): x = 2^k m with m in [sqrt(1/2), sqrt(2)), ln m = 2 artanh s with
 // s = (m - 1)/(m + 1), |s| < 0.172, by its power series to s^23 (the first
 // term left out is below 2^-66).  About 130 cycles where the library's log, which
-// carries twice the precision inside, takes 400.  Zero and negative x give a
-// finite value, NaN gives NaN.
+// carries twice the precision inside, takes 400.  NaN unless x > 0.
 __device__ __forceinline__ double ln(double x) {
     double m = __builtin_amdgcn_frexp_mant(x);   // [1/2, 1)
     int k = __builtin_amdgcn_frexp_exp(x);
@@ -234,20 +233,21 @@ __device__ __forceinline__ double ln(double x) {
     // ln 2 in two parts, the first with trailing zeros so that k times it is exact
     const double hi = 0x1.62e42fefap-1, lo = 0x1.cf79abc9e3b39p-40;
     const double t = s + s;
-    return fma((double)k, hi, fma((double)k, lo, fma(t * z, p, t)));
+    const double v = fma((double)k, hi, fma((double)k, lo, fma(t * z, p, t)));
+    return x > 0.0 ? v : __builtin_nan("");
 }
 
 // exp(x) to about an ulp, e the coefficients above: x = n ln 2 + r.  Beyond
-// |x| = 1000 the result is 0 or infinity already.
+// |x| = 1000 the result is 0 or infinity already.  NaN gives NaN.
 __device__ __forceinline__ double expo(const RLBM_CONST double* e, double x) {
-    x = fmin(fmax(x, -1000.0), 1000.0);
-    const double n = __builtin_rint(x * 0x1.71547652b82fep+0);
-    const double r = fma(-n, 0x1.cf79abc9e3b39p-40, fma(-n, 0x1.62e42fefap-1, x));
+    const double c = fmin(fmax(x, -1000.0), 1000.0);   // loses a NaN
+    const double n = __builtin_rint(c * 0x1.71547652b82fep+0);
+    const double r = fma(-n, 0x1.cf79abc9e3b39p-40, fma(-n, 0x1.62e42fefap-1, c));
     double p = e[EXP_COEF - 1];
 #pragma unroll
     for (int k = EXP_COEF - 2; k >= 0; --k) p = fma(p, r, e[k]);
     p = fma(fma(fma(p, r, 0.5), r, 1.0), r, 1.0);
-    return __builtin_amdgcn_ldexp(p, (int)n);
+    return x == x ? __builtin_amdgcn_ldexp(p, (int)n) : x;
 }
 
 // ---------------------------------------------------------------------------

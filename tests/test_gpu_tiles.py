@@ -289,3 +289,30 @@ def test_flow_tiles(name, dims, storage, mech9):
     gp, op = lat.populations(), ora.populations()
     for l in range(op.shape[0]):
         assert _nerr(gp[l], op[l]) <= (1e-10 if storage == "f64" else TOL[storage]), l
+
+
+@pytest.mark.parametrize("reaction", ["explicit", "implicit"])
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+def test_negative_temperature_is_flagged(mech9, storage, reaction):
+    """A state whose energy stands for a temperature below zero, which the
+    Newton iteration reaches, has no rates: the lattice's flag is set within
+    three steps."""
+    rlbm = _rlbm()
+    print(f"case negative temperature {storage} {reaction}", flush=True)
+    case = wl.make_case("reactor", seed=4, mech=mech9, nx=4, ny=4, nz=4, reaction=reaction)
+    lat = rlbm.Lattice(case, storage=storage).set_state()
+    pops = lat.populations()
+    T0 = lat.fields()["T"].mean()
+    x0, t0, x, t = 1.0, T0, 1.0 + 1e-3, None
+    for _ in range(20):      # secant for the energy of -0.3 T0
+        p = pops.copy()
+        p[-1] *= x
+        lat.write_populations(p)
+        t = lat.fields()["T"].mean()
+        if -0.6 * T0 < t < -0.1 * T0:
+            break
+        x0, t0, x = x, t, x + np.clip((-0.3 * T0 - t) * (x - x0) / (t - t0), -0.5, 0.5)
+    assert -0.6 * T0 < t < -0.1 * T0
+    assert lat.status() == 0
+    lat.step(3)
+    assert lat.status() == 1
