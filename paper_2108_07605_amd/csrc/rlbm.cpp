@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -292,6 +293,51 @@ struct rlbm_mech {
 constexpr size_t PIN_HEAD = 1024, PIN_STAGE = 512 << 10;
 static_assert(64 + (6 + RLBM_MAX_ELEMENTS) * sizeof(double) <= PIN_HEAD, "flags and invariants before the staging");
 
+namespace {
+// The lattices' blocks of pinned memory.  Allocating and freeing one takes 100
+// us, a fifth of the creation of a small lattice, so up to PIN_KEPT of those
+// given back wait for the next lattice; they are freed with the last lattice.
+// A block is idle between calls (every call that uses it waits for its
+// kernels), so the next lattice may be on another stream or device.
+constexpr int PIN_KEPT = 8;
+std::mutex g_pin_mutex;
+char* g_pin_kept[PIN_KEPT];
+int g_pin_n = 0, g_pin_live = 0;
+
+hipError_t take_pinned(char** out) {
+    {
+        std::lock_guard<std::mutex> lock(g_pin_mutex);
+        ++g_pin_live;
+        if (g_pin_n) {
+            *out = g_pin_kept[--g_pin_n];
+            return hipSuccess;
+        }
+    }
+    void* p = nullptr;
+    const hipError_t e = hipHostMalloc(&p, PIN_HEAD + PIN_STAGE, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
+    if (e != hipSuccess) {
+        std::lock_guard<std::mutex> lock(g_pin_mutex);
+        --g_pin_live;
+        return e;
+    }
+    *out = (char*)p;
+    return hipSuccess;
+}
+
+void give_pinned(char* p) {
+    char* drop[PIN_KEPT + 1];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_pin_mutex);
+        if (g_pin_n < PIN_KEPT) g_pin_kept[g_pin_n++] = p;
+        else drop[n++] = p;
+        if (--g_pin_live == 0)
+            while (g_pin_n) drop[n++] = g_pin_kept[--g_pin_n];
+    }
+    while (n) (void)hipHostFree(drop[--n]);
+}
+}  // namespace
+
 struct rlbm_lattice {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -459,7 +505,7 @@ int rlbm_lattice_bytes(const rlbm_lattice_desc* d, const rlbm_mech* mech, size_t
 }
 
 static void drop(rlbm_lattice* lat) {
-    if (lat->pin) (void)hipHostFree(lat->pin);
+    if (lat->pin) give_pinned(lat->pin);
     delete lat;
 }
 
@@ -498,13 +544,10 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
     {
         const size_t need = (6 + (size_t)M) * (size_t)lat->geo.N * sizeof(double);
         lat->stage = need <= PIN_STAGE ? need : 0;
-        void *hp = nullptr, *dp = nullptr;
-        hipError_t e = hipHostMalloc(&hp, PIN_HEAD + lat->stage, hipHostMallocMapped | hipHostMallocCoherent);
-        if (e == hipSuccess) {
-            lat->pin = (char*)hp;
-            e = hipHostGetDevicePointer(&dp, hp, 0);
-            lat->d_pin = (char*)dp;
-        }
+        void* dp = nullptr;
+        hipError_t e = take_pinned(&lat->pin);
+        if (e == hipSuccess) e = hipHostGetDevicePointer(&dp, lat->pin, 0);
+        lat->d_pin = (char*)dp;
         if (e != hipSuccess) {
             drop(lat);
             return hip_fail(e, "hipHostMalloc");
