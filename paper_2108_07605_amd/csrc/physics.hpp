@@ -421,8 +421,8 @@ __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double
         for (int b = 0; b < K; ++b) Jr[a][b] = 0.0;
     const int R = mc.R;
     if (R == 0) return;
-    const double lnT = log(T);
-    const double invT = 1.0 / T;
+    const double lnT = ln(T);
+    const double invT = recip(T);
 #pragma unroll
     for (int a = 0; a < M; ++a) {
         ls.c[a * NT] = fmax(rho_a[a], 0.0) * mc.inv_m[a];
@@ -444,7 +444,7 @@ __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double
             const double v = ls.c[x.fac_f[f] * NT];
             cf[f] = f < nf ? v : 1.0;
         }
-        const double kf = exp(lnkf);
+        const double kf = expo(mc.ec, lnkf);
         double fwd = kf;
 #pragma unroll
         for (int f = 0; f < MAXO; ++f) fwd *= cf[f];
@@ -467,7 +467,7 @@ __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double
             for (int f = 0; f < MAXO; ++f) sg += gr[f];
 #pragma unroll
             for (int f = 0; f < MAXO; ++f) sg -= gf[f];
-            const double kr = exp(lnkf + sg - x.dnu_sum * lnc);
+            const double kr = expo(mc.ec, lnkf + sg - x.dnu_sum * lnc);
             double bwd = kr;
 #pragma unroll
             for (int f = 0; f < MAXO; ++f) bwd *= cr[f];
@@ -504,6 +504,7 @@ __device__ __forceinline__ void rates_jac(MechC mc0, const double* rho_a, double
 // leaves the largest |A[i][k]|, i >= k, in row k (the first one on ties).
 template <int M>
 __device__ __forceinline__ void solve_pivoted(double (*A)[M], double* b) {
+    double inv[M];
 #pragma unroll
     for (int k = 0; k < M; ++k) {
 #pragma unroll
@@ -519,10 +520,10 @@ __device__ __forceinline__ void solve_pivoted(double (*A)[M], double* b) {
             b[k] = sw ? b[i] : t;
             b[i] = sw ? t : b[i];
         }
-        const double inv = 1.0 / A[k][k];
+        inv[k] = recip(A[k][k]);
 #pragma unroll
         for (int i = k + 1; i < M; ++i) {
-            const double f = A[i][k] * inv;
+            const double f = A[i][k] * inv[k];
 #pragma unroll
             for (int j = k + 1; j < M; ++j) A[i][j] = fma(-f, A[k][j], A[i][j]);
             b[i] = fma(-f, b[k], b[i]);
@@ -533,7 +534,7 @@ __device__ __forceinline__ void solve_pivoted(double (*A)[M], double* b) {
         double s = b[k];
 #pragma unroll
         for (int j = k + 1; j < M; ++j) s = fma(-A[k][j], b[j], s);
-        b[k] = s / A[k][k];
+        b[k] = s * inv[k];
     }
 }
 
@@ -556,7 +557,7 @@ __device__ __forceinline__ void reaction_increment(MechC mc0, const double* rho_
         return;
     }
     const double inv_l = 1.0 / (double)l;
-    const double inv_rho = 1.0 / rho;
+    const double inv_rho = recip(rho);
     double Ts = T;
     for (int s = 0; s < l; ++s) {
         MechC mc = in_loop(mc0);
