@@ -822,7 +822,8 @@ __device__ __forceinline__ void tile_gradients(const LatDev& L, int node, int la
 // loads are latency-bound and the chemistry arithmetic-bound, so the two
 // share one launch.  Holds an (M-1)^2 matrix in registers.  150x31x29, two
 // sub-steps: 144 -> 140 us with this file's ln, exp and reciprocals in the rates
-// and the pivots' reciprocals kept.
+// and the pivots' reciprocals kept, 135 us with the derivatives of the factors a
+// reaction has instead of all its slots.
 // ---------------------------------------------------------------------------
 static_assert(NODE_TILE == 64, "one wave per tile");
 template <int M>

@@ -336,8 +336,9 @@ struct ChemLds {
     double* dq;  // &dq[0][tid]
 };
 
-// Adds k prod_{g != f} c[g] to dq[fac[f]] for every factor f < n (c[f] = 1
-// and nothing added for f >= n).
+// Adds k prod_{g != f} c[g] to dq[fac[f]] for every factor f < n (c[f] = 1 for
+// the others).  n is wave-uniform: a branch costs less than the LDS read and
+// write of an unused slot.
 template <int NT>
 __device__ __forceinline__ void scatter_factor_derivs(const ChemLds<NT>& ls, const RLBM_CONST int* fac, int n,
                                                       const double* c, double k) {
@@ -350,7 +351,8 @@ __device__ __forceinline__ void scatter_factor_derivs(const ChemLds<NT>& ls, con
 #pragma unroll
     for (int f = MAXO - 2; f >= 0; --f) suf[f] = suf[f + 1] * c[f + 1];
 #pragma unroll
-    for (int f = 0; f < MAXO; ++f) ls.dq[fac[f] * NT] += f < n ? pre[f] * suf[f] : 0.0;
+    for (int f = 0; f < MAXO; ++f)
+        if (f < n) ls.dq[fac[f] * NT] += pre[f] * suf[f];
 }
 
 // Molar production rates of the reactions r0, r0 + dr, r0 + 2 dr, ...:
