@@ -2872,7 +2872,7 @@ __global__ __launch_bounds__(256) void k_scale_init(const LatDev* __restrict__ l
 // Initial populations: the equilibria of the given state, k_update's split
 // (three waves per 64 nodes, one c_z layer each).  A lattice's axis factors
 // are formed once and multiplied out over the layer's nine velocities; the
-// kernel is bound by its stores.  512x64x64, FP32 storage: 2.38 -> 1.21 ms
+// kernel is bound by its stores.  512x64x64, FP32 storage: 2.38 -> 1.43 ms
 // against one thread per node that evaluated every velocity from the state.
 template <int M, typename S, int W>
 __global__ __launch_bounds__(IO_THREADS) void k_init(const LatDev* __restrict__ lat, const double* __restrict__ rho_in,
@@ -3016,7 +3016,7 @@ __global__ __launch_bounds__(512) void k_refs(const LatDev* __restrict__ lat, do
 
 // Macroscopic fields of the stored populations.  Bound by the populations'
 // read; the layers' sums meet in LDS and the first wave solves for T.
-// 512x64x64, FP32 storage: 2.41 -> 0.59 ms against one thread per node
+// 512x64x64, FP32 storage: 2.41 -> 0.53 ms against one thread per node
 // looping over single velocities; 1024 nodes: 106 -> 8 us.  status[0] takes
 // the failure flag as the steps left it, status[1] this kernel's own, in
 // pinned host memory: a copy of the flag after the kernel takes 11 us.
@@ -3080,7 +3080,7 @@ __global__ __launch_bounds__(IO_THREADS) void k_fields(const LatDev* __restrict_
 // into (write = 1) the current population buffer; buf holds [nl][27][N].  One
 // thread per node and three velocities of one row (blockIdx.y the row, z the
 // lattice): the plane is uniform, where one thread per value divided 64-bit
-// indices.  256x64x16, FP32 storage, all lattices: 423 -> 338 us.
+// indices.  256x64x16, FP32 storage, all lattices: 423 -> 305 us.
 template <int M, typename S, int W>
 __global__ __launch_bounds__(256) void k_pops(const LatDev* __restrict__ lat, long long t, int l0, double* buf, int write) {
     constexpr int LF = Lat<M, W>::LF, LG = Lat<M, W>::LG, NL = Lat<M, W>::NL;
@@ -3120,7 +3120,7 @@ __global__ __launch_bounds__(256) void k_pops(const LatDev* __restrict__ lat, lo
 // Per-block partial sums of the invariants over INV_NODES nodes; nv = 6 + E
 // values per block.  Every sum has a fixed order: over a lane's nodes, over
 // the lanes of a wave (a butterfly), over the three waves.  256x64x64, FP32
-// storage: 1.25 -> 0.34 ms.
+// storage: 1.25 -> 0.25 ms.
 constexpr int INV_NODES = 256;
 template <int M, typename S, int W>
 __global__ __launch_bounds__(IO_THREADS) void k_invariants(const LatDev* __restrict__ lat, long long t,
