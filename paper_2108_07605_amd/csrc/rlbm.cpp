@@ -614,11 +614,13 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
     const int nb64 = (int)((g.N + 63) / 64);
     const int blk[6] = {0, nb_nodes, 0, nb_if, 0, nb64};
     const int zero = 0;
-    // the tables go up one behind the other and are waited for once
+    // the tables go up one behind the other and are waited for once, on the
+    // null stream: the caller may have had the memory from a pool whose earlier
+    // work, on that stream, is still to end
     hipError_t up = hipSuccess;
 #define UP(dst, src, n)                                                                                     \
     do {                                                                                                    \
-        if (up == hipSuccess) up = hipMemcpyAsync((dst), (src), (n), hipMemcpyHostToDevice, lat->stream);  \
+        if (up == hipSuccess) up = hipMemcpyAsync((dst), (src), (n), hipMemcpyHostToDevice, nullptr);       \
     } while (0)
     UP(base + p.off_mech, &mech->dev, sizeof(MechDev));
     UP(lat->d_lat, &h, sizeof(LatDev));
@@ -634,7 +636,7 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
         UP(base + p.off_ifblk, g.if_blk.data(), g.if_blk.size() * sizeof(int));
     }
 #undef UP
-    const hipError_t synced = hipStreamSynchronize(lat->stream);
+    const hipError_t synced = hipStreamSynchronize(nullptr);
     if (up == hipSuccess) up = synced;
     if (up != hipSuccess) {
         drop(lat);

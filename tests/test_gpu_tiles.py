@@ -316,3 +316,26 @@ def test_negative_temperature_is_flagged(mech9, storage, reaction):
     assert lat.status() == 0
     lat.step(3)
     assert lat.status() == 1
+
+
+def test_creation_waits_for_earlier_work_on_its_memory(mech9):
+    """A lattice on a side stream, in memory that the allocator took back from
+    a tensor still being written on the default stream, has its tables intact."""
+    rlbm = _rlbm()
+    import torch
+    case = wl.make_case("tube", seed=8, mech=mech9, nx=300)
+    ref = rlbm.Lattice(case, storage="f64").set_state()
+    ref.step(2)
+    want = ref.populations()
+    side = torch.cuda.Stream()
+    for _ in range(3):
+        block = torch.empty(ref.nbytes + 256, dtype=torch.uint8, device="cuda")
+        a = torch.randn(4096, 4096, device="cuda")
+        for _ in range(20):
+            a = (a @ a).clamp_(-1.0, 1.0)       # a few milliseconds ahead of the fill
+        block.fill_(255)
+        del block
+        lat = rlbm.Lattice(case, storage="f64", stream=side).set_state()
+        lat.step(2)
+        np.testing.assert_array_equal(lat.fields()["T"], ref.fields()["T"])
+        np.testing.assert_array_equal(lat.populations(), want)
