@@ -1946,6 +1946,15 @@ __global__ __launch_bounds__(SPC_THREADS) __attribute__((amdgpu_waves_per_eu(M >
 // ---------------------------------------------------------------------------
 constexpr int FLOW_THREADS = 3 * NODE_TILE;
 
+// What this wave's lanes wrote to LDS before is seen by all of them after.  A
+// wave's LDS operations run in order, so this costs no instruction; it keeps
+// the compiler from moving one lane's reads above another's writes.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sums over c_y of one column of a layer: the enthalpy coefficients and
 // Phi_x, Phi_z with the weights w(c_y), and the coefficients and Phi_y with
 // c_y.
@@ -2019,15 +2028,19 @@ __device__ __forceinline__ void layer_gradients(const LatDev& L, int n0, int lan
         part[5] = c < 0 ? w * v.A : fma(w, v.A, part[5]);
     };
     if (n0 % nx + NODE_TILE <= nx) {
+        double outer = 0.0;
         {
             const int side = lane >= EDGE ? 1 : 0, q = lane - side * EDGE, j = q / 9, k = q - 9 * j;
             const int x0 = n0 % nx, x1 = x0 + NODE_TILE - 1;
             const int xg = side ? (x1 == nx - 1 ? (px ? 0 : x1) : x1 + 1) : (x0 == 0 ? (px ? nx - 1 : 0) : x0 - 1);
             if (lane < 2 * EDGE)
-                edges[lane] = aux[(k < 6 ? AUX_Y + M + k : AUX_PHI + k - 6) * N + (size_t)((zr + sel3(j - 1, gy[0], gy[1], gy[2])) * nx + xg)];
+                outer = aux[(k < 6 ? AUX_Y + M + k : AUX_PHI + k - 6) * N + (size_t)((zr + sel3(j - 1, gy[0], gy[1], gy[2])) * nx + xg)];
         }
         LayerCol s;
         layer_column<M>(aux, N, nx, zr, gy, x, s);
+        // written only now, so that the wait below leaves the columns' loads in flight
+        if (lane < 2 * EDGE) edges[lane] = outer;
+        wave_sync();
         Column edge = {0.0, 0.0, 0.0, 0.0, 0.0};
         if (lane == 0 || lane == NODE_TILE - 1) {
             const double* from = &edges[lane == 0 ? 0 : EDGE];
