@@ -334,7 +334,13 @@ void give_pinned(char* p) {
         if (--g_pin_live == 0)
             while (g_pin_n) drop[n++] = g_pin_kept[--g_pin_n];
     }
+    if (n == 0) return;
+    // a lattice may be destroyed while some stream is captured, and a free in
+    // any other mode than this would invalidate the capture
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
     while (n) (void)hipHostFree(drop[--n]);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
 }
 }  // namespace
 
