@@ -175,8 +175,9 @@ int rlbm_lattice_bytes(const rlbm_lattice_desc* desc, const rlbm_mech* mech, siz
  * (256-byte aligned), which must stay valid until rlbm_lattice_destroy.
  * `stream` is a hipStream_t (NULL = default stream) on which all work of
  * this lattice is enqueued; it is borrowed, not owned.  The device is the
- * current device at creation.  Holds at most 513 KiB of pinned host memory of
- * its own until rlbm_lattice_destroy.  Synchronous (uploads tables). */
+ * current device at creation.  Holds pinned host memory of its own until
+ * rlbm_lattice_destroy: 4 KiB, or up to 513 KiB where that holds its fields.
+ * Synchronous (uploads tables). */
 int rlbm_lattice_create(const rlbm_lattice_desc* desc, const rlbm_mech* mech, void* dev_mem,
                         size_t bytes, void* stream, rlbm_lattice** out);
 void rlbm_lattice_destroy(rlbm_lattice* lat);

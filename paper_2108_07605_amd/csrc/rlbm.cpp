@@ -290,47 +290,61 @@ struct rlbm_mech {
     MechDev dev;
 };
 
-constexpr size_t PIN_HEAD = 1024, PIN_STAGE = 512 << 10;
+constexpr size_t PIN_HEAD = 1024, PIN_STAGE = 512 << 10, PIN_PAGE = 4096;
 static_assert(64 + (6 + RLBM_MAX_ELEMENTS) * sizeof(double) <= PIN_HEAD, "flags and invariants before the staging");
 
 namespace {
-// The lattices' blocks of pinned memory.  Allocating and freeing one takes 100
-// us, a fifth of the creation of a small lattice, so up to PIN_KEPT of those
-// given back wait for the next lattice; they are freed with the last lattice.
-// A block is idle between calls (every call that uses it waits for its
-// kernels), so the next lattice may be on another stream or device.
+// The lattices' blocks of pinned memory, one of 4, 8, .. 256, 513 KiB each.
+// Allocating and freeing one takes tens of us, of the 80 of a small lattice's
+// creation, so up to PIN_KEPT of those given back wait for the next lattice;
+// they are freed with the last lattice.  A block is idle between calls (every
+// call that uses it waits for its kernels), so the next lattice may be on
+// another stream or device.
+struct PinBlock {
+    char* p;
+    size_t bytes;
+};
 constexpr int PIN_KEPT = 8;
 std::mutex g_pin_mutex;
-char* g_pin_kept[PIN_KEPT];
+PinBlock g_pin_kept[PIN_KEPT];
 int g_pin_n = 0, g_pin_live = 0;
 
-hipError_t take_pinned(char** out) {
+size_t pin_bytes(size_t need) {
+    size_t b = PIN_PAGE;
+    while (b < need) b *= 2;
+    return std::min(b, PIN_HEAD + PIN_STAGE);
+}
+
+hipError_t take_pinned(size_t bytes, PinBlock* out) {
     {
         std::lock_guard<std::mutex> lock(g_pin_mutex);
-        ++g_pin_live;
-        if (g_pin_n) {
-            *out = g_pin_kept[--g_pin_n];
-            return hipSuccess;
-        }
+        for (int k = g_pin_n - 1; k >= 0; --k)
+            if (g_pin_kept[k].bytes == bytes) {
+                *out = g_pin_kept[k];
+                g_pin_kept[k] = g_pin_kept[--g_pin_n];
+                ++g_pin_live;
+                return hipSuccess;
+            }
     }
     void* p = nullptr;
-    const hipError_t e = hipHostMalloc(&p, PIN_HEAD + PIN_STAGE, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
+    const hipError_t e = hipHostMalloc(&p, bytes, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
     if (e != hipSuccess) {
-        std::lock_guard<std::mutex> lock(g_pin_mutex);
-        --g_pin_live;
+        (void)hipGetLastError();   // the caller may do with less
         return e;
     }
-    *out = (char*)p;
+    *out = PinBlock{(char*)p, bytes};
+    std::lock_guard<std::mutex> lock(g_pin_mutex);
+    ++g_pin_live;
     return hipSuccess;
 }
 
-void give_pinned(char* p) {
-    char* drop[PIN_KEPT + 1];
+void give_pinned(PinBlock b) {
+    PinBlock drop[PIN_KEPT + 1];
     int n = 0;
     {
         std::lock_guard<std::mutex> lock(g_pin_mutex);
-        if (g_pin_n < PIN_KEPT) g_pin_kept[g_pin_n++] = p;
-        else drop[n++] = p;
+        if (g_pin_n < PIN_KEPT) g_pin_kept[g_pin_n++] = b;
+        else drop[n++] = b;
         if (--g_pin_live == 0)
             while (g_pin_n) drop[n++] = g_pin_kept[--g_pin_n];
     }
@@ -339,7 +353,7 @@ void give_pinned(char* p) {
     // any other mode than this would invalidate the capture
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
-    while (n) (void)hipHostFree(drop[--n]);
+    while (n) (void)hipHostFree(drop[--n].p);
     (void)hipThreadExchangeStreamCaptureMode(&mode);
 }
 }  // namespace
@@ -363,12 +377,12 @@ struct rlbm_lattice {
     // Pinned host memory of the calls that return results: written by the
     // read-out kernels and read once their stream is synchronised, and the
     // staging of small fields (with a copy per array a read of 1024 nodes took
-    // 101 us, through here 24 us).  PIN_STAGE bytes
-    // hold 4369 nodes of nine species; beyond, the copies are bound by their
-    // bytes.
+    // 101 us, through here 24 us).  PIN_STAGE bytes hold 4369 nodes of nine
+    // species; beyond, the copies are bound by their bytes, and the lattice has
+    // no staging.
     char* pin = nullptr;      // [2] flags, then the invariants, then `stage` bytes at PIN_HEAD
     char* d_pin = nullptr;    // the same memory as the device sees it
-    size_t stage = 0;
+    size_t pin_size = 0, stage = 0;
     long long steps_done = 0;
     bool state_set = false;
     unsigned timing = 0;           // bit k: time kernel k
@@ -511,7 +525,7 @@ int rlbm_lattice_bytes(const rlbm_lattice_desc* d, const rlbm_mech* mech, size_t
 }
 
 static void drop(rlbm_lattice* lat) {
-    if (lat->pin) give_pinned(lat->pin);
+    if (lat->pin) give_pinned(PinBlock{lat->pin, lat->pin_size});
     delete lat;
 }
 
@@ -550,8 +564,15 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
     {
         const size_t need = (6 + (size_t)M) * (size_t)lat->geo.N * sizeof(double);
         lat->stage = need <= PIN_STAGE ? need : 0;
+        PinBlock pb{};
+        hipError_t e = take_pinned(pin_bytes(PIN_HEAD + lat->stage), &pb);
+        if (e != hipSuccess && lat->stage) {   // small transfers then go as the others do
+            lat->stage = 0;
+            e = take_pinned(PIN_PAGE, &pb);
+        }
+        lat->pin = pb.p;
+        lat->pin_size = pb.bytes;
         void* dp = nullptr;
-        hipError_t e = take_pinned(&lat->pin);
         if (e == hipSuccess) e = hipHostGetDevicePointer(&dp, lat->pin, 0);
         lat->d_pin = (char*)dp;
         if (e != hipSuccess) {

@@ -1,0 +1,94 @@
+"""Error paths and host memory of the library's host code (CPU).
+
+A stand-in for the HIP runtime (hip_host_stub.cpp) is compiled with g++ and
+loaded in front of librlbm.so in a process of its own; each check below is a
+function that runs there."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+class Host:
+    """Lattices in host memory behind the stand-in."""
+
+    def __init__(self, stub):
+        self.stub = ctypes.CDLL(stub, mode=ctypes.RTLD_GLOBAL)
+        self.stub.stub_pinned.restype = ctypes.c_size_t
+        self.stub.stub_pinned_limit.argtypes = [ctypes.c_size_t]
+        for f in ("stub_queued", "stub_waits", "stub_frees"):
+            getattr(self.stub, f).restype = ctypes.c_long
+        self.stub.stub_fail_launch.argtypes = [ctypes.c_long]
+        sys.path.insert(0, ROOT)
+        from paper_2108_07605_amd import rlbm, workloads as wl
+        self.rlbm, self.wl, self.L = rlbm, wl, rlbm.lib()
+        self.mech9 = wl.mechanism_h2air9()
+        self.mech = rlbm.Mechanism(self.mech9)
+
+    def lattice(self, nx, storage="f32dev", **kw):
+        """(handle, memory, case) of a tube of nx nodes."""
+        case = self.wl.make_case("tube", nx=nx, mech=self.mech9, **kw)
+        d, keep = self.rlbm.lattice_desc(case, storage)
+        n = self.rlbm.lattice_bytes(case, self.mech, storage)
+        mem = np.zeros(n + 256, np.uint8)
+        h = ctypes.c_void_p()
+        self.rlbm._check(self.L.rlbm_lattice_create(ctypes.byref(d), self.mech.handle, (mem.ctypes.data + 255) & ~255, n,
+                                                    None, ctypes.byref(h)))
+        return h, mem, case
+
+    def set_state(self, h, case):
+        arrs = [np.ascontiguousarray(case["init"][k], dtype=np.float64) for k in ("rho", "u", "T", "Y")]
+        return self.L.rlbm_set_state(h, *[a.ctypes.data for a in arrs], 0)
+
+
+def check_pinned_memory_by_size(host):
+    """A lattice holds pinned memory for its own small fields only."""
+    held = host.lattice(30000)
+    at = host.stub.stub_pinned()
+    for nx, most in ((64, 16 << 10), (1024, 256 << 10), (4369, 513 << 10), (4370, 4 << 10), (20000, 4 << 10)):
+        h, _mem, _ = host.lattice(nx)
+        assert host.stub.stub_pinned() - at <= most, nx
+        host.L.rlbm_lattice_destroy(h)
+        at = host.stub.stub_pinned()   # what is kept is used again by a lattice of its size
+        h, _mem, _ = host.lattice(nx)
+        assert host.stub.stub_pinned() == at
+        host.L.rlbm_lattice_destroy(h)
+    host.L.rlbm_lattice_destroy(held[0])
+
+
+def check_creation_without_staging(host):
+    """Where no larger pinned block can be had, lattices are created without
+    staging; their states are still taken."""
+    host.stub.stub_pinned_limit(4096)
+    for nx in (64, 4369, 5000):
+        h, _mem, case = host.lattice(nx)
+        assert host.set_state(h, case) == 0
+        assert host.stub.stub_queued() == 0
+        host.L.rlbm_lattice_destroy(h)
+
+
+CHECKS = {n: f for n, f in list(globals().items()) if n.startswith("check_")}
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "libhip_host_stub.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "hip_host_stub.cpp"), "-o", out],
+                   check=True)
+    return out
+
+
+@pytest.mark.parametrize("name", sorted(CHECKS))
+def test_host_path(stub, name):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, name], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    CHECKS[sys.argv[2]](Host(sys.argv[1]))
