@@ -163,7 +163,9 @@ typedef struct rlbm_lattice_desc {
     int32_t reaction;             /* RLBM_REACTION_* */
 } rlbm_lattice_desc;
 
-/* Create / destroy a mechanism (host object; uploaded per lattice). */
+/* Create / destroy a mechanism (host object; uploaded per lattice).  The pinned
+ * memory that destroyed lattices left for the next ones, 2 MiB at most, is
+ * freed once neither a lattice nor a mechanism is left. */
 int rlbm_mech_create(const rlbm_mech_desc* desc, rlbm_mech** out);
 void rlbm_mech_destroy(rlbm_mech* mech);
 

@@ -295,19 +295,21 @@ static_assert(64 + (6 + RLBM_MAX_ELEMENTS) * sizeof(double) <= PIN_HEAD, "flags 
 
 namespace {
 // The lattices' blocks of pinned memory, one of 4, 8, .. 256, 513 KiB each.
-// Allocating and freeing one takes tens of us, of the 80 of a small lattice's
-// creation, so up to PIN_KEPT of those given back wait for the next lattice;
-// they are freed with the last lattice.  A block is idle between calls (every
-// call that uses it waits for its kernels), so the next lattice may be on
-// another stream or device.
+// Allocating one takes tens of us, of the 80 of a small lattice's creation, and
+// a free waits for all work on the device, so blocks given back wait for the
+// next lattice, PIN_KEPT bytes of them at most.  They are freed once neither a
+// lattice nor a mechanism is left.  A block is idle between calls (every call
+// that uses it waits for its kernels), so the next lattice may be on another
+// stream or device.
 struct PinBlock {
     char* p;
     size_t bytes;
 };
-constexpr int PIN_KEPT = 8;
+constexpr size_t PIN_KEPT = 2 << 20;
 std::mutex g_pin_mutex;
-PinBlock g_pin_kept[PIN_KEPT];
-int g_pin_n = 0, g_pin_live = 0;
+PinBlock g_pin_kept[PIN_KEPT / PIN_PAGE];
+size_t g_pin_kept_bytes = 0;
+int g_pin_n = 0, g_pin_lattices = 0, g_pin_mechs = 0;
 
 size_t pin_bytes(size_t need) {
     size_t b = PIN_PAGE;
@@ -322,7 +324,8 @@ hipError_t take_pinned(size_t bytes, PinBlock* out) {
             if (g_pin_kept[k].bytes == bytes) {
                 *out = g_pin_kept[k];
                 g_pin_kept[k] = g_pin_kept[--g_pin_n];
-                ++g_pin_live;
+                g_pin_kept_bytes -= bytes;
+                ++g_pin_lattices;
                 return hipSuccess;
             }
     }
@@ -334,26 +337,46 @@ hipError_t take_pinned(size_t bytes, PinBlock* out) {
     }
     *out = PinBlock{(char*)p, bytes};
     std::lock_guard<std::mutex> lock(g_pin_mutex);
-    ++g_pin_live;
+    ++g_pin_lattices;
     return hipSuccess;
 }
 
-void give_pinned(PinBlock b) {
-    PinBlock drop[PIN_KEPT + 1];
-    int n = 0;
+// A lattice's block (b) or a mechanism (null) has gone.
+void give_pinned(const PinBlock* b) {
+    PinBlock over{};
+    bool all = false;
     {
         std::lock_guard<std::mutex> lock(g_pin_mutex);
-        if (g_pin_n < PIN_KEPT) g_pin_kept[g_pin_n++] = b;
-        else drop[n++] = b;
-        if (--g_pin_live == 0)
-            while (g_pin_n) drop[n++] = g_pin_kept[--g_pin_n];
+        if (b) {
+            if (g_pin_kept_bytes + b->bytes <= PIN_KEPT) {
+                g_pin_kept[g_pin_n++] = *b;
+                g_pin_kept_bytes += b->bytes;
+            } else {
+                over = *b;
+            }
+            --g_pin_lattices;
+        } else {
+            --g_pin_mechs;
+        }
+        all = g_pin_n > 0 && g_pin_lattices == 0 && g_pin_mechs == 0;
     }
-    if (n == 0) return;
+    if (!over.p && !all) return;
     // a lattice may be destroyed while some stream is captured, and a free in
     // any other mode than this would invalidate the capture
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
-    while (n) (void)hipHostFree(drop[--n].p);
+    if (over.p) (void)hipHostFree(over.p);
+    while (all) {
+        PinBlock k{};
+        {
+            std::lock_guard<std::mutex> lock(g_pin_mutex);
+            if ((all = g_pin_n > 0)) {
+                k = g_pin_kept[--g_pin_n];
+                g_pin_kept_bytes -= k.bytes;
+            }
+        }
+        if (k.p) (void)hipHostFree(k.p);
+    }
     (void)hipThreadExchangeStreamCaptureMode(&mode);
 }
 }  // namespace
@@ -506,11 +529,19 @@ int rlbm_mech_create(const rlbm_mech_desc* d, rlbm_mech** out) {
     md.mu_exp = d->mu_exp;
     md.inv_Pr = 1.0 / d->Pr;
     md.D_exp = d->D_exp;
+    {
+        std::lock_guard<std::mutex> lock(g_pin_mutex);
+        ++g_pin_mechs;
+    }
     *out = m;
     return RLBM_OK;
 }
 
-void rlbm_mech_destroy(rlbm_mech* m) { delete m; }
+void rlbm_mech_destroy(rlbm_mech* m) {
+    if (!m) return;
+    delete m;
+    give_pinned(nullptr);
+}
 
 int rlbm_lattice_bytes(const rlbm_lattice_desc* d, const rlbm_mech* mech, size_t* bytes) {
     if (!mech || !bytes) return fail(RLBM_EINVAL, "null argument");
@@ -525,7 +556,10 @@ int rlbm_lattice_bytes(const rlbm_lattice_desc* d, const rlbm_mech* mech, size_t
 }
 
 static void drop(rlbm_lattice* lat) {
-    if (lat->pin) give_pinned(PinBlock{lat->pin, lat->pin_size});
+    if (lat->pin) {
+        const PinBlock b{lat->pin, lat->pin_size};
+        give_pinned(&b);
+    }
     delete lat;
 }
 

@@ -73,6 +73,27 @@ def check_creation_without_staging(host):
         host.L.rlbm_lattice_destroy(h)
 
 
+def check_destroy_frees_no_pinned_memory(host):
+    """A free waits for the whole device: destroying lattices, the last one
+    among them, leaves up to 2 MiB of blocks for the next ones, and the last
+    mechanism gives those back."""
+    for rounds in range(2):
+        hs = [host.lattice(nx) for nx in [64] * 40 + [300] * 8 + [4000]]
+        at = host.stub.stub_frees()
+        for h, _mem, _ in hs:
+            host.L.rlbm_lattice_destroy(h)
+        assert host.stub.stub_frees() == at
+        assert host.stub.stub_pinned() <= 2 << 20
+    hs = [host.lattice(4000) for _ in range(9)]
+    for h, _mem, _ in hs:
+        host.L.rlbm_lattice_destroy(h)
+    assert host.stub.stub_pinned() <= 2 << 20
+    held, _mem, _ = host.lattice(64)
+    host.mech.__del__()
+    host.L.rlbm_lattice_destroy(held)
+    assert host.stub.stub_pinned() == 0
+
+
 CHECKS = {n: f for n, f in list(globals().items()) if n.startswith("check_")}
 
 
