@@ -800,6 +800,21 @@ struct HostFields {
     double* p = nullptr;
     ~HostFields() { std::free(p); }
 };
+// Waits for a stream on every way out of a call whose copies read host memory
+// that ends with it.  Declared after that memory; done() is the wait of the
+// way out without an error.
+struct StreamWait {
+    hipStream_t stream;
+    bool waited = false;
+    explicit StreamWait(hipStream_t s) : stream(s) {}
+    hipError_t done() {
+        waited = true;
+        return hipStreamSynchronize(stream);
+    }
+    ~StreamWait() {
+        if (!waited) (void)hipStreamSynchronize(stream);
+    }
+};
 }  // namespace
 
 int rlbm_set_state(rlbm_lattice* lat, const double* rho, const double* u, const double* T, const double* Y,
@@ -844,6 +859,7 @@ int rlbm_set_state(rlbm_lattice* lat, const double* rho, const double* u, const 
     }
     lat->steps_done = 0;
     lat->host.parity0 = 0;
+    StreamWait wait(lat->stream);
     HIP_TRY(hipMemcpyAsync(lat->d_lat, &lat->host, sizeof(LatDev), hipMemcpyHostToDevice, lat->stream), "upload");
     {
         const int rc = upload_slot_table(lat, slot);
@@ -867,7 +883,7 @@ int rlbm_set_state(rlbm_lattice* lat, const double* rho, const double* u, const 
     HIP_TRY(launch_init(M, lat->storage, lat->host.weak, lat->d_lat, (long long)N, stage, stage + N, stage + 4 * N,
                         stage + 5 * N, lat->stream),
             "init kernel");
-    HIP_TRY(hipStreamSynchronize(lat->stream), "hipStreamSynchronize");
+    HIP_TRY(wait.done(), "hipStreamSynchronize");
     lat->state_set = true;
     return RLBM_OK;
 }

@@ -94,6 +94,21 @@ def check_destroy_frees_no_pinned_memory(host):
     assert host.stub.stub_pinned() == 0
 
 
+def check_failed_set_state_leaves_no_copy_queued(host):
+    """A state whose kernels cannot be launched is refused with no copy from
+    the caller's arrays or the call's own still on its way."""
+    for storage, kernels in (("f64", 1), ("f32dev", 3)):
+        for nx in (64, 5000):
+            h, _mem, case = host.lattice(nx, storage)
+            for n in range(kernels):
+                host.stub.stub_fail_launch(n)
+                assert host.set_state(h, case) == -3, (storage, nx, n)
+                assert host.stub.stub_queued() == 0, (storage, nx, n)
+            host.stub.stub_fail_launch(-1)
+            assert host.set_state(h, case) == 0
+            host.L.rlbm_lattice_destroy(h)
+
+
 CHECKS = {n: f for n, f in list(globals().items()) if n.startswith("check_")}
 
 
