@@ -77,18 +77,21 @@ template <int NL> constexpr int REF_K0 = NL * Q + NL + 1 + Q;
 template <int NL> constexpr int REF_T = NL * Q + NL + 2 + Q;
 
 // Scales s_l of node n in buffer q: the stored species (rss floats per node),
-// and rho, rho E.  A species population written in a step is encoded with the
+// and rho, rho E (fss floats per node).  Buffer par decodes the step's source
+// populations, buffer par ^ 1 encodes what it writes.
+//   Linearly implicit update: the two share a row (rss = fss floats, f and g
+// after the species), and k_local writes the step's own moments to buffer
+// par ^ 1, for k_update.
+//   Explicit update: a species population written in a step is encoded with the
 // zeroth moment its reader had one step earlier, which is known before the
-// step's moments (the species collide in the kernel that forms them); f and g,
-// which collide a kernel later, with the moment of the step itself.  Buffer
-// par of the species scales decodes the step's source populations, buffer
-// par ^ 1 (the previous step's moments) encodes what it writes, and the step's
-// own moments then replace buffer par, for the step after.
+// step's moments (the species collide in the kernel that forms them); the
+// step's own moments then replace buffer par, for the step after.  f and g,
+// which collide a kernel later, take the moment of the step itself (fss = 2).
 __device__ __forceinline__ const RLBM_GLOBAL float* scale_at(const LatDev& L, int q, long long n) {
     return as_global(L.rscale[q]) + (size_t)n * L.rss;
 }
 __device__ __forceinline__ const RLBM_GLOBAL float* fscale_at(const LatDev& L, int q, long long n) {
-    return as_global(L.fscale[q]) + 2 * (size_t)n;
+    return as_global(L.fscale[q]) + (size_t)n * L.fss;
 }
 // the scale of lattice l (wave-uniform; LF: the momentum lattice)
 __device__ __forceinline__ float scale_l(const LatDev& L, int q, long long n, int l, int LF) {
@@ -186,8 +189,9 @@ __device__ __forceinline__ int reader_at(int node, const PullOff& o, int c0, int
     return node + sel3(c0, o.x[2], 0, o.x[0]) + sel3(c1, o.y[2], 0, o.y[0]) + sel3(c2, o.z[2], 0, o.z[0]);
 }
 
-// The NSP species scales of node n in buffer q (FP32 storage), as whole
-// 16-byte loads (rss is a multiple of four floats).
+// The first NSP scales of node n's row in buffer q (FP32 storage), as whole
+// 16-byte loads (rss is a multiple of four floats): the species, or with the
+// linearly implicit update also all NL.
 template <int NSP>
 __device__ __forceinline__ void species_scales(const LatDev& L, int q, int n, float* out) {
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -200,18 +204,20 @@ __device__ __forceinline__ void species_scales(const LatDev& L, int q, int n, fl
             if (4 * v + e < NSP) out[4 * v + e] = w[e];
     }
 }
-// rho and rho E scales of node n in buffer q.
+// rho and rho E scales of node n in buffer q (explicit update).
 __device__ __forceinline__ void flow_scales(const LatDev& L, int q, int n, float* out) {
     typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 v = *reinterpret_cast<const RLBM_GLOBAL f2*>(fscale_at(L, q, n));
+    const f2 v = *(reinterpret_cast<const RLBM_GLOBAL f2*>(as_global(L.fscale[q])) + n);
     out[0] = v.x;
     out[1] = v.y;
 }
-// all NL of them, stored lattices in order
+// all NL of them, stored lattices in order, of either update
 template <int NL>
 __device__ __forceinline__ void scales_of(const LatDev& L, int q, int n, float (&out)[NL]) {
     species_scales<NL - 2>(L, q, n, out);
-    flow_scales(L, q, n, out + NL - 2);
+    const RLBM_GLOBAL float* f = fscale_at(L, q, n);
+    out[NL - 2] = f[0];
+    out[NL - 1] = f[1];
 }
 
 // Stored lattice of species a; a slaved index of M (the weakly coupled
@@ -349,8 +355,9 @@ __device__ __forceinline__ void relax_rates(MechC mc, double T, double P, double
 // u_a - u is written out at once and only rho_a stays in registers.  In FP32
 // deviation storage the sums run over the stored deviations and the
 // reference's own moments are added in closed form (zeroth s_l sum_i G_li,
-// second s_f sum_i G_fi c c, first zero by symmetry); rho and rho E become
-// the scales of the references of the f and g populations written this step.
+// second s_f sum_i G_fi c c, first zero by symmetry); the stored species'
+// rho_a, rho and rho E become the scales of the populations written this step,
+// one row of whole 16-byte stores.
 // The Stefan-Maxwell solve comes last, once the streaming part no longer holds
 // registers.
 template <int M>
@@ -393,7 +400,8 @@ __device__ __forceinline__ S ld_win(const RLBM_GLOBAL S* win, unsigned plane, in
         return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (unsigned)idx * 8u, iw * plane, 0));
 }
 
-// Scales of what is written for f and g this step: the node's rho and rho E.
+// Scales of what is written for f and g this step: the node's rho and rho E
+// (explicit update).
 __device__ __forceinline__ void store_fscale(const LatDev& L, int q, int node, double rho, double rhoE) {
     typedef float f2 __attribute__((ext_vector_type(2)));
     f2 v;
@@ -463,7 +471,6 @@ __device__ __forceinline__ void local_moments(const LatDev& L, int par, int k, i
         rhoE += (double)fs[1] * G[REF_M0<NL> + LG] + sf * G[REF_K0<NL>];
         const double p2 = sf * G[REF_M2<NL>];
         Pd[0] += p2; Pd[1] += p2; Pd[2] += p2;
-        store_fscale(L, par ^ 1, node, rho, rhoE);
     }
     const double inv_rho = 1.0 / rho;
     const double u[3] = {j[0] * inv_rho, j[1] * inv_rho, j[2] * inv_rho};
@@ -523,6 +530,21 @@ __device__ __forceinline__ void local_moments(const LatDev& L, int par, int k, i
     // registers through the loop
 #pragma unroll
     for (int c = 0; c < M; ++c) m.rho_a[c] = ls.ra[c * LOC_T];
+    if constexpr (sizeof(S) == 4) {
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        RLBM_GLOBAL f4* so = reinterpret_cast<RLBM_GLOBAL f4*>(as_global(L.rscale[par ^ 1]) + (size_t)node * L.rss);
+#pragma unroll
+        for (int v = 0; v < (NL + 3) / 4; ++v) {
+            f4 w = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int l = 4 * v + e;
+                if (l < NSP) w[e] = __double2float_rn(ls.ra[(l + (!W && l >= s ? 1 : 0)) * LOC_T]);
+                else if (l < NL) w[e] = __double2float_rn(l == LF ? rho : rhoE);
+            }
+            so[v] = w;
+        }
+    }
     m.rho = rho;
     m.rhoE = rhoE;
 #pragma unroll
@@ -1007,7 +1029,7 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
 #pragma unroll
                 for (int q = 0; q < LPW; ++q) {
                     const int l = WV + UPD_WAVES * q;
-                    w[q] = scale_l(L, par, nd, l < NS ? l : 0, LF);
+                    w[q] = scale_at(L, par, nd)[l < NS ? l : 0];
                 }
             }
 #pragma unroll
@@ -1097,15 +1119,6 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
     }
     __syncthreads();
     if (!valid) return;
-    if constexpr (sizeof(S) == 4) {
-        // every wave has staged this node's own scales: the step's species
-        // densities replace them
-        if (wave == 1) {
-            RLBM_GLOBAL float* so = as_global(L.rscale[par]) + (size_t)node * L.rss;
-#pragma unroll
-            for (int j = 0; j < NSP; ++j) so[j] = __double2float_rn(sp[PRM_SP + 6 * j][lane]);
-        }
-    }
 
     const int GR = prm_grad(M);
     // per-node values used by every velocity are re-read from LDS where they
@@ -1169,7 +1182,7 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
             // consumed after the species work below), issued before the
             // prefetch so that waiting for them leaves the prefetch in flight
             float srd[NS];
-            if constexpr (sizeof(S) == 4) scales_of<NL>(L, par ^ 1, reader_at(node, o, c0, c1, c2), srd);
+            if constexpr (sizeof(S) == 4) species_scales<NL>(L, par ^ 1, reader_at(node, o, c0, c1, c2), srd);
             // prefetch the next velocity of this thread
             S fnx[NL];
             if constexpr (c0 < 1) {
@@ -2449,7 +2462,7 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
     int sstep = 0;
     if constexpr (F32) {
         sbase = l < LF ? as_global(L.rscale[par]) + l : as_global(L.fscale[par]) + (l - LF);
-        sstep = l < LF ? L.rss : 2;
+        sstep = l < LF ? L.rss : L.fss;
         sl = sbase[(size_t)node * sstep];
         sf = fscale_at(L, par, node)[0];
     }
@@ -2502,7 +2515,7 @@ __global__ __launch_bounds__((bc_threads<M, W>())) void k_boundary(
                     });
                 };
                 readers(sl, sbase, sstep, sb);
-                if (energy) readers(sf, as_global(L.fscale[par]), 2, sbf);
+                if (energy) readers(sf, as_global(L.fscale[par]), L.fss, sbf);
             }
             double m0 = 0.0;
             for_q<0>([&](auto ic) {
@@ -2871,7 +2884,8 @@ __global__ __launch_bounds__(256) void k_scale_init(const LatDev* __restrict__ l
     for (int a = 0; a < M; ++a) Y[a] = Y_in[a * N + node];
     for (int l = 0; l < NSP; ++l) {
         const int a = W ? l : l + (l >= s ? 1 : 0);
-        // both buffers: the populations' own, and what the first step encodes with
+        // both buffers: the populations' own, and what the first explicit step
+        // encodes with
         const float v = __double2float_rn(rho * Y_in[a * N + node]);
         L.rscale[0][(size_t)node * L.rss + l] = v;
         L.rscale[1][(size_t)node * L.rss + l] = v;
@@ -2879,7 +2893,9 @@ __global__ __launch_bounds__(256) void k_scale_init(const LatDev* __restrict__ l
     double usq = 0.0;
 #pragma unroll
     for (int dd = 0; dd < 3; ++dd) usq += u_in[dd * N + node] * u_in[dd * N + node];
-    store_fscale(L, L.parity0, (int)node, rho, rho * (mix_U<M>(mc, Y, T_in[node]) + 0.5 * usq));
+    float* f = L.fscale[L.parity0] + (size_t)node * L.fss;
+    f[0] = __double2float_rn(rho);
+    f[1] = __double2float_rn(rho * (mix_U<M>(mc, Y, T_in[node]) + 0.5 * usq));
 }
 
 // Initial populations: the equilibria of the given state, k_update's split

@@ -90,9 +90,10 @@ struct LatDev {
     const int* if_blk;          // [blocks + 1] first interface slot of every boundary block
     double* out_state;          // [5 + M][n_out]: rho, ux, uy, uz, T, Y
     const double* ref;          // reference shapes and their moments (FP32 storage; REF_* in kernels.hip)
-    float* rscale[2];           // [N][rss] reference scales s_l of the species populations in pop[q] (FP32 storage)
-    float* fscale[2];           // [N][2] the same of the momentum and the energy populations (rho, rho E)
-    int rss, pad2;              // floats per node in rscale (the stored species, rounded up to 4)
+    float* rscale[2];           // rows of rss floats per node: reference scales s_l of the species populations (FP32 storage)
+    float* fscale[2];           // rows of fss floats: the same of the momentum and the energy populations (rho, rho E)
+    int rss, fss;               // explicit: the stored species, rounded up to 4, and 2; linearly implicit: one row of all
+                                // stored lattices, rounded up to 4, with fscale = rscale + the stored species
     const double* slotc;        // [M + M * M] R_a and 1/(D_ref m_a m_b) in slot order (slaved species last)
     double rho_in, u_in, T_in, P_inf, sigma;
     double Y_in[MAXM];

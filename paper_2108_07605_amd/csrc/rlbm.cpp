@@ -231,9 +231,16 @@ int check_planes(const rlbm_lattice_desc* d, const Geometry& g) {
     return RLBM_OK;
 }
 
-// Floats per node of a buffer's species scales (FP32 storage): the stored
-// species, rounded up to whole 16-byte loads.
-int scale_stride(int L, int storage) { return storage == RLBM_STORAGE_F32_DEV ? (L - 2 + 3) / 4 * 4 : 0; }
+// Floats per node of a buffer's scales (FP32 storage), rounded up to whole
+// 16-byte loads: the stored species, f and g having two floats of their own, or
+// with the linearly implicit update all stored lattices.  There, k_update reads
+// the 27 readers' scales of one buffer only, and with f and g apart it took an
+// eighth longer where one load holds a row (128x128x64: two species weak 265
+// against 233 us, three strong 270 against 242).
+int scale_stride(int L, int storage, int reaction) {
+    if (storage != RLBM_STORAGE_F32_DEV) return 0;
+    return (L - (reaction == RLBM_REACTION_EXPLICIT ? 2 : 0) + 3) / 4 * 4;
+}
 
 // Reference table of L stored lattices: shapes [L][27], their moments [L], one
 // second moment, the energy lattice's K [27] and its sum; then the shapes once
@@ -270,7 +277,8 @@ Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     p.off_ifblk = take(g.if_blk.size() * sizeof(int));
     p.off_out = take((size_t)(5 + M) * g.n_out * sizeof(double));
     p.off_partial = take(nblocks * (6 + E) * sizeof(double));
-    const size_t rss = (size_t)scale_stride(L, d->storage), fss = d->storage == RLBM_STORAGE_F32_DEV ? 2 : 0;
+    const size_t rss = (size_t)scale_stride(L, d->storage, d->reaction);
+    const size_t fss = d->storage == RLBM_STORAGE_F32_DEV && d->reaction == RLBM_REACTION_EXPLICIT ? 2 : 0;
     p.off_rscale0 = take(rss * N * sizeof(float));
     p.off_rscale1 = take(rss * N * sizeof(float));
     p.off_fscale0 = take(fss * N * sizeof(float));
@@ -648,12 +656,14 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
     h.if_blk = (const int*)(base + p.off_ifblk);
     h.out_state = (double*)(base + p.off_out);
     h.ref = d->storage == RLBM_STORAGE_F32_DEV ? (const double*)(base + p.off_ref) : nullptr;
-    h.rss = scale_stride(lat->L, d->storage);
+    h.rss = scale_stride(lat->L, d->storage, d->reaction);
     if (d->storage == RLBM_STORAGE_F32_DEV) {
+        const bool apart = d->reaction == RLBM_REACTION_EXPLICIT;
+        h.fss = apart ? 2 : h.rss;
         h.rscale[0] = (float*)(base + p.off_rscale0);
         h.rscale[1] = (float*)(base + p.off_rscale1);
-        h.fscale[0] = (float*)(base + p.off_fscale0);
-        h.fscale[1] = (float*)(base + p.off_fscale1);
+        h.fscale[0] = apart ? (float*)(base + p.off_fscale0) : h.rscale[0] + (lat->L - 2);
+        h.fscale[1] = apart ? (float*)(base + p.off_fscale1) : h.rscale[1] + (lat->L - 2);
     }
     const rlbm_face& fi = d->faces[0];
     if (is_inlet(fi.type)) {
@@ -1040,24 +1050,28 @@ struct StateHeader {
     int32_t M, L, storage, slaved, rss, pad;
     int64_t N, n_out;
 };
-// Version 2 holds the species scales of both buffers (the populations' own and
-// those the next step encodes with) and the scales of f and g.  Version 1 held
-// one vector per node (species, rho, rho E; L rounded up to four floats) of
-// the populations' own scales; it is still loaded, and the next step then
-// encodes with those too.
-constexpr uint32_t STATE_VERSION = 2u;
+// Version 1 holds one vector of scales per node (species, rho, rho E; L rounded
+// up to four floats), the populations' own: what the linearly implicit update
+// keeps.  Version 2 holds what the explicit update keeps: the species scales of
+// both buffers (the populations' own and those the next step encodes with),
+// the scales of f and g apart, and the second copy of the reference shapes.  A
+// lattice writes the version of its update and loads both; an explicit step
+// after a version 1 snapshot encodes with the populations' own scales.
 struct StateLayout {
     size_t ref, pops, scale, scale_next, fscale, aux, out, total;
     size_t n_ref, n_pops, n_scale, n_fscale, n_aux, n_out;   // bytes of each section
+    size_t rss;                                              // floats per node in `scale`
 };
-size_t v1_stride(const rlbm_lattice* lat) { return (size_t)(lat->L + 3) / 4 * 4; }
-StateLayout state_layout(const rlbm_lattice* lat, uint32_t version = STATE_VERSION) {
+uint32_t state_version(const rlbm_lattice* lat) { return lat->host.reaction == RLBM_REACTION_EXPLICIT ? 2u : 1u; }
+StateLayout state_layout(const rlbm_lattice* lat, uint32_t version) {
     StateLayout s{};
     const size_t N = (size_t)lat->geo.N, L = (size_t)lat->L, M = (size_t)lat->M;
     const bool f32 = lat->storage == RLBM_STORAGE_F32_DEV;
     s.n_ref = f32 ? (version == 1u ? ref_doubles_v1(lat->L) : ref_doubles(lat->L)) * sizeof(double) : 0;
     s.n_pops = L * Q * (size_t)lat->host.P * (f32 ? 4 : 8);
-    s.n_scale = f32 ? (version == 1u ? v1_stride(lat) : (size_t)lat->host.rss) * N * sizeof(float) : 0;
+    s.rss = (size_t)scale_stride(lat->L, lat->storage,
+                                 version == 1u ? RLBM_REACTION_LINEARLY_IMPLICIT : RLBM_REACTION_EXPLICIT);
+    s.n_scale = s.rss * N * sizeof(float);
     s.n_fscale = f32 && version != 1u ? 2 * N * sizeof(float) : 0;
     s.n_aux = ((size_t)AUX_Y + M + 6) * N * sizeof(double);
     s.n_out = (5 + M) * (size_t)lat->geo.n_out * sizeof(double);
@@ -1076,7 +1090,7 @@ StateLayout state_layout(const rlbm_lattice* lat, uint32_t version = STATE_VERSI
 
 int rlbm_state_bytes(const rlbm_lattice* lat, size_t* bytes) {
     if (!lat || !bytes) return fail(RLBM_EINVAL, "null argument");
-    *bytes = state_layout(lat).total;
+    *bytes = state_layout(lat, state_version(lat)).total;
     return RLBM_OK;
 }
 
@@ -1086,16 +1100,16 @@ int rlbm_save_state(rlbm_lattice* lat, void* buf, int on_device) {
     HIP_TRY(hipSetDevice(lat->device), "hipSetDevice");
     HIP_TRY(hipStreamSynchronize(lat->stream), "hipStreamSynchronize");
     (void)on_device;   // hipMemcpyDefault resolves host or device pointers
-    const StateLayout sl = state_layout(lat);
+    const StateLayout sl = state_layout(lat, state_version(lat));
     const int q = (int)((lat->host.parity0 + lat->steps_done) & 1);
-    StateHeader h{STATE_MAGIC, STATE_VERSION, lat->M, lat->L, lat->storage, lat->host.slaved, lat->host.rss, 0,
+    StateHeader h{STATE_MAGIC, state_version(lat), lat->M, lat->L, lat->storage, lat->host.slaved, (int32_t)sl.rss, 0,
                   lat->geo.N, lat->geo.n_out};
     char* b = (char*)buf;
     HIP_TRY(hipMemcpy(b, &h, sizeof(h), hipMemcpyDefault), "save state");
     if (sl.n_ref) HIP_TRY(hipMemcpy(b + sl.ref, lat->d_ref, sl.n_ref, hipMemcpyDefault), "save state");
     HIP_TRY(hipMemcpy(b + sl.pops, lat->host.pop[q], sl.n_pops, hipMemcpyDefault), "save state");
-    if (sl.n_scale) {
-        HIP_TRY(hipMemcpy(b + sl.scale, lat->host.rscale[q], sl.n_scale, hipMemcpyDefault), "save state");
+    if (sl.n_scale) HIP_TRY(hipMemcpy(b + sl.scale, lat->host.rscale[q], sl.n_scale, hipMemcpyDefault), "save state");
+    if (sl.n_fscale) {
         HIP_TRY(hipMemcpy(b + sl.scale_next, lat->host.rscale[q ^ 1], sl.n_scale, hipMemcpyDefault), "save state");
         HIP_TRY(hipMemcpy(b + sl.fscale, lat->host.fscale[q], sl.n_fscale, hipMemcpyDefault), "save state");
     }
@@ -1112,12 +1126,11 @@ int rlbm_load_state(rlbm_lattice* lat, const void* buf, int on_device) {
     const char* b = (const char*)buf;
     StateHeader h{};
     HIP_TRY(hipMemcpy(&h, b, sizeof(h), hipMemcpyDefault), "load state");
-    if (h.magic != STATE_MAGIC || (h.version != 1u && h.version != STATE_VERSION))
+    if (h.magic != STATE_MAGIC || (h.version != 1u && h.version != 2u))
         return fail(RLBM_EINVAL, "not a lattice state snapshot");
     const StateLayout sl = state_layout(lat, h.version);
-    const int rss = lat->storage != RLBM_STORAGE_F32_DEV ? 0 : (h.version == 1u ? (int)v1_stride(lat) : lat->host.rss);
     if (h.M != lat->M || h.L != lat->L || h.storage != lat->storage || h.N != lat->geo.N ||
-        h.n_out != lat->geo.n_out || h.rss != rss || h.slaved < 0 || h.slaved >= lat->M + lat->host.weak ||
+        h.n_out != lat->geo.n_out || h.rss != (int32_t)sl.rss || h.slaved < 0 || h.slaved >= lat->M + lat->host.weak ||
         (lat->host.weak && h.slaved != lat->M))
         return fail(RLBM_EINVAL, "snapshot taken on a lattice of another shape, species count or storage");
     lat->host.slaved = h.slaved;
@@ -1130,26 +1143,43 @@ int rlbm_load_state(rlbm_lattice* lat, const void* buf, int on_device) {
     }
     const int q = (int)((lat->host.parity0 + lat->steps_done) & 1);
     if (sl.n_ref) HIP_TRY(hipMemcpy(lat->d_ref, b + sl.ref, sl.n_ref, hipMemcpyDefault), "load state");
-    if (sl.n_ref && h.version == 1u)   // the second copy of the shapes: [L][27] to [27][L]
-        for (int l = 0; l < lat->L; ++l)
-            HIP_TRY(hipMemcpy2D(lat->d_ref + ref_doubles_v1(lat->L) + l, (size_t)lat->L * sizeof(double),
-                                lat->d_ref + (size_t)l * Q, sizeof(double), sizeof(double), Q, hipMemcpyDeviceToDevice),
-                    "load state");
-    HIP_TRY(hipMemcpy(lat->host.pop[q], b + sl.pops, sl.n_pops, hipMemcpyDefault), "load state");
-    if (sl.n_scale && h.version == 1u) {
-        // rows of v1_stride floats: the stored species, then rho and rho E
-        const size_t N = (size_t)lat->geo.N, nsp = (size_t)lat->L - 2, row = v1_stride(lat) * sizeof(float);
-        for (int e = 0; e < 2; ++e)
-            HIP_TRY(hipMemcpy2D(lat->host.rscale[e], (size_t)lat->host.rss * sizeof(float), b + sl.scale, row,
-                                nsp * sizeof(float), N, hipMemcpyDefault),
-                    "load state");
-        HIP_TRY(hipMemcpy2D(lat->host.fscale[q], 2 * sizeof(float), b + sl.scale + nsp * sizeof(float), row,
-                            2 * sizeof(float), N, hipMemcpyDefault),
+    if (sl.n_ref && h.version == 1u) {
+        // the second copy of the shapes: [L][27] to [27][L]
+        const size_t L = (size_t)lat->L;
+        std::vector<double> g(L * Q), gt(L * Q);
+        HIP_TRY(hipMemcpy(g.data(), b + sl.ref, g.size() * sizeof(double), hipMemcpyDefault), "load state");
+        for (size_t l = 0; l < L; ++l)
+            for (size_t i = 0; i < (size_t)Q; ++i) gt[i * L + l] = g[l * Q + i];
+        HIP_TRY(hipMemcpy(lat->d_ref + ref_doubles_v1(lat->L), gt.data(), gt.size() * sizeof(double),
+                          hipMemcpyHostToDevice),
                 "load state");
-    } else if (sl.n_scale) {
+    }
+    HIP_TRY(hipMemcpy(lat->host.pop[q], b + sl.pops, sl.n_pops, hipMemcpyDefault), "load state");
+    if (sl.n_scale && h.version == state_version(lat)) {
         HIP_TRY(hipMemcpy(lat->host.rscale[q], b + sl.scale, sl.n_scale, hipMemcpyDefault), "load state");
-        HIP_TRY(hipMemcpy(lat->host.rscale[q ^ 1], b + sl.scale_next, sl.n_scale, hipMemcpyDefault), "load state");
-        HIP_TRY(hipMemcpy(lat->host.fscale[q], b + sl.fscale, sl.n_fscale, hipMemcpyDefault), "load state");
+        if (sl.n_fscale) {
+            HIP_TRY(hipMemcpy(lat->host.rscale[q ^ 1], b + sl.scale_next, sl.n_scale, hipMemcpyDefault), "load state");
+            HIP_TRY(hipMemcpy(lat->host.fscale[q], b + sl.fscale, sl.n_fscale, hipMemcpyDefault), "load state");
+        }
+    } else if (sl.n_scale) {
+        // rows of the other version, through the idle population buffer: the
+        // species to both buffers, rho and rho E from behind them or apart
+        const size_t N = (size_t)lat->geo.N, F = sizeof(float), nsp = (size_t)lat->L - 2;
+        char* stage = (char*)lat->host.pop[q ^ 1];
+        HIP_TRY(hipMemcpy(stage, b + sl.scale, sl.n_scale, hipMemcpyDefault), "load state");
+        for (int e = 0; e < 2; ++e)
+            HIP_TRY(hipMemcpy2D(lat->host.rscale[e], lat->host.rss * F, stage, sl.rss * F, nsp * F, N,
+                                hipMemcpyDeviceToDevice),
+                    "load state");
+        const char* f = stage + nsp * F;
+        size_t frow = sl.rss * F;
+        if (sl.n_fscale) {
+            HIP_TRY(hipMemcpy(stage + sl.n_scale, b + sl.fscale, sl.n_fscale, hipMemcpyDefault), "load state");
+            f = stage + sl.n_scale;
+            frow = 2 * F;
+        }
+        HIP_TRY(hipMemcpy2D(lat->host.fscale[q], lat->host.fss * F, f, frow, 2 * F, N, hipMemcpyDeviceToDevice),
+                "load state");
     }
     HIP_TRY(hipMemcpy(lat->host.aux, b + sl.aux, sl.n_aux, hipMemcpyDefault), "load state");
     if (sl.n_out) HIP_TRY(hipMemcpy(lat->host.out_state, b + sl.out, sl.n_out, hipMemcpyDefault), "load state");

@@ -86,3 +86,82 @@ def test_implicit_snapshot_resumes_bit_exactly(coupling, mech9):
     back.step(3)
     lat.step(3)
     np.testing.assert_array_equal(back.populations(), lat.populations())
+
+
+@pytest.mark.parametrize("coupling", ["strong", "weak"])
+@pytest.mark.parametrize("species", [9, 3, 2])
+def test_snapshots_between_the_updates(species, coupling, mech9):
+    """A lattice takes a snapshot of the other reaction update's lattice (a
+    linearly implicit one keeps one row of scales per node, an explicit one
+    the species' twice and f and g apart): the same populations, the same
+    bits in the next snapshot's, and runs within the storage's precision of
+    the FP64 ones."""
+    rlbm = _rlbm()
+    print(f"case snapshots between updates M={species} {coupling}", flush=True)
+    ex = _case(species, (66, 5, 3), mech9, coupling)
+    im = dict(ex, reaction="implicit")
+    for a, b in ((ex, im), (im, ex)):
+        lat = rlbm.Lattice(a, storage="f32dev").set_state()
+        lat.step(3)
+        other = rlbm.Lattice(b, storage="f32dev").set_state()
+        f64 = rlbm.Lattice(b, storage="f64").set_state()
+        snap = lat.save_state()
+        assert snap[:8].view(np.uint32)[1] == (2 if a is ex else 1)
+        other.load_state(snap)
+        pops = lat.populations()
+        np.testing.assert_array_equal(other.populations(), pops)
+        f64.write_populations(pops)
+        back = rlbm.Lattice(a, storage="f32dev").load_state(other.save_state())
+        np.testing.assert_array_equal(back.populations(), pops)
+        for n in (1, 2):
+            other.step(n)
+            f64.step(n)
+            _fields_close(other, f64, species)
+
+
+def _fields_close(lat, f64, species):
+    a, b = lat.fields(), f64.fields()
+    assert _nerr(a["T"], b["T"]) <= TOL["f32dev"]
+    for s in range(species):
+        assert _nerr(a["Y"][s], b["Y"][s], 1e-6) <= TOL["f32dev"], s
+
+
+@pytest.mark.parametrize("coupling", ["strong", "weak"])
+def test_step_after_written_populations(coupling, mech9):
+    """FP32 storage: populations of a state far from the lattice's own are
+    rounded once when they are written.  The step after encodes with scales of
+    their own size, so its deviations are small and their rounding too; scales
+    left from the old state would round every population a second time as
+    coarsely, an error of sqrt(2) times the first where the other way leaves
+    it as it is.  The line is at the root of that, 2^(1/4)."""
+    rlbm = _rlbm()
+    base = wl.make_case("bbbox", seed=2, mech=mech9, nx=16, ny=8, nz=6, coupling=coupling, reaction="implicit")
+    print(f"case step after written populations {coupling}", flush=True)
+    _after_write(rlbm, base)
+
+
+def _after_write(rlbm, base):
+    rng = np.random.default_rng(5)
+    init = {k: np.array(v, dtype=np.float64) for k, v in base["init"].items()}
+    N = init["rho"].size
+    Y = init["Y"].reshape(9, N)
+    sl = int(np.argmax(Y.mean(1)))
+    base["slaved"] = sl
+    Y = Y * np.exp(0.7 * rng.uniform(-1.0, 1.0, (9, 1))) + 1e-3
+    Y /= Y.sum(0)
+    Y[sl] += 1.0 - Y.sum(0)
+    init.update(Y=Y.reshape(init["Y"].shape), T=1.1 * init["T"], rho=1.2 * init["rho"])
+    pops = rlbm.Lattice(base, storage="f64").set_state(init).populations()
+    f64, f32 = (rlbm.Lattice(base, storage=s).set_state() for s in ("f64", "f32dev"))
+    f64.write_populations(pops)
+    f32.write_populations(pops)
+
+    def err():
+        p, q = f64.populations(), f32.populations()
+        return max(np.sqrt(((p[l] - q[l]) ** 2).mean() / (p[l] ** 2).mean()) for l in range(p.shape[0]))
+
+    first = err()
+    for n in (1, 2):
+        f64.step(1)
+        f32.step(1)
+        assert err() <= 2.0 ** 0.25 * first, n
