@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2108_07605_amd import workloads as wl
+from test_gpu_implicit import _after_write
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +45,37 @@ def test_lattices_are_destroyed_during_a_capture(mech9):
         torch.cuda.synchronize()
         ref.step(2)
         np.testing.assert_array_equal(lat.populations(), ref.populations())
+
+
+@pytest.mark.parametrize("coupling", ["strong", "weak"])
+def test_explicit_step_after_written_populations(coupling, mech9):
+    """FP32 storage, explicit update: the line that the implicit one is held
+    to (test_step_after_written_populations)."""
+    rlbm = _rlbm()
+    base = wl.make_case("bbbox", seed=2, mech=mech9, nx=16, ny=8, nz=6, coupling=coupling)
+    print(f"case explicit step after written populations {coupling}", flush=True)
+    _after_write(rlbm, base)
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("nx", [1, 63, 64, 65, 200])
+def test_written_populations_come_back(nx, storage, mech9):
+    """Tiles of 64 nodes and their remainders, from the host, a lattice at a
+    time, and from the device, after an odd number of steps: FP64 storage the
+    same bits, FP32 storage a rounding of the deviation (half an ulp of FP32,
+    2^-24 of the value it is taken from)."""
+    rlbm = _rlbm()
+    print(f"case written populations nx={nx} {storage}", flush=True)
+    case = wl.make_case("reactor", seed=3, mech=mech9, nx=nx, ny=1, nz=1)
+    lat = rlbm.Lattice(case, storage=storage).set_state()
+    lat.step(1)
+    pops = np.ascontiguousarray(lat.populations()[:, ::-1] * (1.0 + 1e-2 * np.arange(nx)))
+    lat.write_populations(pops)
+    dev = lat.populations()
+    rlbm._check(rlbm.lib().rlbm_write_populations(lat.handle, ctypes.c_void_p(pops.ctypes.data), 0))
+    np.testing.assert_array_equal(lat.populations(), dev)
+    if storage == "f64":
+        np.testing.assert_array_equal(dev, pops)
+    else:
+        scale = np.abs(pops).sum(1, keepdims=True)     # what the reference scales are the sums of
+        assert (np.abs(dev - pops) <= 2.0 ** -24 * scale).all()
