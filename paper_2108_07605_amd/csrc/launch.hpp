@@ -44,6 +44,18 @@ hipError_t launch_fields(int M, int storage, int weak, const LatDev* lat, long l
                          double* u, double* T, double* Y, double* P, int* status, hipStream_t st);
 hipError_t launch_pops(int M, int storage, int weak, const LatDev* lat, long long N, int l0, int nl, long long t,
                        double* buf, int write, hipStream_t st);
+// Runs of rows of 4-byte words, each copied to rows of another step.
+struct PackSeg {
+    const void* src;
+    void* dst;
+    unsigned rows, words, src_step, dst_step;   // rows of `words` words, their starts the steps apart
+};
+constexpr int PACK_SEGS = 6;
+struct Pack {
+    int n;
+    PackSeg seg[PACK_SEGS];
+};
+hipError_t launch_pack(const Pack& p, hipStream_t st);
 hipError_t launch_invariants(int M, int storage, int weak, const LatDev* lat, long long N, long long t,
                              double* partial, int nv, double* out, hipStream_t st);
 // batched steps: advance the device step counter; read and clear k flags

@@ -740,7 +740,7 @@ int rlbm_lattice_shape(const rlbm_lattice* lat, int32_t* L, int64_t* N, int64_t*
 // slaved one (species order in the weakly coupled storage); gas constants R_a
 // and couplings 1/(D_ref m_a m_b) permuted.
 // The caller synchronises before the host vector goes out of scope.
-static int upload_slot_table(rlbm_lattice* lat, std::vector<double>& slot) {
+static int upload_slot_table(rlbm_lattice* lat, std::vector<double>& slot, hipStream_t stream) {
     const int M = lat->M;
     slot.resize((size_t)M + (size_t)M * M);
     const int sl = lat->host.slaved;
@@ -751,7 +751,7 @@ static int upload_slot_table(rlbm_lattice* lat, std::vector<double>& slot) {
         for (int q = 0; q < M; ++q) slot[M + (size_t)j * M + q] = lat->mech.Kab[spc(j)][spc(q)];
     }
     HIP_TRY(hipMemcpyAsync((void*)lat->host.slotc, slot.data(), slot.size() * sizeof(double), hipMemcpyHostToDevice,
-                           lat->stream),
+                           stream),
             "upload");
     return RLBM_OK;
 }
@@ -872,7 +872,7 @@ int rlbm_set_state(rlbm_lattice* lat, const double* rho, const double* u, const 
     StreamWait wait(lat->stream);
     HIP_TRY(hipMemcpyAsync(lat->d_lat, &lat->host, sizeof(LatDev), hipMemcpyHostToDevice, lat->stream), "upload");
     {
-        const int rc = upload_slot_table(lat, slot);
+        const int rc = upload_slot_table(lat, slot, lat->stream);
         if (rc) return rc;
     }
     // device staging for the fields: the second population buffer is idle now
@@ -1094,6 +1094,33 @@ int rlbm_state_bytes(const rlbm_lattice* lat, size_t* bytes) {
     return RLBM_OK;
 }
 
+// The scales, node fields and outlet states of a snapshot, contiguous in it, are
+// packed in the idle population buffer and copied at once where they fit it and
+// are small: with more bytes than this the second pass over them costs more
+// than the copies it saves.
+constexpr size_t PACK_MOST = 32u << 20;
+bool packs(const StateLayout& s) {
+    return s.total - s.scale <= std::min(s.n_pops, PACK_MOST);
+}
+// The sections' places in the lattice, and at `at` of the snapshot, the source
+// of the copies if `save`.
+Pack pack_of(const rlbm_lattice* lat, const StateLayout& s, int q, char* packed, bool save) {
+    Pack p{};
+    auto add = [&](void* mem, size_t at, size_t n) {
+        char* m = packed + (at - s.scale);
+        if (n) p.seg[p.n++] = PackSeg{save ? mem : m, save ? m : mem, (unsigned)(n / 4), 1u, 1u, 1u};
+    };
+    add(lat->host.rscale[q], s.scale, s.n_scale);
+    add(lat->host.rscale[q ^ 1], s.scale_next, s.n_fscale ? s.n_scale : 0);
+    add(lat->host.fscale[q], s.fscale, s.n_fscale);
+    add(lat->host.aux, s.aux, s.n_aux);
+    add(lat->host.out_state, s.out, s.n_out);
+    return p;
+}
+
+// The copies go one behind the other and are waited for once, on the null
+// stream, so that what the caller has queued there on a device buffer comes
+// before.
 int rlbm_save_state(rlbm_lattice* lat, void* buf, int on_device) {
     if (!lat || !buf) return fail(RLBM_EINVAL, "null argument");
     if (!lat->state_set) return fail(RLBM_EINVAL, "rlbm_set_state has not been called");
@@ -1105,16 +1132,27 @@ int rlbm_save_state(rlbm_lattice* lat, void* buf, int on_device) {
     StateHeader h{STATE_MAGIC, state_version(lat), lat->M, lat->L, lat->storage, lat->host.slaved, (int32_t)sl.rss, 0,
                   lat->geo.N, lat->geo.n_out};
     char* b = (char*)buf;
-    HIP_TRY(hipMemcpy(b, &h, sizeof(h), hipMemcpyDefault), "save state");
-    if (sl.n_ref) HIP_TRY(hipMemcpy(b + sl.ref, lat->d_ref, sl.n_ref, hipMemcpyDefault), "save state");
-    HIP_TRY(hipMemcpy(b + sl.pops, lat->host.pop[q], sl.n_pops, hipMemcpyDefault), "save state");
-    if (sl.n_scale) HIP_TRY(hipMemcpy(b + sl.scale, lat->host.rscale[q], sl.n_scale, hipMemcpyDefault), "save state");
-    if (sl.n_fscale) {
-        HIP_TRY(hipMemcpy(b + sl.scale_next, lat->host.rscale[q ^ 1], sl.n_scale, hipMemcpyDefault), "save state");
-        HIP_TRY(hipMemcpy(b + sl.fscale, lat->host.fscale[q], sl.n_fscale, hipMemcpyDefault), "save state");
+    StreamWait wait(nullptr);
+    auto put = [&](size_t at, const void* src, size_t n) {
+        return n ? hipMemcpyAsync(b + at, src, n, hipMemcpyDefault, nullptr) : hipSuccess;
+    };
+    HIP_TRY(put(0, &h, sizeof(h)), "save state");
+    HIP_TRY(put(sl.ref, lat->d_ref, sl.n_ref), "save state");
+    HIP_TRY(put(sl.pops, lat->host.pop[q], sl.n_pops), "save state");
+    if (packs(sl)) {
+        char* packed = (char*)lat->host.pop[q ^ 1];
+        HIP_TRY(launch_pack(pack_of(lat, sl, q, packed, true), nullptr), "save state");
+        HIP_TRY(put(sl.scale, packed, sl.total - sl.scale), "save state");
+    } else {
+        HIP_TRY(put(sl.scale, lat->host.rscale[q], sl.n_scale), "save state");
+        if (sl.n_fscale) {
+            HIP_TRY(put(sl.scale_next, lat->host.rscale[q ^ 1], sl.n_scale), "save state");
+            HIP_TRY(put(sl.fscale, lat->host.fscale[q], sl.n_fscale), "save state");
+        }
+        HIP_TRY(put(sl.aux, lat->host.aux, sl.n_aux), "save state");
+        HIP_TRY(put(sl.out, lat->host.out_state, sl.n_out), "save state");
     }
-    HIP_TRY(hipMemcpy(b + sl.aux, lat->host.aux, sl.n_aux, hipMemcpyDefault), "save state");
-    if (sl.n_out) HIP_TRY(hipMemcpy(b + sl.out, lat->host.out_state, sl.n_out, hipMemcpyDefault), "save state");
+    HIP_TRY(wait.done(), "save state");
     return RLBM_OK;
 }
 
@@ -1134,55 +1172,60 @@ int rlbm_load_state(rlbm_lattice* lat, const void* buf, int on_device) {
         (lat->host.weak && h.slaved != lat->M))
         return fail(RLBM_EINVAL, "snapshot taken on a lattice of another shape, species count or storage");
     lat->host.slaved = h.slaved;
-    HIP_TRY(hipMemcpy(lat->d_lat, &lat->host, sizeof(LatDev), hipMemcpyHostToDevice), "load state");
+    std::vector<double> slot, shapes;
+    StreamWait wait(nullptr);
+    auto get = [&](void* dst, size_t at, size_t n) {
+        return n ? hipMemcpyAsync(dst, b + at, n, hipMemcpyDefault, nullptr) : hipSuccess;
+    };
+    HIP_TRY(hipMemcpyAsync(lat->d_lat, &lat->host, sizeof(LatDev), hipMemcpyHostToDevice, nullptr), "load state");
     {
-        std::vector<double> slot;
-        const int rc = upload_slot_table(lat, slot);
+        const int rc = upload_slot_table(lat, slot, nullptr);
         if (rc) return rc;
-        HIP_TRY(hipStreamSynchronize(lat->stream), "hipStreamSynchronize");
     }
     const int q = (int)((lat->host.parity0 + lat->steps_done) & 1);
-    if (sl.n_ref) HIP_TRY(hipMemcpy(lat->d_ref, b + sl.ref, sl.n_ref, hipMemcpyDefault), "load state");
-    if (sl.n_ref && h.version == 1u) {
+    HIP_TRY(get(lat->d_ref, sl.ref, sl.n_ref), "load state");
+    if (sl.n_ref && h.version == 1u && state_version(lat) != 1u) {
         // the second copy of the shapes: [L][27] to [27][L]
         const size_t L = (size_t)lat->L;
-        std::vector<double> g(L * Q), gt(L * Q);
+        std::vector<double> g(L * Q);
         HIP_TRY(hipMemcpy(g.data(), b + sl.ref, g.size() * sizeof(double), hipMemcpyDefault), "load state");
+        shapes.resize(L * Q);
         for (size_t l = 0; l < L; ++l)
-            for (size_t i = 0; i < (size_t)Q; ++i) gt[i * L + l] = g[l * Q + i];
-        HIP_TRY(hipMemcpy(lat->d_ref + ref_doubles_v1(lat->L), gt.data(), gt.size() * sizeof(double),
-                          hipMemcpyHostToDevice),
+            for (size_t i = 0; i < (size_t)Q; ++i) shapes[i * L + l] = g[l * Q + i];
+        HIP_TRY(hipMemcpyAsync(lat->d_ref + ref_doubles_v1(lat->L), shapes.data(), shapes.size() * sizeof(double),
+                               hipMemcpyHostToDevice, nullptr),
                 "load state");
     }
-    HIP_TRY(hipMemcpy(lat->host.pop[q], b + sl.pops, sl.n_pops, hipMemcpyDefault), "load state");
-    if (sl.n_scale && h.version == state_version(lat)) {
-        HIP_TRY(hipMemcpy(lat->host.rscale[q], b + sl.scale, sl.n_scale, hipMemcpyDefault), "load state");
-        if (sl.n_fscale) {
-            HIP_TRY(hipMemcpy(lat->host.rscale[q ^ 1], b + sl.scale_next, sl.n_scale, hipMemcpyDefault), "load state");
-            HIP_TRY(hipMemcpy(lat->host.fscale[q], b + sl.fscale, sl.n_fscale, hipMemcpyDefault), "load state");
+    HIP_TRY(get(lat->host.pop[q], sl.pops, sl.n_pops), "load state");
+    char* stage = (char*)lat->host.pop[q ^ 1];
+    const bool same = !sl.n_scale || h.version == state_version(lat);
+    if (same && packs(sl)) {
+        HIP_TRY(get(stage, sl.scale, sl.total - sl.scale), "load state");
+        HIP_TRY(launch_pack(pack_of(lat, sl, q, stage, false), nullptr), "load state");
+    } else {
+        if (same) {
+            HIP_TRY(get(lat->host.rscale[q], sl.scale, sl.n_scale), "load state");
+            if (sl.n_fscale) {
+                HIP_TRY(get(lat->host.rscale[q ^ 1], sl.scale_next, sl.n_scale), "load state");
+                HIP_TRY(get(lat->host.fscale[q], sl.fscale, sl.n_fscale), "load state");
+            }
+        } else {
+            // rows of the other version: the species to both buffers, rho and
+            // rho E from behind them or apart
+            const unsigned N = (unsigned)lat->geo.N, nsp = (unsigned)(lat->L - 2), row = (unsigned)sl.rss;
+            const unsigned rss = (unsigned)lat->host.rss, fss = (unsigned)lat->host.fss;
+            float *sc = (float*)stage, *f = sc + (sl.n_fscale ? sl.n_scale / sizeof(float) : nsp);
+            HIP_TRY(get(sc, sl.scale, sl.n_scale), "load state");
+            HIP_TRY(get(f, sl.fscale, sl.n_fscale), "load state");
+            Pack p{};
+            for (int e = 0; e < 2; ++e) p.seg[p.n++] = PackSeg{sc, lat->host.rscale[e], N, nsp, row, rss};
+            p.seg[p.n++] = PackSeg{f, lat->host.fscale[q], N, 2u, sl.n_fscale ? 2u : row, fss};
+            HIP_TRY(launch_pack(p, nullptr), "load state");
         }
-    } else if (sl.n_scale) {
-        // rows of the other version, through the idle population buffer: the
-        // species to both buffers, rho and rho E from behind them or apart
-        const size_t N = (size_t)lat->geo.N, F = sizeof(float), nsp = (size_t)lat->L - 2;
-        char* stage = (char*)lat->host.pop[q ^ 1];
-        HIP_TRY(hipMemcpy(stage, b + sl.scale, sl.n_scale, hipMemcpyDefault), "load state");
-        for (int e = 0; e < 2; ++e)
-            HIP_TRY(hipMemcpy2D(lat->host.rscale[e], lat->host.rss * F, stage, sl.rss * F, nsp * F, N,
-                                hipMemcpyDeviceToDevice),
-                    "load state");
-        const char* f = stage + nsp * F;
-        size_t frow = sl.rss * F;
-        if (sl.n_fscale) {
-            HIP_TRY(hipMemcpy(stage + sl.n_scale, b + sl.fscale, sl.n_fscale, hipMemcpyDefault), "load state");
-            f = stage + sl.n_scale;
-            frow = 2 * F;
-        }
-        HIP_TRY(hipMemcpy2D(lat->host.fscale[q], lat->host.fss * F, f, frow, 2 * F, N, hipMemcpyDeviceToDevice),
-                "load state");
+        HIP_TRY(get(lat->host.aux, sl.aux, sl.n_aux), "load state");
+        HIP_TRY(get(lat->host.out_state, sl.out, sl.n_out), "load state");
     }
-    HIP_TRY(hipMemcpy(lat->host.aux, b + sl.aux, sl.n_aux, hipMemcpyDefault), "load state");
-    if (sl.n_out) HIP_TRY(hipMemcpy(lat->host.out_state, b + sl.out, sl.n_out, hipMemcpyDefault), "load state");
+    HIP_TRY(wait.done(), "load state");
     lat->state_set = true;
     return RLBM_OK;
 }

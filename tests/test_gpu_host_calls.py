@@ -79,3 +79,37 @@ def test_written_populations_come_back(nx, storage, mech9):
     else:
         scale = np.abs(pops).sum(1, keepdims=True)     # what the reference scales are the sums of
         assert (np.abs(dev - pops) <= 2.0 ** -24 * scale).all()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+@pytest.mark.parametrize("kind,dims,kw", [
+    ("reactor", (1, 1, 1), {}), ("reactor", (7, 1, 1), {}), ("channel3d", (9, 7, 5), {}),      # sections apart, or packed
+    ("channel3d", (9, 7, 5), dict(coupling="weak")), ("channel3d", (9, 7, 5), dict(reaction="implicit")),
+    ("channel2d", (1030, 150, 1), {})])                                                        # beyond the packed size
+def test_snapshots_to_host_and_device(kind, dims, kw, storage, mech9):
+    """Snapshots taken after even and odd numbers of steps, to the host and to
+    the device, resume in another lattice (its buffers the other way round) to
+    the same bits."""
+    rlbm = _rlbm()
+    import torch
+    print(f"case snapshots {kind} {dims} {kw} {storage}", flush=True)
+    case = wl.make_case(kind, seed=4, nx=dims[0], ny=dims[1], nz=dims[2], mech=mech9, **kw)
+    m = rlbm.Mechanism(mech9)
+    lat, back, dev = (rlbm.Lattice(case, storage=storage, mech=m).set_state() for _ in range(3))
+    size = lat.save_state().size
+    for n in (0, 1, 2):
+        lat.step(n)
+        host = lat.save_state()
+        buf = torch.empty(size, dtype=torch.uint8, device="cuda")
+        rlbm._check(rlbm.lib().rlbm_save_state(lat.handle, ctypes.c_void_p(buf.data_ptr()), 1))
+        back.load_state(host)
+        rlbm._check(rlbm.lib().rlbm_load_state(dev.handle, ctypes.c_void_p(buf.data_ptr()), 1))
+        pops = lat.populations()
+        for other in (back, dev):
+            np.testing.assert_array_equal(other.populations(), pops)
+            other.step(1)
+        lat.step(1)
+        pops = lat.populations()
+        for other in (back, dev):
+            np.testing.assert_array_equal(other.populations(), pops)
+            np.testing.assert_array_equal(other.fields()["T"], lat.fields()["T"])

@@ -109,6 +109,26 @@ def check_failed_set_state_leaves_no_copy_queued(host):
             host.L.rlbm_lattice_destroy(h)
 
 
+def check_snapshots_wait_once(host):
+    """Saving and loading a snapshot queue their copies and wait for them at
+    the end (and for the lattice's own work, and a loaded header), however
+    many sections there are."""
+    for storage in ("f64", "f32dev"):
+        for kw in ({}, {"reaction": "implicit"}):
+            for nx in (4, 100):     # copied section by section, and packed
+                h, _mem, case = host.lattice(nx, storage, **kw)
+                assert host.set_state(h, case) == 0
+                n = ctypes.c_size_t()
+                host.rlbm._check(host.L.rlbm_state_bytes(h, ctypes.byref(n)))
+                a = np.zeros(n.value, np.uint8)
+                for f, most in ((host.L.rlbm_save_state, 2), (host.L.rlbm_load_state, 3)):
+                    at = host.stub.stub_waits()
+                    host.rlbm._check(f(h, a.ctypes.data, 0))
+                    assert host.stub.stub_waits() - at <= most, (storage, kw, nx)
+                    assert host.stub.stub_queued() == 0
+                host.L.rlbm_lattice_destroy(h)
+
+
 CHECKS = {n: f for n, f in list(globals().items()) if n.startswith("check_")}
 
 
