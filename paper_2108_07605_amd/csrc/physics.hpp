@@ -80,7 +80,7 @@ struct LatDev {
                                 // step reads holds interface node k's post-boundary population (written by the
                                 // boundary kernel of that step)
     double* aux;                // [14 + M][N]: rho, ux, uy, uz, T, Phi_x,y,z, Y_0..Y_{M-1}, P_0..P_5
-    double* prm;                // [14 + 6 M + 6][N] per-node record for k_update
+    double* prm;                // [prm_rows][N] per-node record for k_flow or k_update
     const int* if_index;        // [N]: interface slot or -1 (NULL if n_if == 0)
     const int* if_node;         // [n_if]
     const unsigned* if_mask;    // [n_if] incoming set D as a 27-bit mask
@@ -105,17 +105,22 @@ struct LatDev {
 
 constexpr int AUX_RHO = 0, AUX_U = 1, AUX_T = 4, AUX_PHI = 5, AUX_Y = 8;
 
-// Per-node record written by k_local (the reaction increment also by
-// k_chem_implicit, the gradients by k_gradients) for k_update (structure of
-// arrays, row r of node n at prm[r * N + n]).  The rows PRM_TH, PRM_OMEGA,
-// PRM_COMMON, PRM_WQ, PRM_CC and the beta_a rows are not stored: k_update
-// derives them once per node and keeps them in its LDS copy of the record.
+// Per-node record (structure of arrays, row r of node n at prm[r * N + n]).
+//   Explicit update: rows up to PRM_QB + 2 only, written by k_species for
+// k_flow: rho, u, U, theta, omega, omega_1 and the energy flux base (PRM_T is
+// not used).
+//   Linearly implicit update: every row, written by k_local (the reaction
+// increment and the gradients by k_chem_implicit) for k_update.  The rows
+// PRM_TH, PRM_OMEGA, PRM_COMMON, PRM_WQ, PRM_CC and the beta_a rows are not
+// stored: k_update derives them once per node and keeps them in its LDS copy
+// of the record.
 constexpr int PRM_RHO = 0, PRM_U = 1, PRM_T = 4, PRM_UINT = 5, PRM_TH = 6, PRM_OMEGA = 7, PRM_COMMON = 8,
               PRM_QB = 9, PRM_WQ = 12, PRM_CC = 13, PRM_SP = 14;
 constexpr int PRM_OMEGA1 = PRM_COMMON;   // the row holds omega_1 in the record that k_flow reads
 // species rows: PRM_SP + 6 a + {0: rho_a, 1..3: V_a, 4: beta_a, 5: drho_a}
 __host__ __device__ constexpr int prm_grad(int M) { return PRM_SP + 6 * M; }   // d (3), sum H grad Y (3)
 __host__ __device__ constexpr int prm_rows(int M) { return PRM_SP + 6 * M + 6; }
+constexpr int PRM_ROWS_EXPLICIT = PRM_QB + 3;
 // Correction rows: the energy flux base, the diffusion velocities V_a, the
 // reaction increments drho_a and the gradients.  They enter the collision as
 // small additive terms, so in FP32 deviation storage they are kept as FP32

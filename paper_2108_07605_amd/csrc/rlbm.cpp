@@ -267,7 +267,8 @@ Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     p.off_pop0 = take((size_t)L * Q * P * s);
     p.off_pop1 = take((size_t)L * Q * P * s);
     p.off_aux = take((size_t)(AUX_Y + M + 6) * N * sizeof(double));
-    p.off_prm = take((size_t)prm_rows(M) * N * sizeof(double));
+    const int rows = d->reaction == RLBM_REACTION_EXPLICIT ? PRM_ROWS_EXPLICIT : prm_rows(M);
+    p.off_prm = take((size_t)rows * N * sizeof(double));
     p.off_ifindex = take(nif ? N * sizeof(int) : 0);
     p.off_ifnode = take(nif * sizeof(int));
     p.off_ifmask = take(nif * sizeof(unsigned));

@@ -151,3 +151,16 @@ def test_inlet_composition_must_sum_to_one(mech9):
     with pytest.raises(rlbm.RlbmError) as e:
         rlbm.lattice_bytes(case, m, "f64")
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32dev"])
+def test_record_of_the_explicit_update(mech9, storage):
+    """The explicit step hands on 12 rows of doubles per node, the linearly
+    implicit one 14 + 6 M + 6: a lattice is charged for its own."""
+    m = rlbm.Mechanism(mech9)
+    kw = dict(nx=64, ny=16, nz=1, mech=mech9)
+    ex = rlbm.lattice_bytes(wl.make_case("channel2d", **kw), m, storage)
+    im = rlbm.lattice_bytes(wl.make_case("channel2d", reaction="implicit", **kw), m, storage)
+    N = 64 * 16
+    scales = 2 * 4 * N * ((8 + 2) - 12) if storage == "f32dev" else 0   # explicit: 8 + 2 floats twice, implicit: 12
+    assert abs(im - ex - ((14 + 6 * 9 + 6 - 12) * 8 * N - scales)) <= 8 * 256
