@@ -367,19 +367,7 @@ struct LocalMoments {
     double rho_a[M];
 };
 
-
-// Buffer-resource load: a wave-uniform base (scalar registers) plus a 32-bit
-// per-lane byte offset (node counts are limited so that idx * sizeof(S) fits).
-// An offset at or beyond nbytes reads zero instead of leaving the buffer.
-template <typename S>
-__device__ __forceinline__ S ldb(const RLBM_GLOBAL S* base, unsigned nbytes, int idx) {
-    const __amdgpu_buffer_rsrc_t r =
-        __builtin_amdgcn_make_buffer_rsrc((void*)(unsigned long long)base, 0, (int)nbytes, 0x00020000);
-    if constexpr (sizeof(S) == 4)
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (unsigned)idx * 4u, 0, 0));
-    else
-        return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (unsigned)idx * 8u, 0, 0));
-}
+// Bytes of a population plane.
 __device__ __forceinline__ unsigned plane_bytes(long long N, int s) {
     const unsigned long long b = (unsigned long long)N * (unsigned)s;
     return b > 0xffffffffull ? 0xffffffffu : (unsigned)b;
@@ -388,8 +376,8 @@ __device__ __forceinline__ unsigned plane_bytes(long long N, int s) {
 // Population loads through one resource per window of nine planes (the nine
 // velocities of one c_z layer of one lattice): the plane within the window is
 // a scalar offset, the node a per-lane offset.  Few resources stay live, so
-// the scalar registers do not run out.  The host keeps 9 N sizeof(S) below
-// 2^32.
+// the scalar registers do not run out.  The host keeps nine planes below 2^32
+// bytes.
 template <typename S>
 __device__ __forceinline__ S ld_win(const RLBM_GLOBAL S* win, unsigned plane, int iw, int idx) {
     const __amdgpu_buffer_rsrc_t r =
@@ -1288,8 +1276,8 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
 // node: temperature, relaxation rates, Stefan-Maxwell system.  The reactions
 // are dealt to the first three waves.
 //   Bound: FP64 issue and its latency (two waves per SIMD; about 15,000 vector
-// instructions per tile, which the SIMDs issue 55% of the time) in FP32
-// storage, those and the traffic in FP64: 2.1 and 4.1 KB per node, against
+// instructions per tile, which keep the SIMDs issuing 48% of the time at 2.4
+// GHz) in FP32 storage, those and the traffic in FP64: 2.1 and 4.1 KB per node, against
 // 4.0 and 7.5 for a moments pass and a collision that each read every
 // population.  Three waves hold what one cannot, 216 registers of populations
 // per node (FP32) beside the collision's working set, and they divide the
@@ -1923,7 +1911,7 @@ __device__ __forceinline__ void node_solve(const LatDev& L, int par, int lane, i
 }
 
 template <int M, typename S, int W>
-__global__ __launch_bounds__(SPC_THREADS) __attribute__((amdgpu_waves_per_eu(M > 4 && sizeof(S) == 8 ? 2 : 2))) void k_species(
+__global__ __launch_bounds__(SPC_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_species(
     const LatDev* __restrict__ lats, const int* __restrict__ blk, int n_lat, const long long* __restrict__ tp, long long toff) {
     __shared__ double sp[SpcRows<M, W>::N][SPC_NODES];
     const long long t = step_time(tp, toff);
@@ -2250,9 +2238,6 @@ __global__ __launch_bounds__(FLOW_THREADS) __attribute__((amdgpu_waves_per_eu(3)
     }
 }
 
-// ---------------------------------------------------------------------------
-// boundary reconstruction (section 4)
-// ---------------------------------------------------------------------------
 // ---------------------------------------------------------------------------
 // k_boundary: reconstruction at interface nodes (section 4).  A block takes
 // up to 64 consecutive entries of the interface list (grouped by boundary type

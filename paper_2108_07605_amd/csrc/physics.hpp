@@ -22,9 +22,6 @@ constexpr int MAXO = RLBM_MAX_ORDER;   // molecules per side of a reaction
 __host__ __device__ constexpr int cx_of(int i) { return i % 3 - 1; }
 __host__ __device__ constexpr int cy_of(int i) { return (i / 3) % 3 - 1; }
 __host__ __device__ constexpr int cz_of(int i) { return i / 9 - 1; }
-__host__ __device__ constexpr int c2_of(int i) {
-    return cx_of(i) * cx_of(i) + cy_of(i) * cy_of(i) + cz_of(i) * cz_of(i);
-}
 
 // One reaction: Arrhenius parameters, reversibility, each side as a list of
 // factors (its species in ascending order, each repeated by its coefficient:
@@ -214,7 +211,8 @@ __device__ __forceinline__ void geq_axis(double u, double th, GeqAxis& a) {
 
 // 1/x to within an ulp: the hardware estimate and two Newton steps (8 cycles
 // each of a wave's issue time, 32 in all, where the IEEE division with its
-// scaling takes 60).  For normal x away from overflow; 1/0 gives NaN.
+// scaling takes 60).  For normal x away from overflow; zero and infinity, which
+// only non-physical states have, give NaN.
 __device__ __forceinline__ double recip(double x) {
     double r = __builtin_amdgcn_rcp(x);
     r = fma(fma(-x, r, 1.0), r, r);

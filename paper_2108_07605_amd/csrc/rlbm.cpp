@@ -41,7 +41,9 @@ int hip_fail(hipError_t e, const char* what) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-constexpr int NPHASE = 4;   // boundary, moments + diffusion, chemistry + gradients, update
+// Launch phases of a step.  Explicit update: k_boundary, k_species, none, k_flow;
+// linearly implicit: k_boundary, k_local, k_chem_implicit, k_update.
+constexpr int NPHASE = 4;
 
 struct Plan {
     size_t off_lat, off_mech, off_blk, off_flag, off_ref, off_pop0, off_pop1, off_aux, off_prm, off_ifindex, off_ifnode,
@@ -914,7 +916,7 @@ static int step_one(rlbm_lattice* lat, long long t) {
         a.stream = lat->stream;
         a.schemes = 1u << lat->host.reaction;
         if (a.blocks == 0) continue;
-        if (phase == 2 && lat->host.reaction == RLBM_REACTION_EXPLICIT) continue;   // the update takes the gradients
+        if (phase == 2 && lat->host.reaction == RLBM_REACTION_EXPLICIT) continue;   // k_flow takes the gradients
         Timing* ev = nullptr;
         if (lat->timing >> phase & 1u) {
             if (lat->n_events == lat->events.size()) {

@@ -24,7 +24,10 @@ _FACE_CODES = {"periodic": FACE_PERIODIC, "wall": FACE_WALL, "inlet": FACE_INLET
                "outlet": FACE_OUTLET, "bounceback": FACE_BOUNCEBACK, "inlet_local": FACE_INLET_LOCAL}
 _STORAGE = {"f64": STORAGE_F64, "f32dev": STORAGE_F32_DEV}
 _REACTION = {"explicit": REACTION_EXPLICIT, "implicit": REACTION_LINEARLY_IMPLICIT}
-# kernels of one step, in launch order (rlbm_kernel_times)
+# kernels of one step, in launch order (rlbm_kernel_times): k_boundary; k_species
+# ("local") and k_flow ("update") of the explicit update, which launches nothing
+# between them; k_local, k_chem_implicit ("gradients") and k_update of the
+# linearly implicit one
 KERNELS = ("boundary", "local", "gradients", "update")
 
 EXPORTS = (
