@@ -63,6 +63,9 @@ struct Lat {
     static constexpr int LF = NSP;
     static constexpr int LG = NSP + 1;
     static constexpr int NL = NSP + 2;
+    // linearly implicit update, FP32 storage: the scales of f and g fill up the
+    // species' row
+    static constexpr bool ROW = (NL + 3) / 4 == (NSP + 3) / 4;
 };
 
 // Layout of the reference table for NL stored lattices: shapes G[NL][Q] (the
@@ -79,9 +82,9 @@ template <int NL> constexpr int REF_T = NL * Q + NL + 2 + Q;
 // Scales s_l of node n in buffer q: the stored species (rss floats per node),
 // and rho, rho E (fss floats per node).  Buffer par decodes the step's source
 // populations, buffer par ^ 1 encodes what it writes.
-//   Linearly implicit update: the two share a row (rss = fss floats, f and g
-// after the species), and k_local writes the step's own moments to buffer
-// par ^ 1, for k_update.
+//   Linearly implicit update: k_local writes the step's own moments to buffer
+// par ^ 1, for k_update.  Where the species leave two floats of their row free
+// (Lat::ROW), f and g take them (rss = fss).
 //   Explicit update: a species population written in a step is encoded with the
 // zeroth moment its reader had one step earlier, which is known before the
 // step's moments (the species collide in the kernel that forms them); the
@@ -190,8 +193,7 @@ __device__ __forceinline__ int reader_at(int node, const PullOff& o, int c0, int
 }
 
 // The first NSP scales of node n's row in buffer q (FP32 storage), as whole
-// 16-byte loads (rss is a multiple of four floats): the species, or with the
-// linearly implicit update also all NL.
+// 16-byte loads (rss is a multiple of four floats).
 template <int NSP>
 __device__ __forceinline__ void species_scales(const LatDev& L, int q, int n, float* out) {
     typedef float f4 __attribute__((ext_vector_type(4)));
@@ -204,7 +206,7 @@ __device__ __forceinline__ void species_scales(const LatDev& L, int q, int n, fl
             if (4 * v + e < NSP) out[4 * v + e] = w[e];
     }
 }
-// rho and rho E scales of node n in buffer q (explicit update).
+// rho and rho E scales of node n in buffer q, in rows of two floats.
 __device__ __forceinline__ void flow_scales(const LatDev& L, int q, int n, float* out) {
     typedef float f2 __attribute__((ext_vector_type(2)));
     const f2 v = *(reinterpret_cast<const RLBM_GLOBAL f2*>(as_global(L.fscale[q])) + n);
@@ -357,7 +359,7 @@ __device__ __forceinline__ void relax_rates(MechC mc, double T, double P, double
 // reference's own moments are added in closed form (zeroth s_l sum_i G_li,
 // second s_f sum_i G_fi c c, first zero by symmetry); the stored species'
 // rho_a, rho and rho E become the scales of the populations written this step,
-// one row of whole 16-byte stores.
+// in whole 16-byte stores.
 // The Stefan-Maxwell solve comes last, once the streaming part no longer holds
 // registers.
 template <int M>
@@ -389,7 +391,7 @@ __device__ __forceinline__ S ld_win(const RLBM_GLOBAL S* win, unsigned plane, in
 }
 
 // Scales of what is written for f and g this step: the node's rho and rho E
-// (explicit update).
+// (rows of two floats).
 __device__ __forceinline__ void store_fscale(const LatDev& L, int q, int node, double rho, double rhoE) {
     typedef float f2 __attribute__((ext_vector_type(2)));
     f2 v;
@@ -522,16 +524,17 @@ __device__ __forceinline__ void local_moments(const LatDev& L, int par, int k, i
         typedef float f4 __attribute__((ext_vector_type(4)));
         RLBM_GLOBAL f4* so = reinterpret_cast<RLBM_GLOBAL f4*>(as_global(L.rscale[par ^ 1]) + (size_t)node * L.rss);
 #pragma unroll
-        for (int v = 0; v < (NL + 3) / 4; ++v) {
+        for (int v = 0; v < (NSP + 3) / 4; ++v) {
             f4 w = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int l = 4 * v + e;
                 if (l < NSP) w[e] = __double2float_rn(ls.ra[(l + (!W && l >= s ? 1 : 0)) * LOC_T]);
-                else if (l < NL) w[e] = __double2float_rn(l == LF ? rho : rhoE);
+                else if (Lat<M, W>::ROW && l < NL) w[e] = __double2float_rn(l == LF ? rho : rhoE);
             }
             so[v] = w;
         }
+        if constexpr (!Lat<M, W>::ROW) store_fscale(L, par ^ 1, node, rho, rhoE);
     }
     m.rho = rho;
     m.rhoE = rhoE;
@@ -1017,7 +1020,7 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
 #pragma unroll
                 for (int q = 0; q < LPW; ++q) {
                     const int l = WV + UPD_WAVES * q;
-                    w[q] = scale_at(L, par, nd)[l < NS ? l : 0];
+                    w[q] = scale_l(L, par, nd, l < NS ? l : 0, LF);
                 }
             }
 #pragma unroll
@@ -1170,7 +1173,14 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
             // consumed after the species work below), issued before the
             // prefetch so that waiting for them leaves the prefetch in flight
             float srd[NS];
-            if constexpr (sizeof(S) == 4) species_scales<NL>(L, par ^ 1, reader_at(node, o, c0, c1, c2), srd);
+            if constexpr (sizeof(S) == 4) {
+                const int rd = reader_at(node, o, c0, c1, c2);
+                if constexpr (Lat<M, W>::ROW) species_scales<NL>(L, par ^ 1, rd, srd);
+                else {
+                    species_scales<NSP>(L, par ^ 1, rd, srd);
+                    flow_scales(L, par ^ 1, rd, srd + NSP);
+                }
+            }
             // prefetch the next velocity of this thread
             S fnx[NL];
             if constexpr (c0 < 1) {

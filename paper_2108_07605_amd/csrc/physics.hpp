@@ -89,8 +89,8 @@ struct LatDev {
     const double* ref;          // reference shapes and their moments (FP32 storage; REF_* in kernels.hip)
     float* rscale[2];           // rows of rss floats per node: reference scales s_l of the species populations (FP32 storage)
     float* fscale[2];           // rows of fss floats: the same of the momentum and the energy populations (rho, rho E)
-    int rss, fss;               // explicit: the stored species, rounded up to 4, and 2; linearly implicit: one row of all
-                                // stored lattices, rounded up to 4, with fscale = rscale + the stored species
+    int rss, fss;               // the stored species, rounded up to 4, and 2; linearly implicit, where two floats of the
+                                // species' row are free: fss = rss and fscale = rscale + the stored species
     const double* slotc;        // [M + M * M] R_a and 1/(D_ref m_a m_b) in slot order (slaved species last)
     double rho_in, u_in, T_in, P_inf, sigma;
     double Y_in[MAXM];

@@ -233,15 +233,17 @@ int check_planes(const rlbm_lattice_desc* d, const Geometry& g) {
     return RLBM_OK;
 }
 
-// Floats per node of a buffer's scales (FP32 storage), rounded up to whole
-// 16-byte loads: the stored species, f and g having two floats of their own, or
-// with the linearly implicit update all stored lattices.  There, k_update reads
-// the 27 readers' scales of one buffer only, and with f and g apart it took an
-// eighth longer where one load holds a row (128x128x64: two species weak 265
-// against 233 us, three strong 270 against 242).
-int scale_stride(int L, int storage, int reaction) {
-    if (storage != RLBM_STORAGE_F32_DEV) return 0;
-    return (L - (reaction == RLBM_REACTION_EXPLICIT ? 2 : 0) + 3) / 4 * 4;
+// Floats per node of a buffer's species scales (FP32 storage): the stored
+// species, rounded up to whole 16-byte loads.
+int scale_stride(int L) { return (L - 2 + 3) / 4 * 4; }
+// The scales of f and g in the rest of the species' row: with the linearly
+// implicit update, whose k_update reads the 27 readers' scales of both, where
+// they fit.  Apart they are a load more: 128x128x64, two species weak 265
+// against 231 us, three strong 270 against 239.  Where they do not fit, a row
+// for all would be the longer one: nine species strong, 150x31x29, 101.5
+// against 99 us.
+bool flow_in_row(int L, int reaction) {
+    return reaction == RLBM_REACTION_LINEARLY_IMPLICIT && (L + 3) / 4 * 4 == scale_stride(L);
 }
 
 // Reference table of L stored lattices: shapes [L][27], their moments [L], one
@@ -280,8 +282,8 @@ Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     p.off_ifblk = take(g.if_blk.size() * sizeof(int));
     p.off_out = take((size_t)(5 + M) * g.n_out * sizeof(double));
     p.off_partial = take(nblocks * (6 + E) * sizeof(double));
-    const size_t rss = (size_t)scale_stride(L, d->storage, d->reaction);
-    const size_t fss = d->storage == RLBM_STORAGE_F32_DEV && d->reaction == RLBM_REACTION_EXPLICIT ? 2 : 0;
+    const bool f32 = d->storage == RLBM_STORAGE_F32_DEV;
+    const size_t rss = f32 ? (size_t)scale_stride(L) : 0, fss = f32 && !flow_in_row(L, d->reaction) ? 2 : 0;
     p.off_rscale0 = take(rss * N * sizeof(float));
     p.off_rscale1 = take(rss * N * sizeof(float));
     p.off_fscale0 = take(fss * N * sizeof(float));
@@ -659,14 +661,14 @@ int rlbm_lattice_create(const rlbm_lattice_desc* d, const rlbm_mech* mech, void*
     h.if_blk = (const int*)(base + p.off_ifblk);
     h.out_state = (double*)(base + p.off_out);
     h.ref = d->storage == RLBM_STORAGE_F32_DEV ? (const double*)(base + p.off_ref) : nullptr;
-    h.rss = scale_stride(lat->L, d->storage, d->reaction);
     if (d->storage == RLBM_STORAGE_F32_DEV) {
-        const bool apart = d->reaction == RLBM_REACTION_EXPLICIT;
-        h.fss = apart ? 2 : h.rss;
+        const bool row = flow_in_row(lat->L, d->reaction);
+        h.rss = scale_stride(lat->L);
+        h.fss = row ? h.rss : 2;
         h.rscale[0] = (float*)(base + p.off_rscale0);
         h.rscale[1] = (float*)(base + p.off_rscale1);
-        h.fscale[0] = apart ? (float*)(base + p.off_fscale0) : h.rscale[0] + (lat->L - 2);
-        h.fscale[1] = apart ? (float*)(base + p.off_fscale1) : h.rscale[1] + (lat->L - 2);
+        h.fscale[0] = row ? h.rscale[0] + (lat->L - 2) : (float*)(base + p.off_fscale0);
+        h.fscale[1] = row ? h.rscale[1] + (lat->L - 2) : (float*)(base + p.off_fscale1);
     }
     const rlbm_face& fi = d->faces[0];
     if (is_inlet(fi.type)) {
@@ -1072,8 +1074,7 @@ StateLayout state_layout(const rlbm_lattice* lat, uint32_t version) {
     const bool f32 = lat->storage == RLBM_STORAGE_F32_DEV;
     s.n_ref = f32 ? (version == 1u ? ref_doubles_v1(lat->L) : ref_doubles(lat->L)) * sizeof(double) : 0;
     s.n_pops = L * Q * (size_t)lat->host.P * (f32 ? 4 : 8);
-    s.rss = (size_t)scale_stride(lat->L, lat->storage,
-                                 version == 1u ? RLBM_REACTION_LINEARLY_IMPLICIT : RLBM_REACTION_EXPLICIT);
+    s.rss = !f32 ? 0 : (version == 1u ? (L + 3) / 4 * 4 : (size_t)scale_stride(lat->L));
     s.n_scale = s.rss * N * sizeof(float);
     s.n_fscale = f32 && version != 1u ? 2 * N * sizeof(float) : 0;
     s.n_aux = ((size_t)AUX_Y + M + 6) * N * sizeof(double);
@@ -1105,19 +1106,33 @@ constexpr size_t PACK_MOST = 32u << 20;
 bool packs(const StateLayout& s) {
     return s.total - s.scale <= std::min(s.n_pops, PACK_MOST);
 }
-// The sections' places in the lattice, and at `at` of the snapshot, the source
-// of the copies if `save`.
+// The sections as they lie in the lattice already.
+bool direct(const rlbm_lattice* lat, const StateLayout& s, uint32_t version) {
+    return !s.n_scale || (version == state_version(lat) && (version == 2u || lat->host.fss == (int)s.rss));
+}
+void add_seg(Pack& p, bool save, void* mem, unsigned step, void* file, unsigned fstep, unsigned rows, unsigned words) {
+    if (rows && words)
+        p.seg[p.n++] = save ? PackSeg{mem, file, rows, words, step, fstep} : PackSeg{file, mem, rows, words, fstep, step};
+}
+// The scales, between the lattice and rows of s.rss floats at sc: the species,
+// with rho and rho E behind them or (version 2) in rows of two at f; an
+// explicit lattice's second buffer at `next`.
+void add_scales(Pack& p, const rlbm_lattice* lat, const StateLayout& s, int q, float* sc, float* next, float* f, bool save) {
+    const unsigned N = (unsigned)lat->geo.N, nsp = (unsigned)lat->L - 2u, rss = (unsigned)lat->host.rss;
+    if (!s.n_scale) return;
+    add_seg(p, save, lat->host.rscale[q], rss, sc, (unsigned)s.rss, N, nsp);
+    if (next) add_seg(p, save, lat->host.rscale[q ^ 1], rss, next, (unsigned)s.rss, N, nsp);
+    add_seg(p, save, lat->host.fscale[q], (unsigned)lat->host.fss, f, s.n_fscale ? 2u : (unsigned)s.rss, N, 2u);
+}
+// All that follows the populations, packed at `packed` as in the snapshot.
 Pack pack_of(const rlbm_lattice* lat, const StateLayout& s, int q, char* packed, bool save) {
     Pack p{};
-    auto add = [&](void* mem, size_t at, size_t n) {
-        char* m = packed + (at - s.scale);
-        if (n) p.seg[p.n++] = PackSeg{save ? mem : m, save ? m : mem, (unsigned)(n / 4), 1u, 1u, 1u};
-    };
-    add(lat->host.rscale[q], s.scale, s.n_scale);
-    add(lat->host.rscale[q ^ 1], s.scale_next, s.n_fscale ? s.n_scale : 0);
-    add(lat->host.fscale[q], s.fscale, s.n_fscale);
-    add(lat->host.aux, s.aux, s.n_aux);
-    add(lat->host.out_state, s.out, s.n_out);
+    float* sc = (float*)packed;
+    const bool ex = state_version(lat) == 2u;
+    add_scales(p, lat, s, q, sc, !ex ? nullptr : (s.n_fscale ? (float*)(packed + (s.scale_next - s.scale)) : sc),
+               s.n_fscale ? (float*)(packed + (s.fscale - s.scale)) : sc + (lat->L - 2), save);
+    add_seg(p, save, lat->host.aux, 1u, packed + (s.aux - s.scale), 1u, (unsigned)(s.n_aux / 4), 1u);
+    add_seg(p, save, lat->host.out_state, 1u, packed + (s.out - s.scale), 1u, (unsigned)(s.n_out / 4), 1u);
     return p;
 }
 
@@ -1142,15 +1157,22 @@ int rlbm_save_state(rlbm_lattice* lat, void* buf, int on_device) {
     HIP_TRY(put(0, &h, sizeof(h)), "save state");
     HIP_TRY(put(sl.ref, lat->d_ref, sl.n_ref), "save state");
     HIP_TRY(put(sl.pops, lat->host.pop[q], sl.n_pops), "save state");
+    char* stage = (char*)lat->host.pop[q ^ 1];
     if (packs(sl)) {
-        char* packed = (char*)lat->host.pop[q ^ 1];
-        HIP_TRY(launch_pack(pack_of(lat, sl, q, packed, true), nullptr), "save state");
-        HIP_TRY(put(sl.scale, packed, sl.total - sl.scale), "save state");
+        HIP_TRY(launch_pack(pack_of(lat, sl, q, stage, true), nullptr), "save state");
+        HIP_TRY(put(sl.scale, stage, sl.total - sl.scale), "save state");
     } else {
-        HIP_TRY(put(sl.scale, lat->host.rscale[q], sl.n_scale), "save state");
-        if (sl.n_fscale) {
-            HIP_TRY(put(sl.scale_next, lat->host.rscale[q ^ 1], sl.n_scale), "save state");
-            HIP_TRY(put(sl.fscale, lat->host.fscale[q], sl.n_fscale), "save state");
+        if (direct(lat, sl, h.version)) {
+            HIP_TRY(put(sl.scale, lat->host.rscale[q], sl.n_scale), "save state");
+            if (sl.n_fscale) {
+                HIP_TRY(put(sl.scale_next, lat->host.rscale[q ^ 1], sl.n_scale), "save state");
+                HIP_TRY(put(sl.fscale, lat->host.fscale[q], sl.n_fscale), "save state");
+            }
+        } else {
+            Pack p{};
+            add_scales(p, lat, sl, q, (float*)stage, nullptr, (float*)stage + (lat->L - 2), true);
+            HIP_TRY(launch_pack(p, nullptr), "save state");
+            HIP_TRY(put(sl.scale, stage, sl.n_scale), "save state");
         }
         HIP_TRY(put(sl.aux, lat->host.aux, sl.n_aux), "save state");
         HIP_TRY(put(sl.out, lat->host.out_state, sl.n_out), "save state");
@@ -1201,28 +1223,22 @@ int rlbm_load_state(rlbm_lattice* lat, const void* buf, int on_device) {
     }
     HIP_TRY(get(lat->host.pop[q], sl.pops, sl.n_pops), "load state");
     char* stage = (char*)lat->host.pop[q ^ 1];
-    const bool same = !sl.n_scale || h.version == state_version(lat);
-    if (same && packs(sl)) {
+    if (packs(sl)) {
         HIP_TRY(get(stage, sl.scale, sl.total - sl.scale), "load state");
         HIP_TRY(launch_pack(pack_of(lat, sl, q, stage, false), nullptr), "load state");
     } else {
-        if (same) {
+        if (direct(lat, sl, h.version)) {
             HIP_TRY(get(lat->host.rscale[q], sl.scale, sl.n_scale), "load state");
             if (sl.n_fscale) {
                 HIP_TRY(get(lat->host.rscale[q ^ 1], sl.scale_next, sl.n_scale), "load state");
                 HIP_TRY(get(lat->host.fscale[q], sl.fscale, sl.n_fscale), "load state");
             }
         } else {
-            // rows of the other version: the species to both buffers, rho and
-            // rho E from behind them or apart
-            const unsigned N = (unsigned)lat->geo.N, nsp = (unsigned)(lat->L - 2), row = (unsigned)sl.rss;
-            const unsigned rss = (unsigned)lat->host.rss, fss = (unsigned)lat->host.fss;
-            float *sc = (float*)stage, *f = sc + (sl.n_fscale ? sl.n_scale / sizeof(float) : nsp);
+            float *sc = (float*)stage, *f = sc + (sl.n_fscale ? sl.n_scale / sizeof(float) : (size_t)lat->L - 2);
             HIP_TRY(get(sc, sl.scale, sl.n_scale), "load state");
             HIP_TRY(get(f, sl.fscale, sl.n_fscale), "load state");
             Pack p{};
-            for (int e = 0; e < 2; ++e) p.seg[p.n++] = PackSeg{sc, lat->host.rscale[e], N, nsp, row, rss};
-            p.seg[p.n++] = PackSeg{f, lat->host.fscale[q], N, 2u, sl.n_fscale ? 2u : row, fss};
+            add_scales(p, lat, sl, q, sc, state_version(lat) == 2u ? sc : nullptr, f, false);
             HIP_TRY(launch_pack(p, nullptr), "load state");
         }
         HIP_TRY(get(lat->host.aux, sl.aux, sl.n_aux), "load state");

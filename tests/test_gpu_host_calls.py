@@ -85,7 +85,8 @@ def test_written_populations_come_back(nx, storage, mech9):
 @pytest.mark.parametrize("kind,dims,kw", [
     ("reactor", (1, 1, 1), {}), ("reactor", (7, 1, 1), {}), ("channel3d", (9, 7, 5), {}),      # sections apart, or packed
     ("channel3d", (9, 7, 5), dict(coupling="weak")), ("channel3d", (9, 7, 5), dict(reaction="implicit")),
-    ("channel2d", (1030, 150, 1), {})])                                                        # beyond the packed size
+    ("reactor", (1, 1, 1), dict(reaction="implicit")),
+    ("channel2d", (1030, 150, 1), {}), ("channel2d", (1030, 150, 1), dict(reaction="implicit"))])   # beyond the packed size
 def test_snapshots_to_host_and_device(kind, dims, kw, storage, mech9):
     """Snapshots taken after even and odd numbers of steps, to the host and to
     the device, resume in another lattice (its buffers the other way round) to
