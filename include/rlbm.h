@@ -285,8 +285,9 @@ int rlbm_batch_create(rlbm_lattice* const* lats, int32_t k, void* dev_mem, size_
  * enqueued on the first lattice's stream, after the work already queued on
  * the other lattices' streams, and those streams wait for it, so later calls
  * on any lattice of the batch see its result.  Whole chunks of 16 steps are
- * enqueued as replays of one captured HIP graph (kernel nodes only), the
- * rest as direct launches.  Returns at once unless the host staging of the
+ * enqueued as replays of one captured HIP graph (kernel nodes only) while
+ * hardly any of the lattices has finished, the rest as direct launches for
+ * those that have not.  Returns at once unless the host staging of the
  * call before last is still in flight. */
 int rlbm_batch_step(rlbm_batch* batch, const int64_t* steps);
 /* Failure flags of every lattice, status[k] (see rlbm_lattice_status), read

@@ -1327,8 +1327,12 @@ BatchPlan batch_plan(int k) {
     p.total = o;
     return p;
 }
-// Steps per captured chunk of a batch.
-constexpr int BATCH_CHUNK = 16;
+// Steps per captured chunk of a batch.  A replay takes a third of the host's
+// time of its launches (16 steps: 33 against 86 us), and as long on the GPU
+// while the tiles of finished lattices in its grids are no more than
+// BATCH_IDLE (an eighth of the places of 512 resident blocks), or an eighth of
+// the others.
+constexpr int BATCH_CHUNK = 16, BATCH_IDLE = 64;
 constexpr int BATCH_RING = 2;
 }  // namespace
 
@@ -1349,9 +1353,8 @@ struct rlbm_batch {
     bool slot_used[BATCH_RING] = {false, false};
     int next_slot = 0;
     int* pinned_status = nullptr;
-    int nb[3] = {0, 0, 0};                      // node, interface and 64-node blocks of all lattices
-    unsigned schemes = 0;
-    std::vector<int> host_blk;
+    std::vector<int> order;                     // lattices by descending steps of the call
+    std::vector<unsigned> schemes;              // [k + 1]: bit r set if one of the first n of them uses RLBM_REACTION r
     bool graphs = true;
     hipStream_t cap = nullptr;                  // private stream for graph capture
     hipGraph_t graph = nullptr;
@@ -1373,37 +1376,66 @@ static void batch_free(rlbm_batch* b) {
     delete b;
 }
 
-// Launches of steps t = *tp + toff0 .. *tp + toff0 + n - 1 of every lattice
-// of the batch (a lattice is active while t < its t_end).
-static hipError_t batch_launch(rlbm_batch* b, hipStream_t st, long long toff0, long long n) {
-    const int k = (int)b->lats.size();
-    rlbm_lattice* l0 = b->lats[0];
-    const long long* tp = (const long long*)(b->base + b->plan.off_t);
-    const LatDev* table = (const LatDev*)(b->base + b->plan.off_table);
-    const int* blk = (const int*)(b->base + b->plan.off_blk);
-    for (long long t = toff0; t < toff0 + n; ++t) {
-        for (int phase = 0; phase < NPHASE; ++phase) {
-            StepLaunch a;
-            a.lats = table;
-            a.blk = phase == 0 ? blk + (k + 1) : (phase == NPHASE - 1 ? blk + 2 * (k + 1) : blk);
-            a.n_lat = k;
-            a.blocks = phase == 0 ? b->nb[1] : (phase == NPHASE - 1 ? b->nb[2] : b->nb[0]);
-            a.tp = tp;
-            a.toff = t;
-            a.stream = st;
-            a.schemes = b->schemes;
-            if (a.blocks == 0) continue;
-            const hipError_t e = launch_phase(phase, l0->M, l0->storage, l0->host.weak, a);
-            if (e != hipSuccess) return e;
-        }
+// Blocks of a lattice in the launches: node tiles, boundary blocks, 64-node tiles.
+static void lattice_blocks(const rlbm_lattice* lat, int (&nb)[3]) {
+    nb[0] = (int)((lat->geo.N + NODE_TILE - 1) / NODE_TILE);
+    nb[1] = lat->geo.if_blocks();
+    nb[2] = (int)((lat->geo.N + 63) / 64);
+}
+
+// The lattices of a joint step by descending step count (equal ones in the
+// caller's order), so that those still stepping are the first n of the table
+// at any time and a launch has blocks for them only.  With the blocks of all of
+// them, twelve finished 256x64x64 channels made 160 steps of eight reactors and
+// eight tubes take 73 ms instead of 15: a block that only returns still takes
+// its place and its LDS on a CU, and the one contiguous range of tiles each XCD
+// gets leaves the active ones to one or two XCDs.
+static void by_steps(int* order, int k, const int64_t* steps) {
+    for (int j = 0; j < k; ++j) order[j] = j;
+    std::sort(order, order + k, [&](int a, int b) { return steps[a] != steps[b] ? steps[a] > steps[b] : a < b; });
+}
+// Lattices of the order with more than t steps, from n (a bound) down.
+static int still_active(const int* order, const int64_t* steps, int n, long long t) {
+    while (n > 0 && steps[order[n - 1]] <= t) --n;
+    return n;
+}
+
+// The launches of step *tp + toff of the first n lattices of a table of k, blk
+// its three block prefixes on the device and host_blk the same on the host.
+static hipError_t launch_joint(const rlbm_lattice* l0, const LatDev* table, const int* blk, const int* host_blk, int k,
+                               int n, unsigned schemes, const long long* tp, long long toff, hipStream_t st) {
+    for (int phase = 0; phase < NPHASE; ++phase) {
+        const int which = phase == 0 ? 1 : (phase == NPHASE - 1 ? 2 : 0);
+        StepLaunch a;
+        a.lats = table;
+        a.blk = blk + which * (k + 1);
+        a.n_lat = n;
+        a.blocks = host_blk[which * (k + 1) + n];
+        a.tp = tp;
+        a.toff = toff;
+        a.stream = st;
+        a.schemes = schemes;
+        if (a.blocks == 0) continue;
+        const hipError_t e = launch_phase(phase, l0->M, l0->storage, l0->host.weak, a);
+        if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-// Captures BATCH_CHUNK steps and the counter advance as one graph.
-static int batch_capture(rlbm_batch* b) {
+// Step *tp + toff of the first n lattices of the call's order; up: the call's
+// upload.
+static hipError_t batch_launch(rlbm_batch* b, hipStream_t st, const char* up, int n, long long toff) {
+    return launch_joint(b->lats[0], (const LatDev*)(b->base + b->plan.off_table), (const int*)(b->base + b->plan.off_blk),
+                        (const int*)(up + b->plan.off_blk), (int)b->lats.size(), n, b->schemes[n],
+                        (const long long*)(b->base + b->plan.off_t), toff, st);
+}
+
+// Captures BATCH_CHUNK steps of all lattices and the counter advance as one
+// graph.  Its grids hold for every call: the order changes, their sum does not.
+static int batch_capture(rlbm_batch* b, const char* up) {
     HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeRelaxed), "hipStreamBeginCapture");
-    hipError_t e = batch_launch(b, b->cap, 0, BATCH_CHUNK);
+    hipError_t e = hipSuccess;
+    for (int t = 0; t < BATCH_CHUNK && e == hipSuccess; ++t) e = batch_launch(b, b->cap, up, (int)b->lats.size(), t);
     if (e == hipSuccess) e = launch_advance_time((long long*)(b->base + b->plan.off_t), BATCH_CHUNK, b->cap);
     hipGraph_t g = nullptr;
     const hipError_t e2 = hipStreamEndCapture(b->cap, &g);
@@ -1476,22 +1508,10 @@ int rlbm_batch_create(rlbm_lattice* const* lats, int32_t k, void* dev_mem, size_
     if ((e = hipHostMalloc((void**)&b->pinned_status, (size_t)k * sizeof(int), hipHostMallocDefault)) != hipSuccess)
         return bail(e, "hipHostMalloc");
     if ((e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking)) != hipSuccess) return bail(e, "hipStreamCreate");
-    // every lattice takes part in every launch (a lattice without steps in a
-    // call returns at once), so the grids, and with them a captured chunk,
-    // stay the same from call to call
-    b->host_blk.assign(3 * (k + 1), 0);
+    b->order.resize(k);
+    b->schemes.resize(k + 1);
     std::vector<int*> flagp(k);
-    for (int j = 0; j < k; ++j) {
-        const rlbm_lattice* lat = lats[j];
-        b->schemes |= 1u << lat->host.reaction;
-        b->host_blk[j + 1] = b->host_blk[j] + (int)((lat->geo.N + NODE_TILE - 1) / NODE_TILE);
-        b->host_blk[(k + 1) + j + 1] = b->host_blk[(k + 1) + j] + lat->geo.if_blocks();
-        b->host_blk[2 * (k + 1) + j + 1] = b->host_blk[2 * (k + 1) + j] + (int)((lat->geo.N + 63) / 64);
-        flagp[j] = lat->d_flag;
-    }
-    b->nb[0] = b->host_blk[k];
-    b->nb[1] = b->host_blk[2 * (k + 1) - 1];
-    b->nb[2] = b->host_blk[3 * (k + 1) - 1];
+    for (int j = 0; j < k; ++j) flagp[j] = lats[j]->d_flag;
     if ((e = hipMemcpy(b->base + plan.off_flagp, flagp.data(), (size_t)k * sizeof(int*), hipMemcpyHostToDevice)) !=
         hipSuccess)
         return bail(e, "upload batch table");
@@ -1516,14 +1536,21 @@ int rlbm_batch_step(rlbm_batch* b, const int64_t* steps) {
     char* up = b->pinned[r];
     *(long long*)(up + b->plan.off_t) = 0;
     LatDev* tab = (LatDev*)(up + b->plan.off_table);
+    int* blk = (int*)(up + b->plan.off_blk);
+    by_steps(b->order.data(), k, steps);
+    for (int a = 0; a < 3; ++a) blk[a * (k + 1)] = 0;
+    b->schemes[0] = 0;
     for (int j = 0; j < k; ++j) {
-        const rlbm_lattice* lat = b->lats[j];
+        const rlbm_lattice* lat = b->lats[b->order[j]];
         LatDev e = lat->host;
         e.parity0 = (int)((lat->host.parity0 + lat->steps_done) & 1);
-        e.t_end = steps[j];
+        e.t_end = steps[b->order[j]];
         tab[j] = e;
+        int nb[3];
+        lattice_blocks(lat, nb);
+        for (int a = 0; a < 3; ++a) blk[a * (k + 1) + j + 1] = blk[a * (k + 1) + j] + nb[a];
+        b->schemes[j + 1] = b->schemes[j] | 1u << lat->host.reaction;
     }
-    std::memcpy(up + b->plan.off_blk, b->host_blk.data(), b->host_blk.size() * sizeof(int));
     // order after the work already queued on the lattices' own streams
     for (size_t q = 0; q < b->others.size(); ++q) {
         HIP_TRY(hipEventRecord(b->other_ev[q], b->others[q]), "hipEventRecord");
@@ -1533,14 +1560,26 @@ int rlbm_batch_step(rlbm_batch* b, const int64_t* steps) {
     HIP_TRY(hipEventRecord(b->slot_ev[r], b->stream), "hipEventRecord");
     b->slot_used[r] = true;
     b->next_slot = (r + 1) % BATCH_RING;
-    // whole chunks replay the captured graph; the rest are direct launches
-    long long full = b->graphs ? tmax / BATCH_CHUNK : 0;
+    // whole chunks replay the captured graph of all lattices while few of its
+    // blocks are of lattices that are done; the rest are direct launches of the
+    // lattices still stepping
+    long long full = 0;
+    if (b->graphs) {
+        for (int m = k; (full + 1) * BATCH_CHUNK <= tmax; ++full) {
+            m = still_active(b->order.data(), steps, m, (full + 1) * BATCH_CHUNK - 1);
+            if (blk[k] - blk[m] > std::max(BATCH_IDLE, blk[m] / 8)) break;
+        }
+    }
     if (full > 0 && !b->exec) {
-        const int rc = batch_capture(b);
+        const int rc = batch_capture(b, up);
         if (rc) return rc;
     }
     for (long long c = 0; c < full; ++c) HIP_TRY(hipGraphLaunch(b->exec, b->stream), "hipGraphLaunch");
-    HIP_TRY(batch_launch(b, b->stream, 0, tmax - full * BATCH_CHUNK), "batch kernel launch");
+    int n = k;
+    for (long long t = full * BATCH_CHUNK; t < tmax; ++t) {
+        n = still_active(b->order.data(), steps, n, t);
+        HIP_TRY(batch_launch(b, b->stream, up, n, t - full * BATCH_CHUNK), "batch kernel launch");
+    }
     HIP_TRY(hipEventRecord(b->done, b->stream), "hipEventRecord");
     b->stepped = true;
     for (size_t q = 0; q < b->others.size(); ++q)
@@ -1591,8 +1630,9 @@ int rlbm_step_group(rlbm_lattice* const* lats, int32_t k, const int64_t* steps) 
     HIP_TRY(group_scratch(l0->device, &sc), "hipGetSymbolAddress");
     // the table, filled on the device from the lattices' own entries in
     // chunks whose data travel as kernel arguments
-    int pre[3] = {0, 0, 0};
-    unsigned schemes = 0;
+    int order[RLBM_GROUP_MAX_LATTICES], host_blk[3 * (RLBM_GROUP_MAX_LATTICES + 1)] = {};
+    unsigned schemes[RLBM_GROUP_MAX_LATTICES + 1] = {};
+    by_steps(order, k, steps);
     for (int base = 0; base < k; base += GROUP_CHUNK) {
         GroupChunk c;
         std::memset(&c, 0, sizeof(c));
@@ -1600,35 +1640,27 @@ int rlbm_step_group(rlbm_lattice* const* lats, int32_t k, const int64_t* steps) 
         c.n = std::min(GROUP_CHUNK, k - base);
         c.k = k;
         for (int j = 0; j <= c.n; ++j) {
-            for (int a = 0; a < 3; ++a) c.blk[a][j] = pre[a];
+            const int at = base + j;
+            for (int a = 0; a < 3; ++a) c.blk[a][j] = host_blk[a * (k + 1) + at];
             if (j == c.n) break;
-            const rlbm_lattice* lat = lats[base + j];
+            const rlbm_lattice* lat = lats[order[at]];
             c.src[j] = lat->d_lat;
-            c.t_end[j] = steps[base + j];
+            c.t_end[j] = steps[order[at]];
             c.parity[j] = (int)((lat->host.parity0 + lat->steps_done) & 1);
-            schemes |= 1u << lat->host.reaction;
-            pre[0] += (int)((lat->geo.N + NODE_TILE - 1) / NODE_TILE);
-            pre[1] += lat->geo.if_blocks();
-            pre[2] += (int)((lat->geo.N + 63) / 64);
+            schemes[at + 1] = schemes[at] | 1u << lat->host.reaction;
+            int nb[3];
+            lattice_blocks(lat, nb);
+            for (int a = 0; a < 3; ++a) host_blk[a * (k + 1) + at + 1] = host_blk[a * (k + 1) + at] + nb[a];
         }
         HIP_TRY(launch_group_gather(sc, c, l0->stream), "group table kernel");
     }
     const LatDev* table = (const LatDev*)(sc + GROUP_OFF_TABLE);
     const int* blk = (const int*)(sc + GROUP_OFF_BLK);
+    int n = k;
     for (long long t = 0; t < tmax; ++t) {
-        for (int phase = 0; phase < NPHASE; ++phase) {
-            StepLaunch a;
-            a.lats = table;
-            a.blk = phase == 0 ? blk + (k + 1) : (phase == NPHASE - 1 ? blk + 2 * (k + 1) : blk);
-            a.n_lat = k;
-            a.blocks = phase == 0 ? pre[1] : (phase == NPHASE - 1 ? pre[2] : pre[0]);
-            a.tp = (const long long*)sc;
-            a.toff = t;
-            a.stream = l0->stream;
-            a.schemes = schemes;
-            if (a.blocks == 0) continue;
-            HIP_TRY(launch_phase(phase, l0->M, l0->storage, l0->host.weak, a), "group kernel launch");
-        }
+        n = still_active(order, steps, n, t);
+        HIP_TRY(launch_joint(l0, table, blk, host_blk, k, n, schemes[n], (const long long*)sc, t, l0->stream),
+                "group kernel launch");
     }
     for (int j = 0; j < k; ++j) lats[j]->steps_done += steps[j];
     return RLBM_OK;

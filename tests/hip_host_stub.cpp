@@ -17,7 +17,7 @@ struct Copy {
 std::vector<Copy> queued;
 std::map<void*, size_t> pinned;
 size_t pinned_bytes = 0, pinned_peak = 0, pinned_limit = (size_t)-1;
-long frees = 0, waits = 0, launches = 0, fail_at = -1;
+long frees = 0, waits = 0, launches = 0, blocks = 0, replays = 0, fail_at = -1;
 int last_error = 0;
 constexpr int OUT_OF_MEMORY = 2, LAUNCH_FAILURE = 719;
 
@@ -28,10 +28,12 @@ void drain() {
 }
 }  // namespace
 
-extern "C" {
 struct Dim3 {
     unsigned x, y, z;
 };
+static Dim3 pushed[2];
+
+extern "C" {
 
 // what a test sets and reads
 void stub_pinned_limit(size_t bytes) { pinned_limit = bytes; }          // hipHostMalloc fails beyond
@@ -39,6 +41,8 @@ void stub_fail_launch(long n) { fail_at = n < 0 ? -1 : launches + n; }  // the n
 long stub_queued() { return (long)queued.size(); }
 long stub_waits() { return waits; }
 long stub_frees() { return frees; }
+long stub_blocks() { return blocks; }      // of all launches
+long stub_replays() { return replays; }    // of graphs
 size_t stub_pinned() { return pinned_bytes; }
 
 int hipGetDevice(int* d) { *d = 0; return 0; }
@@ -83,14 +87,39 @@ int hipMemcpy2DAsync(void* dst, size_t dp, const void* src, size_t sp, size_t w,
 }
 int hipStreamSynchronize(void*) { drain(); return 0; }
 
-int __hipPushCallConfiguration(Dim3, Dim3, size_t, void*) { return 0; }
+int hipEventCreateWithFlags(void** e, unsigned) { *e = nullptr; return 0; }
+int hipEventDestroy(void*) { return 0; }
+int hipEventRecord(void*, void*) { return 0; }
+int hipEventSynchronize(void*) { return 0; }
+int hipStreamCreateWithFlags(void** s, unsigned) { *s = nullptr; return 0; }
+int hipStreamDestroy(void*) { return 0; }
+int hipStreamWaitEvent(void*, void*, unsigned) { return 0; }
+int hipStreamBeginCapture(void*, int) { return 0; }
+int hipStreamEndCapture(void*, void** g) { *g = nullptr; return 0; }
+int hipGraphInstantiate(void** x, void*, void*, char*, size_t) { *x = &pushed; return 0; }
+int hipGraphLaunch(void*, void*) { ++replays; return 0; }
+int hipGraphDestroy(void*) { return 0; }
+int hipGraphExecDestroy(void*) { return 0; }
+int hipGetSymbolAddress(void** p, const void*) {
+    static char device_array[1 << 20];
+    *p = device_array;
+    return 0;
+}
+
+int __hipPushCallConfiguration(Dim3 g, Dim3 b, size_t, void*) {
+    pushed[0] = g;
+    pushed[1] = b;
+    return 0;
+}
 int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* s, void** st) {
-    *g = *b = Dim3{1, 1, 1};
+    *g = pushed[0];
+    *b = pushed[1];
     *s = 0;
     *st = nullptr;
     return 0;
 }
-int hipLaunchKernel(const void*, Dim3, Dim3, void**, size_t, void*) {
+int hipLaunchKernel(const void*, Dim3 g, Dim3, void**, size_t, void*) {
+    blocks += (long)g.x * g.y * g.z;
     if (launches++ == fail_at) return last_error = LAUNCH_FAILURE;
     return 0;
 }

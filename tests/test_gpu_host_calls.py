@@ -114,3 +114,30 @@ def test_snapshots_to_host_and_device(kind, dims, kw, storage, mech9):
         for other in (back, dev):
             np.testing.assert_array_equal(other.populations(), pops)
             np.testing.assert_array_equal(other.fields()["T"], lat.fields()["T"])
+
+
+@pytest.mark.parametrize("steps", [(40, 3, 0, 70, 16), (0, 5, 40, 33, 40), (48, 48, 48, 48, 48), (17, 64, 64, 64, 64)])
+def test_joint_steps_with_uneven_counts(steps, mech9):
+    """Lattices of uneven step counts in any order, one of them on the linearly
+    implicit update, by a batch (graph replays where hardly any has finished,
+    direct launches of those that have not) and by a group: the bits of stepping
+    each alone, two calls in a row."""
+    rlbm = _rlbm()
+    print(f"case joint steps {steps}", flush=True)
+    m = rlbm.Mechanism(mech9)
+    cases = [wl.make_case("tube", seed=21, mech=mech9, nx=130),
+             wl.make_case("channel3d", seed=22, mech=mech9, nx=40, ny=24, nz=8),
+             wl.make_case("channel2d", seed=23, mech=mech9, nx=40, ny=10, nz=1, reaction="implicit"),
+             wl.make_case("reactor", seed=24, mech=mech9, nx=4, ny=4, nz=4),
+             wl.make_case("tube", seed=25, mech=mech9, nx=64)]
+    alone, batched, grouped = ([rlbm.Lattice(c, storage="f32dev", mech=m).set_state() for c in cases] for _ in range(3))
+    batch = rlbm.Batch(batched)
+    for order in (steps, steps[::-1]):
+        batch.step(order)
+        rlbm.step_group(grouped, order)
+        for a, n in zip(alone, order):
+            a.step(n)
+        for a, b, g in zip(alone, batched, grouped):
+            pops = a.populations()
+            np.testing.assert_array_equal(b.populations(), pops)
+            np.testing.assert_array_equal(g.populations(), pops)

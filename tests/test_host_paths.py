@@ -22,7 +22,7 @@ class Host:
         self.stub = ctypes.CDLL(stub, mode=ctypes.RTLD_GLOBAL)
         self.stub.stub_pinned.restype = ctypes.c_size_t
         self.stub.stub_pinned_limit.argtypes = [ctypes.c_size_t]
-        for f in ("stub_queued", "stub_waits", "stub_frees"):
+        for f in ("stub_queued", "stub_waits", "stub_frees", "stub_blocks", "stub_replays"):
             getattr(self.stub, f).restype = ctypes.c_long
         self.stub.stub_fail_launch.argtypes = [ctypes.c_long]
         sys.path.insert(0, ROOT)
@@ -127,6 +127,35 @@ def check_snapshots_wait_once(host):
                     assert host.stub.stub_waits() - at <= most, (storage, kw, nx)
                     assert host.stub.stub_queued() == 0
                 host.L.rlbm_lattice_destroy(h)
+
+
+def check_finished_lattices_take_no_blocks(host):
+    """Joint steps of a long tube (1 step) and two short ones: the long one's
+    tiles are in the grids of its step only, wherever it stands in the batch."""
+    tiles = lambda n: (n + 63) // 64                     # noqa: E731
+    for sizes, steps in (((64000, 64, 128), (1, 40, 37)), ((128, 64000, 64), (37, 1, 40)), ((64, 128, 64000), (40, 37, 0))):
+        hs = [host.lattice(nx) for nx in sizes]
+        for h, _mem, case in hs:
+            assert host.set_state(h, case) == 0
+        k = len(hs)
+        lats = (ctypes.c_void_p * k)(*[h.value for h, _, _ in hs])
+        st = (ctypes.c_int64 * k)(*steps)
+        n = ctypes.c_size_t()
+        host.rlbm._check(host.L.rlbm_batch_bytes(k, ctypes.byref(n)))
+        mem = np.zeros(n.value + 256, np.uint8)
+        b = ctypes.c_void_p()
+        host.rlbm._check(host.L.rlbm_batch_create(lats, k, (mem.ctypes.data + 255) & ~255, n.value, ctypes.byref(b)))
+        # k_boundary: an inlet and an outlet node per tube, a block; k_species and k_flow: a block per tile
+        want = sum(s * (1 + 2 * tiles(nx)) for nx, s in zip(sizes, steps))
+        at = host.stub.stub_blocks()
+        host.rlbm._check(host.L.rlbm_batch_step(b, st))
+        assert host.stub.stub_blocks() - at == want and host.stub.stub_replays() == 0
+        at = host.stub.stub_blocks()
+        host.rlbm._check(host.L.rlbm_step_group(lats, k, st))
+        assert host.stub.stub_blocks() - at == want + k     # and the table kernel's
+        host.L.rlbm_batch_destroy(b)
+        for h, _mem, _ in hs:
+            host.L.rlbm_lattice_destroy(h)
 
 
 CHECKS = {n: f for n, f in list(globals().items()) if n.startswith("check_")}
