@@ -3269,7 +3269,7 @@ __global__ __launch_bounds__(256) void k_reduce_partials(const double* __restric
 
 // The small sections of a snapshot, to or from one piece of memory: one launch
 // in place of a copy each, of which the runtime takes four in 3 us apiece and
-// every further one in 8 (to the host 13 apiece).
+// every further one in 8.
 __global__ __launch_bounds__(256) void k_pack(Pack p) {
     const PackSeg g = p.seg[blockIdx.y];
     const RLBM_GLOBAL unsigned* src = as_global(static_cast<const unsigned*>(g.src));

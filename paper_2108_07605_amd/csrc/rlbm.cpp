@@ -270,7 +270,6 @@ Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     const size_t P = plane_stride(g);
     p.off_pop0 = take((size_t)L * Q * P * s);
     p.off_pop1 = take((size_t)L * Q * P * s);
-    p.off_aux = take((size_t)(AUX_Y + M + 6) * N * sizeof(double));
     const int rows = d->reaction == RLBM_REACTION_EXPLICIT ? PRM_ROWS_EXPLICIT : prm_rows(M);
     p.off_prm = take((size_t)rows * N * sizeof(double));
     p.off_ifindex = take(nif ? N * sizeof(int) : 0);
@@ -280,14 +279,17 @@ Plan make_plan(const rlbm_lattice_desc* d, int M, int E, const Geometry& g) {
     p.off_ifT = take(nif * sizeof(double));
     p.off_ifout = take(nif * sizeof(int));
     p.off_ifblk = take(g.if_blk.size() * sizeof(int));
-    p.off_out = take((size_t)(5 + M) * g.n_out * sizeof(double));
     p.off_partial = take(nblocks * (6 + E) * sizeof(double));
     const bool f32 = d->storage == RLBM_STORAGE_F32_DEV;
     const size_t rss = f32 ? (size_t)scale_stride(L) : 0, fss = f32 && !flow_in_row(L, d->reaction) ? 2 : 0;
+    // from here in the order of a snapshot (of buffer 0), which copies what lies
+    // side by side at once
+    p.off_fscale1 = take(fss * N * sizeof(float));
     p.off_rscale0 = take(rss * N * sizeof(float));
     p.off_rscale1 = take(rss * N * sizeof(float));
     p.off_fscale0 = take(fss * N * sizeof(float));
-    p.off_fscale1 = take(fss * N * sizeof(float));
+    p.off_aux = take((size_t)(AUX_Y + M + 6) * N * sizeof(double));
+    p.off_out = take((size_t)(5 + M) * g.n_out * sizeof(double));
     p.total = o;
     return p;
 }
@@ -1055,19 +1057,19 @@ struct StateHeader {
     int32_t M, L, storage, slaved, rss, pad;
     int64_t N, n_out;
 };
-// Version 1 holds one vector of scales per node (species, rho, rho E; L rounded
-// up to four floats), the populations' own: what the linearly implicit update
-// keeps.  Version 2 holds what the explicit update keeps: the species scales of
-// both buffers (the populations' own and those the next step encodes with),
-// the scales of f and g apart, and the second copy of the reference shapes.  A
-// lattice writes the version of its update and loads both; an explicit step
+// Version 1 holds one vector of scales per node, the populations' own (species,
+// rho, rho E; L rounded up to four floats): what a lattice with f and g in the
+// species' row keeps.  Version 2 holds the species scales of both buffers (the
+// populations' own and those the next explicit step encodes with), the scales
+// of f and g apart, and the second copy of the reference shapes.  A lattice
+// writes the version that its own memory has, and loads both; an explicit step
 // after a version 1 snapshot encodes with the populations' own scales.
 struct StateLayout {
     size_t ref, pops, scale, scale_next, fscale, aux, out, total;
     size_t n_ref, n_pops, n_scale, n_fscale, n_aux, n_out;   // bytes of each section
     size_t rss;                                              // floats per node in `scale`
 };
-uint32_t state_version(const rlbm_lattice* lat) { return lat->host.reaction == RLBM_REACTION_EXPLICIT ? 2u : 1u; }
+uint32_t state_version(const rlbm_lattice* lat) { return flow_in_row(lat->L, lat->host.reaction) ? 1u : 2u; }
 StateLayout state_layout(const rlbm_lattice* lat, uint32_t version) {
     StateLayout s{};
     const size_t N = (size_t)lat->geo.N, L = (size_t)lat->L, M = (size_t)lat->M;
@@ -1098,41 +1100,68 @@ int rlbm_state_bytes(const rlbm_lattice* lat, size_t* bytes) {
     return RLBM_OK;
 }
 
-// The scales, node fields and outlet states of a snapshot, contiguous in it, are
-// packed in the idle population buffer and copied at once where they fit it and
-// are small: with more bytes than this the second pass over them costs more
-// than the copies it saves.
-constexpr size_t PACK_MOST = 32u << 20;
-bool packs(const StateLayout& s) {
-    return s.total - s.scale <= std::min(s.n_pops, PACK_MOST);
+// The sections of a snapshot, and where they are in a lattice: copies between
+// them, sections side by side in both as one.
+struct Sections {
+    struct Piece {
+        char* mem;
+        size_t at, n;
+    };
+    Piece piece[8];
+    int n = 0, first_packed = 0;
+    void add(void* mem, size_t at, size_t bytes) {
+        if (!bytes) return;
+        if (n) {
+            Piece& l = piece[n - 1];
+            const size_t step = align256(l.at + l.n) - l.at;
+            if (n > first_packed && l.at + step == at && l.mem + step == (char*)mem) {
+                l.n = step + bytes;
+                return;
+            }
+        }
+        piece[n++] = Piece{(char*)mem, at, bytes};
+    }
+};
+// first_packed: the first piece behind the populations.
+Sections sections_of(const rlbm_lattice* lat, const StateLayout& s, int q) {
+    Sections c;
+    c.add(lat->d_ref, s.ref, s.n_ref);
+    c.add(lat->host.pop[q], s.pops, s.n_pops);
+    c.first_packed = c.n;
+    c.add(lat->host.rscale[q], s.scale, s.n_scale);
+    if (s.n_fscale) {
+        c.add(lat->host.rscale[q ^ 1], s.scale_next, s.n_scale);
+        c.add(lat->host.fscale[q], s.fscale, s.n_fscale);
+    }
+    c.add(lat->host.aux, s.aux, s.n_aux);
+    c.add(lat->host.out_state, s.out, s.n_out);
+    return c;
 }
-// The sections as they lie in the lattice already.
-bool direct(const rlbm_lattice* lat, const StateLayout& s, uint32_t version) {
-    return !s.n_scale || (version == state_version(lat) && (version == 2u || lat->host.fss == (int)s.rss));
+// Several pieces behind the populations: between device buffers, where a copy
+// is a kernel as well, they go through the idle population buffer in one launch
+// and one copy, if they fit it and are small (with more bytes than this the
+// second pass over them costs more than the copies it saves); to the host all
+// that lies between them is copied at once, if it is smaller still, and sorted
+// there.
+constexpr size_t PACK_MOST = 32u << 20, SORT_MOST = 1u << 20;
+bool several(const Sections& c) { return c.n - c.first_packed > 1; }
+bool packs(const StateLayout& s, const Sections& c) {
+    return several(c) && s.total - s.scale <= std::min(s.n_pops, PACK_MOST);
 }
-void add_seg(Pack& p, bool save, void* mem, unsigned step, void* file, unsigned fstep, unsigned rows, unsigned words) {
-    if (rows && words)
-        p.seg[p.n++] = save ? PackSeg{mem, file, rows, words, step, fstep} : PackSeg{file, mem, rows, words, fstep, step};
+bool on_device_memory(const void* buf) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, buf) != hipSuccess) {
+        (void)hipGetLastError();   // memory the runtime does not know: the host's
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice;
 }
-// The scales, between the lattice and rows of s.rss floats at sc: the species,
-// with rho and rho E behind them or (version 2) in rows of two at f; an
-// explicit lattice's second buffer at `next`.
-void add_scales(Pack& p, const rlbm_lattice* lat, const StateLayout& s, int q, float* sc, float* next, float* f, bool save) {
-    const unsigned N = (unsigned)lat->geo.N, nsp = (unsigned)lat->L - 2u, rss = (unsigned)lat->host.rss;
-    if (!s.n_scale) return;
-    add_seg(p, save, lat->host.rscale[q], rss, sc, (unsigned)s.rss, N, nsp);
-    if (next) add_seg(p, save, lat->host.rscale[q ^ 1], rss, next, (unsigned)s.rss, N, nsp);
-    add_seg(p, save, lat->host.fscale[q], (unsigned)lat->host.fss, f, s.n_fscale ? 2u : (unsigned)s.rss, N, 2u);
-}
-// All that follows the populations, packed at `packed` as in the snapshot.
-Pack pack_of(const rlbm_lattice* lat, const StateLayout& s, int q, char* packed, bool save) {
+Pack pack_of(const Sections& c, const StateLayout& s, char* packed, bool save) {
     Pack p{};
-    float* sc = (float*)packed;
-    const bool ex = state_version(lat) == 2u;
-    add_scales(p, lat, s, q, sc, !ex ? nullptr : (s.n_fscale ? (float*)(packed + (s.scale_next - s.scale)) : sc),
-               s.n_fscale ? (float*)(packed + (s.fscale - s.scale)) : sc + (lat->L - 2), save);
-    add_seg(p, save, lat->host.aux, 1u, packed + (s.aux - s.scale), 1u, (unsigned)(s.n_aux / 4), 1u);
-    add_seg(p, save, lat->host.out_state, 1u, packed + (s.out - s.scale), 1u, (unsigned)(s.n_out / 4), 1u);
+    for (int k = c.first_packed; k < c.n; ++k) {
+        char *mem = c.piece[k].mem, *file = packed + (c.piece[k].at - s.scale);
+        p.seg[p.n++] = PackSeg{save ? mem : file, save ? file : mem, (unsigned)(c.piece[k].n / 4), 1u, 1u, 1u};
+    }
     return p;
 }
 
@@ -1150,32 +1179,32 @@ int rlbm_save_state(rlbm_lattice* lat, void* buf, int on_device) {
     StateHeader h{STATE_MAGIC, state_version(lat), lat->M, lat->L, lat->storage, lat->host.slaved, (int32_t)sl.rss, 0,
                   lat->geo.N, lat->geo.n_out};
     char* b = (char*)buf;
+    HostFields all;
     StreamWait wait(nullptr);
     auto put = [&](size_t at, const void* src, size_t n) {
         return n ? hipMemcpyAsync(b + at, src, n, hipMemcpyDefault, nullptr) : hipSuccess;
     };
     HIP_TRY(put(0, &h, sizeof(h)), "save state");
-    HIP_TRY(put(sl.ref, lat->d_ref, sl.n_ref), "save state");
-    HIP_TRY(put(sl.pops, lat->host.pop[q], sl.n_pops), "save state");
-    char* stage = (char*)lat->host.pop[q ^ 1];
-    if (packs(sl)) {
-        HIP_TRY(launch_pack(pack_of(lat, sl, q, stage, true), nullptr), "save state");
+    const Sections c = sections_of(lat, sl, q);
+    const bool dev = several(c) && on_device_memory(buf), pack = dev && packs(sl, c);
+    char *stage = (char*)lat->host.pop[q ^ 1], *lo = nullptr, *hi = nullptr;
+    for (int k = c.first_packed; k < c.n; ++k) {
+        lo = lo ? std::min(lo, c.piece[k].mem) : c.piece[k].mem;
+        hi = std::max(hi, c.piece[k].mem + c.piece[k].n);
+    }
+    if (several(c) && !dev && (size_t)(hi - lo) <= SORT_MOST) all.p = (double*)std::malloc(hi - lo);
+    for (int k = 0; k < (pack || all.p ? c.first_packed : c.n); ++k)
+        HIP_TRY(put(c.piece[k].at, c.piece[k].mem, c.piece[k].n), "save state");
+    if (pack) {
+        HIP_TRY(launch_pack(pack_of(c, sl, stage, true), nullptr), "save state");
         HIP_TRY(put(sl.scale, stage, sl.total - sl.scale), "save state");
-    } else {
-        if (direct(lat, sl, h.version)) {
-            HIP_TRY(put(sl.scale, lat->host.rscale[q], sl.n_scale), "save state");
-            if (sl.n_fscale) {
-                HIP_TRY(put(sl.scale_next, lat->host.rscale[q ^ 1], sl.n_scale), "save state");
-                HIP_TRY(put(sl.fscale, lat->host.fscale[q], sl.n_fscale), "save state");
-            }
-        } else {
-            Pack p{};
-            add_scales(p, lat, sl, q, (float*)stage, nullptr, (float*)stage + (lat->L - 2), true);
-            HIP_TRY(launch_pack(p, nullptr), "save state");
-            HIP_TRY(put(sl.scale, stage, sl.n_scale), "save state");
-        }
-        HIP_TRY(put(sl.aux, lat->host.aux, sl.n_aux), "save state");
-        HIP_TRY(put(sl.out, lat->host.out_state, sl.n_out), "save state");
+    }
+    if (all.p) {
+        HIP_TRY(hipMemcpyAsync(all.p, lo, hi - lo, hipMemcpyDeviceToHost, nullptr), "save state");
+        HIP_TRY(wait.done(), "save state");
+        for (int k = c.first_packed; k < c.n; ++k)
+            std::memcpy(b + c.piece[k].at, (char*)all.p + (c.piece[k].mem - lo), c.piece[k].n);
+        return RLBM_OK;
     }
     HIP_TRY(wait.done(), "save state");
     return RLBM_OK;
@@ -1208,8 +1237,24 @@ int rlbm_load_state(rlbm_lattice* lat, const void* buf, int on_device) {
         if (rc) return rc;
     }
     const int q = (int)((lat->host.parity0 + lat->steps_done) & 1);
+    char* stage = (char*)lat->host.pop[q ^ 1];
+    const bool same = !sl.n_scale || h.version == state_version(lat);
+    if (same) {
+        const Sections c = sections_of(lat, sl, q);
+        const bool pack = packs(sl, c) && on_device_memory(buf);
+        for (int k = 0; k < (pack ? c.first_packed : c.n); ++k)
+            HIP_TRY(get(c.piece[k].mem, c.piece[k].at, c.piece[k].n), "load state");
+        if (pack) {
+            HIP_TRY(get(stage, sl.scale, sl.total - sl.scale), "load state");
+            HIP_TRY(launch_pack(pack_of(c, sl, stage, false), nullptr), "load state");
+        }
+        HIP_TRY(wait.done(), "load state");
+        lat->state_set = true;
+        return RLBM_OK;
+    }
+    // the other version
     HIP_TRY(get(lat->d_ref, sl.ref, sl.n_ref), "load state");
-    if (sl.n_ref && h.version == 1u && state_version(lat) != 1u) {
+    if (h.version == 1u) {
         // the second copy of the shapes: [L][27] to [27][L]
         const size_t L = (size_t)lat->L;
         std::vector<double> g(L * Q);
@@ -1222,28 +1267,21 @@ int rlbm_load_state(rlbm_lattice* lat, const void* buf, int on_device) {
                 "load state");
     }
     HIP_TRY(get(lat->host.pop[q], sl.pops, sl.n_pops), "load state");
-    char* stage = (char*)lat->host.pop[q ^ 1];
-    if (packs(sl)) {
-        HIP_TRY(get(stage, sl.scale, sl.total - sl.scale), "load state");
-        HIP_TRY(launch_pack(pack_of(lat, sl, q, stage, false), nullptr), "load state");
-    } else {
-        if (direct(lat, sl, h.version)) {
-            HIP_TRY(get(lat->host.rscale[q], sl.scale, sl.n_scale), "load state");
-            if (sl.n_fscale) {
-                HIP_TRY(get(lat->host.rscale[q ^ 1], sl.scale_next, sl.n_scale), "load state");
-                HIP_TRY(get(lat->host.fscale[q], sl.fscale, sl.n_fscale), "load state");
-            }
-        } else {
-            float *sc = (float*)stage, *f = sc + (sl.n_fscale ? sl.n_scale / sizeof(float) : (size_t)lat->L - 2);
-            HIP_TRY(get(sc, sl.scale, sl.n_scale), "load state");
-            HIP_TRY(get(f, sl.fscale, sl.n_fscale), "load state");
-            Pack p{};
-            add_scales(p, lat, sl, q, sc, state_version(lat) == 2u ? sc : nullptr, f, false);
-            HIP_TRY(launch_pack(p, nullptr), "load state");
-        }
-        HIP_TRY(get(lat->host.aux, sl.aux, sl.n_aux), "load state");
-        HIP_TRY(get(lat->host.out_state, sl.out, sl.n_out), "load state");
+    // its rows of scales, through the idle population buffer: the species to
+    // both buffers, rho and rho E from behind them or apart
+    {
+        const unsigned N = (unsigned)lat->geo.N, nsp = (unsigned)lat->L - 2u, row = (unsigned)sl.rss;
+        const unsigned rss = (unsigned)lat->host.rss, fss = (unsigned)lat->host.fss;
+        float *sc = (float*)stage, *f = sc + (sl.n_fscale ? sl.n_scale / sizeof(float) : nsp);
+        HIP_TRY(get(sc, sl.scale, sl.n_scale), "load state");
+        HIP_TRY(get(f, sl.fscale, sl.n_fscale), "load state");
+        Pack p{};
+        for (int e = 0; e < 2; ++e) p.seg[p.n++] = PackSeg{sc, lat->host.rscale[e], N, nsp, row, rss};
+        p.seg[p.n++] = PackSeg{f, lat->host.fscale[q], N, 2u, sl.n_fscale ? 2u : row, fss};
+        HIP_TRY(launch_pack(p, nullptr), "load state");
     }
+    HIP_TRY(get(lat->host.aux, sl.aux, sl.n_aux), "load state");
+    HIP_TRY(get(lat->host.out_state, sl.out, sl.n_out), "load state");
     HIP_TRY(wait.done(), "load state");
     lat->state_set = true;
     return RLBM_OK;

@@ -92,10 +92,10 @@ def test_implicit_snapshot_resumes_bit_exactly(coupling, mech9):
 @pytest.mark.parametrize("species", [9, 3, 2])
 def test_snapshots_between_the_updates(species, coupling, mech9):
     """A lattice takes a snapshot of the other reaction update's lattice (a
-    linearly implicit one keeps one row of scales per node, an explicit one
-    the species' twice and f and g apart): the same populations, the same
-    bits in the next snapshot's, and runs within the storage's precision of
-    the FP64 ones."""
+    linearly implicit one keeps the scales of f and g in the species' row where
+    they fit, an explicit one apart): the same populations, the same bits in
+    the next snapshot's, and runs within the storage's precision of the FP64
+    ones."""
     rlbm = _rlbm()
     print(f"case snapshots between updates M={species} {coupling}", flush=True)
     ex = _case(species, (66, 5, 3), mech9, coupling)
@@ -106,7 +106,8 @@ def test_snapshots_between_the_updates(species, coupling, mech9):
         other = rlbm.Lattice(b, storage="f32dev").set_state()
         f64 = rlbm.Lattice(b, storage="f64").set_state()
         snap = lat.save_state()
-        assert snap[:8].view(np.uint32)[1] == (2 if a is ex else 1)
+        row = (lat.L + 3) // 4 == (lat.L + 1) // 4     # f and g fit in the species' row of scales
+        assert snap[:8].view(np.uint32)[1] == (1 if a is im and row else 2)
         other.load_state(snap)
         pops = lat.populations()
         np.testing.assert_array_equal(other.populations(), pops)
