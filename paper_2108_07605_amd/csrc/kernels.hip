@@ -1286,7 +1286,7 @@ __global__ __launch_bounds__(UPD_THREADS) __attribute__((amdgpu_waves_per_eu(W ?
 // node: temperature, relaxation rates, Stefan-Maxwell system.  The reactions
 // are dealt to the first three waves.
 //   Bound: FP64 issue and its latency (two waves per SIMD; about 15,000 vector
-// instructions per tile, which keep the SIMDs issuing 48% of the time at 2.4
+// instructions per tile, which keep the SIMDs issuing 49% of the time at 2.4
 // GHz) in FP32 storage, those and the traffic in FP64: 2.1 and 4.1 KB per node, against
 // 4.0 and 7.5 for a moments pass and a collision that each read every
 // population.  Three waves hold what one cannot, 216 registers of populations
@@ -1949,9 +1949,9 @@ __global__ __launch_bounds__(SPC_THREADS) __attribute__((amdgpu_waves_per_eu(2))
 // nine velocities.  Populations and the readers' scales are asked for ahead of
 // the barrier.  Bound by its traffic on large lattices (54 populations in and
 // out, the record, nine fields for the stencil: 512x64x64 moves 1.3 GB in FP32
-// storage, 0.36 ms) and by one tile's latency on small ones.  Against one wave
+// storage, 0.35 ms) and by one tile's latency on small ones.  Against one wave
 // per 64 nodes: 1024 nodes 14.4 -> 6.3 us, 203x53x37 (weak coupling) 105 -> 88,
-// 512x64x64 419 -> 358 (FP32) and 530 -> 496 (FP64).  Three waves per SIMD: at
+// 512x64x64 419 -> 354 (FP32) and 530 -> 493 (FP64).  Three waves per SIMD: at
 // four the registers spill (423 and 582 us at 512x64x64 without the early
 // scales).
 // ---------------------------------------------------------------------------
