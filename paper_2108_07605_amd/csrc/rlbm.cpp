@@ -1202,8 +1202,9 @@ int rlbm_save_state(rlbm_lattice* lat, void* buf, int on_device) {
     if (all.p) {
         HIP_TRY(hipMemcpyAsync(all.p, lo, hi - lo, hipMemcpyDeviceToHost, nullptr), "save state");
         HIP_TRY(wait.done(), "save state");
-        for (int k = c.first_packed; k < c.n; ++k)
-            std::memcpy(b + c.piece[k].at, (char*)all.p + (c.piece[k].mem - lo), c.piece[k].n);
+        for (int k = c.first_packed; k < c.n; ++k)   // by the runtime: it knows memory that the attributes above do not
+            HIP_TRY(hipMemcpy(b + c.piece[k].at, (char*)all.p + (c.piece[k].mem - lo), c.piece[k].n, hipMemcpyDefault),
+                    "save state");
         return RLBM_OK;
     }
     HIP_TRY(wait.done(), "save state");
