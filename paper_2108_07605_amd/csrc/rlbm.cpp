@@ -1069,8 +1069,8 @@ struct StateLayout {
     size_t n_ref, n_pops, n_scale, n_fscale, n_aux, n_out;   // bytes of each section
     size_t rss;                                              // floats per node in `scale`
 };
-uint32_t state_version(const rlbm_lattice* lat) { return flow_in_row(lat->L, lat->host.reaction) ? 1u : 2u; }
-StateLayout state_layout(const rlbm_lattice* lat, uint32_t version) {
+static uint32_t state_version(const rlbm_lattice* lat) { return flow_in_row(lat->L, lat->host.reaction) ? 1u : 2u; }
+static StateLayout state_layout(const rlbm_lattice* lat, uint32_t version) {
     StateLayout s{};
     const size_t N = (size_t)lat->geo.N, L = (size_t)lat->L, M = (size_t)lat->M;
     const bool f32 = lat->storage == RLBM_STORAGE_F32_DEV;
@@ -1100,6 +1100,7 @@ int rlbm_state_bytes(const rlbm_lattice* lat, size_t* bytes) {
     return RLBM_OK;
 }
 
+namespace {
 // The sections of a snapshot, and where they are in a lattice: copies between
 // them, sections side by side in both as one.
 struct Sections {
@@ -1123,7 +1124,7 @@ struct Sections {
     }
 };
 // first_packed: the first piece behind the populations.
-Sections sections_of(const rlbm_lattice* lat, const StateLayout& s, int q) {
+static Sections sections_of(const rlbm_lattice* lat, const StateLayout& s, int q) {
     Sections c;
     c.add(lat->d_ref, s.ref, s.n_ref);
     c.add(lat->host.pop[q], s.pops, s.n_pops);
@@ -1144,11 +1145,11 @@ Sections sections_of(const rlbm_lattice* lat, const StateLayout& s, int q) {
 // that lies between them is copied at once, if it is smaller still, and sorted
 // there.
 constexpr size_t PACK_MOST = 32u << 20, SORT_MOST = 1u << 20;
-bool several(const Sections& c) { return c.n - c.first_packed > 1; }
-bool packs(const StateLayout& s, const Sections& c) {
+static bool several(const Sections& c) { return c.n - c.first_packed > 1; }
+static bool packs(const StateLayout& s, const Sections& c) {
     return several(c) && s.total - s.scale <= std::min(s.n_pops, PACK_MOST);
 }
-bool on_device_memory(const void* buf) {
+static bool on_device_memory(const void* buf) {
     hipPointerAttribute_t a{};
     if (hipPointerGetAttributes(&a, buf) != hipSuccess) {
         (void)hipGetLastError();   // memory the runtime does not know: the host's
@@ -1156,7 +1157,7 @@ bool on_device_memory(const void* buf) {
     }
     return a.type == hipMemoryTypeDevice;
 }
-Pack pack_of(const Sections& c, const StateLayout& s, char* packed, bool save) {
+static Pack pack_of(const Sections& c, const StateLayout& s, char* packed, bool save) {
     Pack p{};
     for (int k = c.first_packed; k < c.n; ++k) {
         char *mem = c.piece[k].mem, *file = packed + (c.piece[k].at - s.scale);
@@ -1164,6 +1165,7 @@ Pack pack_of(const Sections& c, const StateLayout& s, char* packed, bool save) {
     }
     return p;
 }
+}  // namespace
 
 // The copies go one behind the other and are waited for once, on the null
 // stream, so that what the caller has queued there on a device buffer comes
@@ -1353,7 +1355,7 @@ namespace {
 struct BatchPlan {
     size_t off_t, off_table, off_blk, upload, off_flagp, off_status, total;
 };
-BatchPlan batch_plan(int k) {
+static BatchPlan batch_plan(int k) {
     BatchPlan p{};
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t at = o; o = align256(o + bytes); return at; };

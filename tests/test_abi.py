@@ -3,6 +3,7 @@ header declares, and validates descriptors.  No call here touches a GPU."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -26,6 +27,14 @@ def test_library_exports_every_declared_symbol():
     for name in names:
         assert hasattr(L, name), name
     assert set(names) == set(rlbm.EXPORTS)
+
+
+def test_library_exports_no_other_plain_name():
+    """Functions with C linkage beside the declared ones would stand in for
+    another library's of the same name in the process."""
+    out = subprocess.run(["nm", "-D", "--defined-only", rlbm.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    names = [ln.split()[-1] for ln in out.splitlines() if " T " in ln]
+    assert set(n for n in names if not n.startswith(("_Z", "_init", "_fini"))) == set(rlbm.EXPORTS)
 
 
 def test_mechanism_validation(mech9):
